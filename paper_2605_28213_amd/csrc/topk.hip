@@ -136,6 +136,35 @@ __global__ __launch_bounds__(SEL_T) void topk_selection(TopkArgs a)
     compact<SEL_T>(a, lo, hi, 0, wsum, [&](int64_t i) { return taken[i] ? 2 : 0; }, [&](int64_t i) { return row[i]; });
 }
 
+// The digit d of a histogram of nb bins with  #(keys with a larger digit) < remaining <= #(keys with digit >= d),
+// and how many of the keys with that digit are still wanted.  The caller has a barrier between the counting and
+// this call; both results are readable by every thread on return.
+template <int T>
+__device__ __forceinline__ void pick_digit(const int* hist, int nb, int remaining, int* wsum, int* digit, int* left)
+{
+    const int tid = threadIdx.x;
+    const int ch = nb >= T ? nb / T : 1;                   // bins per thread, a contiguous chunk
+    const bool active = tid * ch < nb;
+    int s = 0;
+    if (active)
+        for (int c = 0; c < ch; ++c) s += hist[tid * ch + c];
+    int total;
+    const int incl = block_scan<T>(s, wsum, &total);
+    const int above = total - incl;                         // keys in the chunks above this thread's
+    if (active && above < remaining && remaining <= above + s) {
+        int acc = above;
+        for (int d = tid * ch + ch - 1; d >= tid * ch; --d) {
+            if (acc + hist[d] >= remaining) {
+                *digit = d;
+                *left = remaining - acc;
+                break;
+            }
+            acc += hist[d];
+        }
+    }
+    __syncthreads();
+}
+
 // ---- T1 / T2: radix select ----------------------------------------------------------------------
 // NPASS histogram passes over digits of B0, B1, ... bits, most significant first (they add up to 32).
 // RESIDENT: the thread's ITEMS consecutive keys are loaded once (16 bytes at a time) and every pass
@@ -193,27 +222,7 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
             }
         }
         __syncthreads();
-        // the digit d with  #(candidates with a larger digit) < remaining <= #(candidates with digit >= d)
-        const int ch = nb >= T ? nb / T : 1;               // bins per thread, a contiguous chunk
-        const bool active = tid * ch < nb;
-        int s = 0;
-        if (active)
-            for (int c = 0; c < ch; ++c) s += hist[tid * ch + c];
-        int total;
-        const int incl = block_scan<T>(s, wsum, &total);
-        const int above = total - incl;                     // candidates in the chunks above this thread's
-        if (active && above < remaining && remaining <= above + s) {
-            int acc = above;
-            for (int d = tid * ch + ch - 1; d >= tid * ch; --d) {
-                if (acc + hist[d] >= remaining) {
-                    found_digit = d;
-                    found_remaining = remaining - acc;
-                    break;
-                }
-                acc += hist[d];
-            }
-        }
-        __syncthreads();
+        pick_digit<T>(hist, nb, remaining, wsum, &found_digit, &found_remaining);
         prefix |= (uint32_t)found_digit << shift;
         mask |= (uint32_t)(nb - 1) << shift;
         remaining = found_remaining;
@@ -239,6 +248,268 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
                    [&](int64_t i) { const uint32_t key = key_of(row[i]); return key > thr ? 2 : key == thr ? 1 : 0; },
                    [&](int64_t i) { return row[i]; });
     }
+}
+
+// ---- T1 on long rows ------------------------------------------------------------------------------
+// A row too long to be counted by 256 lanes at a stride.  One workgroup of 1024 lanes per row (no scratch is lent, so
+// rows are not split over workgroups); what bounds it is what one CU can fetch, so the row is read twice (the form with
+// 256 lanes and five passes took 460 us on 8 x 131072, k = 64; this one 27.5, 18.5 of them for k = 1, where the second
+// read is one lane's; 128 x 200000, k = 100: 1426 -> 40; 64 x 16384, k = 512: 67 -> 18) and everything else works on few keys:
+//   1. each lane keeps the largest value of four interleaved groups of elements (4096 groups in all);
+//   2. the k-th largest of the 4096 maxima is a lower bound of the row's k-th largest value (k groups each hold an
+//      element at least that large): two 11-bit digits of it, the rest zero, are bound enough;
+//   3. the row is read again, by the lanes only whose own maxima reach the bound, and the elements that reach it are
+//      listed in LDS (k = 64 of 131072 normal values: about 65; k = 2048: about 2840 of the 4096 there is room for);
+//   4. radix select on the list, a counting sort of it by index, ordered compaction.
+// A list that overflows (long runs of values equal to the threshold, rows that put the large values into few groups)
+// or k above half the groups takes the general form below: three histogram passes over the row and two passes of
+// ordered compaction, 16 bytes per lane and load.
+constexpr int LONG_T = 1024;
+constexpr int LONG_GROUPS = 4 * LONG_T;
+constexpr int LONG_CAP = 4096;                  // listed elements: 4 per lane
+constexpr int LONG_MAX_K = LONG_GROUPS / 2;
+typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));      // rows start at any element
+
+// f(four values, index of the first, how many of them exist) for every run of four that belongs to this lane,
+// 16 bytes a load, UNROLL loads in flight
+template <int UNROLL, typename F>
+__device__ __forceinline__ void for_each_of_lane(const float* row, int64_t n, F f)
+{
+    const int64_t whole = n & ~(int64_t)3;
+    int64_t i = (int64_t)threadIdx.x * 4;
+    for (; i + (int64_t)(UNROLL - 1) * LONG_GROUPS < whole; i += (int64_t)UNROLL * LONG_GROUPS) {
+        float4_u v[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) v[u] = *(const float4_u*)(row + i + (int64_t)u * LONG_GROUPS);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) f(v[u], i + (int64_t)u * LONG_GROUPS, 4);
+    }
+    for (; i < n; i += LONG_GROUPS) {
+        float4_u v = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        if (i < whole) v = *(const float4_u*)(row + i);
+        else
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (i + e < n) v[e] = row[i + e];
+        f(v, i, i < whole ? 4 : (int)(n - i));
+    }
+}
+
+struct LongShared {
+    int hist[2048];
+    uint32_t bits[LONG_CAP];                    // the listed elements' patterns, in order of arrival
+    int32_t idx[LONG_CAP];
+    uint16_t bucketed[LONG_CAP], ordered[LONG_CAP];
+    int wsum[LONG_T / 64];
+    int wcount[2][LONG_T / 64];
+    int digit, left, listed;
+};
+
+// the k-th largest of the keys held, digit by digit from the top; `passes` digits of 11, 11, 10 bits, the rest zero
+template <int ITEMS>
+__device__ __forceinline__ uint32_t select_key(LongShared& sh, const uint32_t (&key)[ITEMS], int count, int passes, int& remaining)
+{
+    const int tid = threadIdx.x;
+    uint32_t prefix = 0, mask = 0;
+    int shift = 32;
+    for (int p = 0; p < passes; ++p) {
+        const int bits = p < 2 ? 11 : 10, nb = 1 << bits;
+        shift -= bits;
+        for (int i = tid; i < nb; i += LONG_T) sh.hist[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j)
+            if (j * LONG_T + tid < count && (key[j] & mask) == prefix) atomicAdd(&sh.hist[(key[j] >> shift) & (nb - 1)], 1);
+        __syncthreads();
+        pick_digit<LONG_T>(sh.hist, nb, remaining, sh.wsum, &sh.digit, &sh.left);
+        prefix |= (uint32_t)sh.digit << shift;
+        mask |= (uint32_t)(nb - 1) << shift;
+        remaining = sh.left;
+    }
+    return prefix;
+}
+
+// any k, any values: every pass reads the row
+__device__ void long_row_general(const TopkArgs& a, const float* row, LongShared& sh)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t prefix = 0, mask = 0;
+    int remaining = (int)a.k, shift = 32;
+    for (int p = 0; p < 3; ++p) {
+        const int bits = p < 2 ? 11 : 10, nb = 1 << bits;
+        shift -= bits;
+        for (int i = tid; i < nb; i += LONG_T) sh.hist[i] = 0;
+        __syncthreads();
+        for_each_of_lane<4>(row, a.n, [&](float4_u v, int64_t, int count) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t key = key_of(v[e]);
+                if (e < count && (key & mask) == prefix) atomicAdd(&sh.hist[(key >> shift) & (nb - 1)], 1);
+            }
+        });
+        __syncthreads();
+        pick_digit<LONG_T>(sh.hist, nb, remaining, sh.wsum, &sh.digit, &sh.left);
+        prefix |= (uint32_t)sh.digit << shift;
+        mask |= (uint32_t)(nb - 1) << shift;
+        remaining = sh.left;
+    }
+    // ordered compaction: a wave owns a contiguous run of whole 256-element steps
+    const int64_t seg = (a.n + LONG_GROUPS - 1) / LONG_GROUPS * 256;
+    const int64_t lo = wave * seg < a.n ? wave * seg : a.n, hi = lo + seg < a.n ? lo + seg : a.n;
+    auto fetch = [&](int64_t i, float (&v)[4], bool (&in)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            in[u] = i + u * 64 + lane < hi;
+            v[u] = in[u] ? row[i + u * 64 + lane] : 0.0f;
+        }
+    };
+    float v[4];
+    bool in[4];
+    int gt = 0, eq = 0;
+    for (int64_t i = lo; i < hi; i += 256) {
+        fetch(i, v, in);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            gt += __popcll(__ballot(in[u] && key_of(v[u]) > prefix));
+            eq += __popcll(__ballot(in[u] && key_of(v[u]) == prefix));
+        }
+    }
+    if (lane == 0) { sh.wcount[0][wave] = gt; sh.wcount[1][wave] = eq; }
+    __syncthreads();
+    int64_t g = 0, e = 0;
+    for (int w = 0; w < wave; ++w) { g += sh.wcount[0][w]; e += sh.wcount[1][w]; }
+    int32_t* idx = a.idx + (int64_t)blockIdx.x * a.k;
+    float* val = a.val + (int64_t)blockIdx.x * a.k;
+    const uint64_t below = ((uint64_t)1 << lane) - 1;
+    for (int64_t i = lo; i < hi; i += 256) {
+        fetch(i, v, in);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t key = key_of(v[u]);
+            const uint64_t mg = __ballot(in[u] && key > prefix), me = __ballot(in[u] && key == prefix);
+            const int64_t le = e + __popcll(me & below);
+            if (in[u] && (key > prefix || (key == prefix && le < remaining))) {
+                const int64_t pos = g + __popcll(mg & below) + (le < remaining ? le : remaining);
+                if (pos < a.k) {                        // always true for NaN-free rows
+                    idx[pos] = (int32_t)(i + u * 64 + lane);
+                    val[pos] = v[u];
+                }
+            }
+            g += __popcll(mg);
+            e += __popcll(me);
+        }
+    }
+}
+
+// k <= LONG_MAX_K; false (nothing written) when the list does not hold the row's candidates
+__device__ bool long_row_filtered(const TopkArgs& a, const float* row, LongShared& sh)
+{
+    const int tid = threadIdx.x;
+    float top[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    auto larger = [](float v, float w) { return __builtin_amdgcn_fmed3f(v, w, INFINITY); };
+    for_each_of_lane<8>(row, a.n, [&](float4_u v, int64_t, int) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) top[e] = larger(v[e], top[e]);
+    });
+    uint32_t key[LONG_CAP / LONG_T];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key[e] = key_of(top[e]);
+    int remaining = (int)a.k;
+    const uint32_t bound = select_key(sh, key, LONG_GROUPS, 2, remaining);
+    bool full = false;
+    if (key[0] >= bound || key[1] >= bound || key[2] >= bound || key[3] >= bound)
+        // (four values are tested at once: with a test per element 8 x 131072, k = 64 took 40 us)
+        for_each_of_lane<8>(row, a.n, [&](float4_u v, int64_t i, int count) {
+            if (!full && key_of(larger(larger(v[0], v[1]), larger(v[2], v[3]))) >= bound)
+                for (int e = 0; e < count; ++e) {
+                    const float x = e == 0 ? v[0] : e == 1 ? v[1] : e == 2 ? v[2] : v[3];
+                    if (key_of(x) < bound) continue;
+                    const int at = atomicAdd(&sh.listed, 1);
+                    if (at >= LONG_CAP) {
+                        full = true;
+                        break;
+                    }
+                    sh.bits[at] = __float_as_uint(x);
+                    sh.idx[at] = (int32_t)(i + e);
+                }
+        });
+    __syncthreads();
+    const int listed = sh.listed;
+    if (listed > LONG_CAP || listed < a.k) return false;            // fewer than k only where NaNs hid a group's elements
+    int32_t pos[LONG_CAP / LONG_T];
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
+        const int c = j * LONG_T + tid;
+        key[j] = c < listed ? key_of(__uint_as_float(sh.bits[c])) : 0;
+        pos[j] = c < listed ? sh.idx[c] : 0;
+    }
+    remaining = (int)a.k;
+    const uint32_t thr = select_key(sh, key, listed, 3, remaining);
+    // counting sort by index: 2048 buckets of consecutive indices, then the rank among the bucket's few elements
+    int shift = 0;
+    while (((a.n - 1) >> shift) >= 2048) ++shift;
+    sh.hist[2 * tid] = sh.hist[2 * tid + 1] = 0;
+    __syncthreads();
+    int slot[LONG_CAP / LONG_T];
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
+        if (j * LONG_T + tid < listed) slot[j] = atomicAdd(&sh.hist[pos[j] >> shift], 1);
+    __syncthreads();
+    const int h0 = sh.hist[2 * tid], h1 = sh.hist[2 * tid + 1];
+    int total;
+    const int start = block_scan<LONG_T>(h0 + h1, sh.wsum, &total) - h0 - h1;
+    sh.hist[2 * tid] = start;
+    sh.hist[2 * tid + 1] = start + h0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
+        if (j * LONG_T + tid < listed) sh.bucketed[sh.hist[pos[j] >> shift] + slot[j]] = (uint16_t)(j * LONG_T + tid);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
+        if (j * LONG_T + tid < listed) {
+            const int b = pos[j] >> shift, first = sh.hist[b], last = b + 1 < 2048 ? sh.hist[b + 1] : listed;
+            int rank = 0;
+            for (int c = first; c < last; ++c) rank += sh.idx[sh.bucketed[c]] < pos[j];
+            sh.ordered[first + rank] = (uint16_t)(j * LONG_T + tid);
+        }
+    __syncthreads();
+    const int lo = tid * (LONG_CAP / LONG_T);
+    int c[LONG_CAP / LONG_T], gt = 0, eq = 0;
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
+        c[j] = lo + j < listed ? sh.ordered[lo + j] : -1;
+        key[j] = c[j] >= 0 ? key_of(__uint_as_float(sh.bits[c[j]])) : 0;
+        gt += c[j] >= 0 && key[j] > thr;
+        eq += c[j] >= 0 && key[j] == thr;
+    }
+    const int both = block_scan<LONG_T>(gt | (eq << 16), sh.wsum, &total) - (gt | (eq << 16));
+    int g = both & 0xFFFF, e = both >> 16;
+    int32_t* idx = a.idx + (int64_t)blockIdx.x * a.k;
+    float* val = a.val + (int64_t)blockIdx.x * a.k;
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
+        if (c[j] < 0) break;
+        if (key[j] > thr || (key[j] == thr && e < remaining)) {
+            const int at = g + (e < remaining ? e : remaining);
+            if (at < a.k) {
+                idx[at] = sh.idx[c[j]];
+                val[at] = __uint_as_float(sh.bits[c[j]]);
+            }
+        }
+        g += key[j] > thr;
+        e += key[j] == thr;
+    }
+    return true;
+}
+
+__global__ __launch_bounds__(LONG_T) void topk_long(TopkArgs a)
+{
+    __shared__ LongShared sh;
+    const float* row = a.x + (int64_t)blockIdx.x * a.ld;
+    if (threadIdx.x == 0) { sh.digit = 0; sh.left = 0; sh.listed = 0; }      // a row of NaNs may leave a digit unfound
+    if (a.k <= LONG_MAX_K && long_row_filtered(a, row, sh)) return;
+    long_row_general(a, row, sh);
 }
 
 constexpr int RES_ITEMS = 16;
@@ -279,6 +550,13 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
         p.threads = SEL_T; q.passes = (int32_t)(d->k < 0x7FFFFFFF ? d->k : 0x7FFFFFFF); q.lds_bytes = SEL_MAX_N + 48;
         break;
     case TOPK_T1_RADIX_SELECT:
+        // 4096 groups need an element each (17000 elements, k = 8000, beyond the filter: 74 -> 19 us all the same)
+        if (d->n > LONG_GROUPS) {
+            const bool filter = d->k <= LONG_MAX_K;
+            path = filter ? "group-maxima filter + radix-select(11+11+10), 1024 lanes" : "radix-select(11+11+10, streaming, 1024 lanes)";
+            p.threads = LONG_T; q.passes = filter ? 2 : 5; q.lds_bytes = sizeof(LongShared);
+            break;
+        }
         path = "radix-select(8+8+8+8, streaming)";
         p.threads = 256; q.passes = 5; q.lds_bytes = 256 * 4 + 24;
         break;
@@ -324,6 +602,8 @@ int topk_run(int variant, const topk_desc_t* d, const float* x, int32_t* idx, fl
     const dim3 grid((unsigned)d->batch);
     if (variant == TOPK_T0_SELECTION)
         hipLaunchKernelGGL(topk_selection, grid, dim3(SEL_T), 0, p.stream, p.a);
+    else if (variant == TOPK_T1_RADIX_SELECT && p.threads == LONG_T)
+        hipLaunchKernelGGL(topk_long, grid, dim3(LONG_T), 0, p.stream, p.a);
     else if (variant == TOPK_T1_RADIX_SELECT)
         hipLaunchKernelGGL((topk_radix<256, 1, false, 4, 8, 8, 8, 8>), grid, dim3(256), 0, p.stream, p.a);
     else if (p.items == 4)

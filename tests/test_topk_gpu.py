@@ -134,3 +134,28 @@ def test_gate_table_of_the_paper_shape():
         for r in rows:
             f.write(json.dumps(r) + "\n")
     assert rows[2]["median_us"] < rows[0]["median_us"] and rows[1]["median_us"] < rows[0]["median_us"]
+
+
+@pytest.mark.parametrize("n,k", [(4097, 1), (4097, 2048), (4098, 2049), (8191, 64), (32768, 2048), (70003, 4097), (131072, 64), (262147, 700)])
+@pytest.mark.parametrize("values", ["normal", "ascending", "few", "zeros", "neginf"])
+def test_long_rows(n, k, values):
+    """Rows beyond 4096 elements: a list of candidates that suffices, one that overflows (equal values) and k beyond
+    the filter; every length modulo 4, every row start modulo 16 bytes (odd ld)."""
+    rng = np.random.default_rng(n + k)
+    ld = n | 1
+    x = rng.standard_normal((3, ld)).astype(np.float32)
+    if values == "ascending":
+        x.sort(axis=1)
+    elif values == "few":
+        x = np.round(x * 2) / 2                          # about 15 values, both zeros among them
+    elif values == "zeros":
+        x = np.where(rng.random((3, ld)) < 0.999, np.float32(0.0), x).astype(np.float32)
+    elif values == "neginf":
+        x = np.where(rng.random((3, ld)) < 0.995, np.float32(-np.inf), x).astype(np.float32)
+    x[:, n:] = 1e30
+    rc, idx, val, q = run_state(1, x, n, k)
+    assert rc == gemm.GEMM_OK and q.threads == 1024
+    # the oracle counts ranks in O(n^2); a stable sort of the negated row is the same selection (one of the oracle's pins)
+    ridx = np.sort(np.argsort(-x[:, :n], axis=1, kind="stable")[:, :k], axis=1)
+    np.testing.assert_array_equal(idx, ridx)
+    np.testing.assert_array_equal(val.view(np.uint32), np.take_along_axis(x, ridx, 1).view(np.uint32))
