@@ -160,6 +160,11 @@ inline bool tail_element_in_last_page(const void* base, int64_t elems, int64_t l
     return (end & 4095u) != 0;
 }
 hipError_t launch_k4_thin_row_major_b(const Args& a);
+// The masked state's direct-to-LDS form (fp32, bf16, fp16; any layout and alignment): whether it takes a product, its
+// launcher (tile: 64 or 128) and the slabs its ring holds.
+bool k4_direct_applies(const Args& a);
+hipError_t launch_k4_direct(const Args& a, int tile);
+constexpr int K4_DIRECT_STAGES_64 = 4, K4_DIRECT_STAGES_128 = 2;
 
 hipError_t launch_k0(const Args& a);
 hipError_t launch_valu_tiled(int variant, int path, const Args& a);

@@ -35,8 +35,8 @@ static hipError_t launch_fast(const Args& a)
     return hipGetLastError();
 }
 
-// The masked kernel takes 64 x 64 tiles (one 32 x 32 accumulator tile per wave) when 128 x 128 tiles would
-// leave most CUs idle (fp32 256^3: 4 workgroups took 37 us).
+// The masked state takes 64 x 64 tiles (one 32 x 32 accumulator tile per wave) when 128 x 128 tiles would
+// leave most CUs idle (fp32 256^3, element-by-element kernel: 4 workgroups took 37 us, 16 of them 15 us).
 static int masked_tile(const Args& a)
 {
     const int64_t t = ((a.M + MASKED_BM - 1) / MASKED_BM) * ((a.N + MASKED_BN - 1) / MASKED_BN) * a.batch;
@@ -55,6 +55,8 @@ static hipError_t launch_masked_tile(const Args& a, int vec_mask)
 template <typename IN>
 static hipError_t launch_masked(const Args& a, int vec_mask)
 {
+    // element by element only what the direct-to-LDS form cannot address (fp32 2048^3: 205 against 136 us, fp16 1000^3: 31 / 8 us)
+    if (k4_direct_applies(a)) return launch_k4_direct(a, masked_tile(a));
     return masked_tile(a) == 64 ? launch_masked_tile<IN, 64>(a, vec_mask) : launch_masked_tile<IN, MASKED_BM>(a, vec_mask);
 }
 
@@ -439,6 +441,10 @@ Geometry geometry_k4(int path, const Args& a)
     }
     const int bt = masked_tile(a);
     const int64_t g = ((a.M + bt - 1) / bt) * ((a.N + bt - 1) / bt) * a.batch;
+    if (k4_direct_applies(a)) {
+        const int stages = bt == 64 ? K4_DIRECT_STAGES_64 : K4_DIRECT_STAGES_128;
+        return Geometry{bt, bt, ROW_BYTES / es, MASKED_WM * MASKED_WN * 64, stages, stages * 2 * bt * ROW_BYTES, g};
+    }
     return Geometry{bt, bt, ROW_BYTES / es, MASKED_WM * MASKED_WN * 64, 2, 4 * bt * ROW_BYTES, g};
 }
 

@@ -131,7 +131,8 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
         if "+thin(" in path or "+split(" in path:
             pats.append(r"k4_thin_brow<gl::ThinCfg<%s, " % dt)
         return pats
-    return [r"k4_mfma_masked<%s, %d, %d, " % (dt, bm, bn)]
+    # (the direct-to-LDS form wherever it applies, the element-by-element one otherwise)
+    return [r"k4_mfma_(direct<gl::DirectCfg<%s, %d, |masked<%s, %d, %d, )" % (dt, bm, dt, bm, bn)]
 
 
 def compile_leg(rebuild: bool = False) -> dict:
