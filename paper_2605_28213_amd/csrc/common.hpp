@@ -160,11 +160,12 @@ inline bool tail_element_in_last_page(const void* base, int64_t elems, int64_t l
     return (end & 4095u) != 0;
 }
 hipError_t launch_k4_thin_row_major_b(const Args& a);
-// The masked state's direct-to-LDS form (fp32, bf16, fp16; any layout and alignment): whether it takes a product, its
-// launcher (tile: 64 or 128) and the slabs its ring holds.
+// The masked state's direct-to-LDS form (fp32, bf16, fp16; any layout and alignment): whether it takes a product, the
+// form it runs in (side of the tile, workgroups per tile and direction, slabs of the LDS ring) and its launcher.
+struct DirectForm { int tile, parts, stages; };
 bool k4_direct_applies(const Args& a);
-hipError_t launch_k4_direct(const Args& a, int tile);
-constexpr int K4_DIRECT_STAGES_64 = 4, K4_DIRECT_STAGES_128 = 2;
+DirectForm k4_direct_form(const Args& a);
+hipError_t launch_k4_direct(const Args& a);
 
 hipError_t launch_k0(const Args& a);
 hipError_t launch_valu_tiled(int variant, int path, const Args& a);
@@ -183,6 +184,7 @@ Geometry geometry_k0(const Args& a);
 Geometry geometry_valu_tiled(int variant, int path, const Args& a);
 Geometry geometry_k3_async(const Args& a);
 Geometry geometry_k4(int path, const Args& a);
+Geometry geometry_k4_direct(const Args& a);
 Geometry geometry_k4_conv(const Args& a);
 
 }  // namespace gl

@@ -11,6 +11,7 @@ bool k4_direct_applies(const Args& a)
     if (a.in_dtype == GEMM_FP8_E4M3 || a.flags != 0 || a.K <= 0) return false;
     const int es = elem_size(a.in_dtype);
     const int64_t ke = ROW_BYTES / es;
+    if (((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch >= ((int64_t)1 << 29)) return false;      // (the grid, quarters included)
     auto fits = [&](const void* p, int64_t batch_stride, int64_t sr, int64_t sk, int64_t rows) {
         const bool kc = sk == 1;
         if (kc ? sr * es > ((int64_t)1 << 22) || a.K * es > ((int64_t)1 << 30) : (a.K + 2 * ke) * sk * es >= ((int64_t)1 << 31)) return false;
@@ -21,39 +22,75 @@ bool k4_direct_applies(const Args& a)
     return fits(a.A, a.stride_a, a.a_si, a.a_sk, a.M) && fits(a.B, a.stride_b, a.b_sj, a.b_sk, a.N);
 }
 
+// Which form multiplies a product: by how many tiles it has for the 256 CUs.
+//   fp32 (row-major A and B; the matrix pipe bounds it, so no CU may be idle): quarters of 64-tiles up to 192 tiles
+//     (512^3, 64 tiles: 7.0 against 13.4 us; 2300 x 300 x 2300, 180: 36 / 48; 777 x 1111 x 555, 234: 17.5 / 16.2), whole
+//     64-tiles beyond, two slabs of LDS each so that five workgroups share a CU and fill each other's barriers
+//     (2048^3: 126 us against 137 with 128-tiles; 2300^3: 208 / 266; with three slabs 171 / 233).
+//   two-byte types (loads and barriers bound it): quarters up to 96 tiles of 64 (200 x 300 x 4000, 20: 13.4 against
+//     20.1 us; 1000^3, 256: 14.3 / 8.7), whole 64-tiles with four slabs below 128 tiles of 128, then 128-tiles: one
+//     workgroup per CU with four slabs up to 256 of them (4300 x 700 x 4300, 204: 47 against 63 us with 64-tiles and 59
+//     with two slabs; 1500^3, 144: 23.1 / 24.3 / 26.3), two with two slabs beyond (3000 x 2000 x 4000, 384: 61 against 82 us).
+DirectForm k4_direct_form(const Args& a)
+{
+    const int64_t t64 = ((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch, t128 = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
+    if (a.in_dtype == GEMM_F32) return t64 <= 192 ? DirectForm{64, 2, 4} : DirectForm{64, 1, 2};
+    if (t64 <= 96) return DirectForm{64, 2, 4};
+    if (t128 < 128) return DirectForm{64, 1, 4};
+    return t128 <= 256 ? DirectForm{128, 1, 4} : DirectForm{128, 1, 2};
+}
+
+// Tiles of a product, and the workgroups they are launched as (quarters: padded to groups of eight tiles).
+static int64_t direct_tiles(const Args& a, const DirectForm& f) { return ((a.M + f.tile - 1) / f.tile) * ((a.N + f.tile - 1) / f.tile) * a.batch; }
+static int64_t direct_grid(const Args& a, const DirectForm& f) { return f.parts == 2 ? (direct_tiles(a, f) + 7) / 8 * 32 : direct_tiles(a, f); }
+
+Geometry geometry_k4_direct(const Args& a)
+{
+    const DirectForm f = k4_direct_form(a);
+    return Geometry{f.tile, f.tile, ROW_BYTES / elem_size(a.in_dtype), 256, f.stages, f.stages * 2 * (f.tile / f.parts) * ROW_BYTES, direct_grid(a, f)};
+}
+
 template <typename CFG>
 static hipError_t launch_cfg(const Args& a)
 {
+    const DirectForm f{CFG::TILE, CFG::PARTS, CFG::STAGES};
     const int tiles_m = (int)((a.M + CFG::TILE - 1) / CFG::TILE), tiles_n = (int)((a.N + CFG::TILE - 1) / CFG::TILE);
     const int eo = a.out_dtype == GEMM_F32 ? 4 : 2;
     const bool vec_c = ((uintptr_t)a.C % 16 == 0) && (a.ldc * eo) % 16 == 0 && (a.batch <= 1 || (a.stride_c * eo) % 16 == 0);
-    hipLaunchKernelGGL(k4_mfma_direct<CFG>, dim3((unsigned)((int64_t)tiles_m * tiles_n * a.batch)), dim3(CFG::T), 0, a.stream, a, tiles_m, tiles_n,
-                       vec_c ? (int)FAST_VEC_C : 0);
+    hipLaunchKernelGGL(k4_mfma_direct<CFG>, dim3((unsigned)direct_grid(a, f)), dim3(CFG::T), 0, a.stream, a, tiles_m, tiles_n,
+                       (int)direct_tiles(a, f), vec_c ? (int)FAST_VEC_C : 0);
     return hipGetLastError();
 }
 
-template <typename IN, int TILE, int STAGES>
+template <typename IN, int TILE, int PARTS, int STAGES>
 static hipError_t launch_layout(const Args& a)
 {
     const bool ka = a.a_sk == 1, kb = a.b_sk == 1;
-    if (ka && kb) return launch_cfg<DirectCfg<IN, TILE, STAGES, true, true>>(a);
-    if (ka) return launch_cfg<DirectCfg<IN, TILE, STAGES, true, false>>(a);
-    if (kb) return launch_cfg<DirectCfg<IN, TILE, STAGES, false, true>>(a);
-    return launch_cfg<DirectCfg<IN, TILE, STAGES, false, false>>(a);
+    if (ka && kb) return launch_cfg<DirectCfg<IN, TILE, PARTS, STAGES, true, true>>(a);
+    if (ka) return launch_cfg<DirectCfg<IN, TILE, PARTS, STAGES, true, false>>(a);
+    if (kb) return launch_cfg<DirectCfg<IN, TILE, PARTS, STAGES, false, true>>(a);
+    return launch_cfg<DirectCfg<IN, TILE, PARTS, STAGES, false, false>>(a);
 }
 
 template <typename IN>
-static hipError_t launch_tile(const Args& a, int tile)
+static hipError_t launch_form(const Args& a)
 {
-    return tile == 64 ? launch_layout<IN, 64, K4_DIRECT_STAGES_64>(a) : launch_layout<IN, 128, K4_DIRECT_STAGES_128>(a);
+    const DirectForm f = k4_direct_form(a);
+    if (f.parts == 2) return launch_layout<IN, 64, 2, 4>(a);
+    if constexpr (IN::BYTES == 4) {
+        return launch_layout<IN, 64, 1, 2>(a);
+    } else {
+        if (f.tile == 64) return launch_layout<IN, 64, 1, 4>(a);
+        return f.stages == 4 ? launch_layout<IN, 128, 1, 4>(a) : launch_layout<IN, 128, 1, 2>(a);
+    }
 }
 
-hipError_t launch_k4_direct(const Args& a, int tile)
+hipError_t launch_k4_direct(const Args& a)
 {
     switch (a.in_dtype) {
-    case GEMM_F32: return launch_tile<F32>(a, tile);
-    case GEMM_BF16: return launch_tile<BF16>(a, tile);
-    case GEMM_F16: return launch_tile<F16>(a, tile);
+    case GEMM_F32: return launch_form<F32>(a);
+    case GEMM_BF16: return launch_form<BF16>(a);
+    case GEMM_F16: return launch_form<F16>(a);
     default: return hipErrorInvalidValue;
     }
 }

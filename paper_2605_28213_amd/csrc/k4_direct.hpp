@@ -5,7 +5,7 @@
 // into dwords in registers, so its loads are waited for before the slab they should hide behind.  Here every operand
 // travels global -> LDS with 16-byte buffer loads, in the order it has in memory:
 //   K contiguous:   rows of 128 bytes of K, chunks swizzled as in k4_mfma_fast; operand reads are ds_read_b128
-//   rows contiguous (row-major B, column-major A): lines of one k each, TILE elements long; two-byte types read their
+//   rows contiguous (row-major B, column-major A): lines of one k each, as long as the workgroup's rows; two-byte types read their
 //                   fragments with the transposing ds_read_b64_tr_b16 (see RingCfg for the instruction), fp32, whose
 //                   matrix instruction takes one k per lane, with four ds_read_b32
 // Loads are issued from inline assembly with the wait states k4_ring.hpp explains (they stand outside any hand-placed
@@ -22,38 +22,48 @@
 
 namespace gl {
 
-// A_KC, B_KC: K is contiguous in that operand.
-template <typename IN, int TILE_, int STAGES_, bool A_KC_, bool B_KC_>
+// A_KC, B_KC: K is contiguous in that operand.  A tile of 64 or 128 belongs to a workgroup of 2 x 2 waves, or (PARTS = 2,
+// 64-tiles) to four workgroups that take a 32 x 32 quarter each: its four waves then take one of a slab's four k-steps
+// each and add their sums in LDS at the end, so that a product with few tiles has work for every CU.
+template <typename IN, int TILE_, int PARTS_, int STAGES_, bool A_KC_, bool B_KC_>
 struct DirectCfg {
     using In = IN;
-    static constexpr int TILE = TILE_, STAGES = STAGES_, T = 256;
-    static constexpr bool A_KC = A_KC_, B_KC = B_KC_;
-    static constexpr int REGION = TILE_ * ROW_BYTES, STAGE = 2 * REGION, LDS_BYTES = STAGES_ * STAGE;
-    static constexpr int TM = TILE_ / 64;                 // 32 x 32 accumulator tiles per wave and direction (2 x 2 waves)
+    static constexpr int TILE = TILE_, PARTS = PARTS_, STAGES = STAGES_, T = 256;
+    static constexpr bool A_KC = A_KC_, B_KC = B_KC_, SPLIT = PARTS_ == 2;
+    static constexpr int SIDE = TILE_ / PARTS_;           // rows and columns of a workgroup
+    static constexpr int REGION = SIDE * ROW_BYTES, STAGE = 2 * REGION, LDS_BYTES = STAGES_ * STAGE;
+    static constexpr int TM = SPLIT ? 1 : SIDE / 64;      // 32 x 32 accumulator tiles per wave and direction
+    static constexpr int SUM_PITCH = 36;                  // floats per row of a wave's partial sums (SPLIT)
     static_assert(IN::BYTES == 2 || IN::BYTES == 4, "fp32 and the two-byte types");
-    static_assert(4 * 32 * (TM * 128 + 16) <= LDS_BYTES, "epilogue staging must fit");
+    static_assert(PARTS_ == 1 || SIDE == 32, "quarters of a 64-tile");
+    static_assert((SPLIT ? 4 * 32 * SUM_PITCH * 4 : 4 * 32 * (TM * 128 + 16)) <= LDS_BYTES, "the epilogue reuses the slabs");
 };
 
 template <typename CFG>
-__global__ __launch_bounds__(CFG::T, CFG::LDS_BYTES <= 80 * 1024 ? 2 : 1) void k4_mfma_direct(Args a, int tiles_m, int tiles_n, int flags)
+__global__ __launch_bounds__(CFG::T, CFG::LDS_BYTES <= 80 * 1024 ? 2 : 1) void k4_mfma_direct(Args a, int tiles_m, int tiles_n, int total, int flags)
 {
     using IN = typename CFG::In;
-    constexpr int TILE = CFG::TILE, S = CFG::STAGES, REGION = CFG::REGION, STAGE = CFG::STAGE, TM = CFG::TM;
+    constexpr int SIDE = CFG::SIDE, S = CFG::STAGES, REGION = CFG::REGION, STAGE = CFG::STAGE, TM = CFG::TM;
     constexpr int ES = IN::BYTES, KE = ROW_BYTES / ES, V = 16 / ES;
     constexpr int NK = CHUNKS / 2;                        // k-steps per slab: one 16-byte chunk per lane half
-    constexpr int LD = TILE / 32;                         // direct loads per wave, operand and slab
-    constexpr int LINE = TILE * ES, CPL = LINE / 16, LPB = 1024 / LINE;   // rows-contiguous form: bytes and chunks per line, lines per load
+    constexpr int LD = SIDE / 32;                         // direct loads per wave, operand and slab
+    constexpr int LINE = SIDE * ES, CPL = LINE / 16, LPB = 1024 / LINE;   // rows-contiguous form: bytes and chunks per line, lines per load
     constexpr int SLACK = ES == 2 ? 2 : 0;                // the dword of an odd-length last row (see tail_element_in_last_page)
     __shared__ __attribute__((aligned(1024))) char lds[CFG::LDS_BYTES];
 
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = CFG::SPLIT ? 0 : wave >> 1, wn = CFG::SPLIT ? 0 : wave & 1;
     int64_t b;
     int tm, tn;
-    tile_of<8>(blockIdx.x, (int)gridDim.x, tiles_m, tiles_n, b, tm, tn);
+    // (workgroup ids are dealt to the 8 XCDs in turn: a tile's quarters are 8 ids apart, on the same XCD, one after the
+    // other; the grid is padded to whole groups of 8 tiles, and a workgroup past the last tile leaves as a whole)
+    const int pid = CFG::SPLIT ? (int)((blockIdx.x >> 5) * 8 + (blockIdx.x & 7)) : (int)blockIdx.x, quarter = (int)(blockIdx.x >> 3) & 3;
+    if (CFG::SPLIT && pid >= total) return;
+    tile_of<8>(pid, total, tiles_m, tiles_n, b, tm, tn);
     b = __builtin_amdgcn_readfirstlane((int)b);
-    const int64_t m0 = (int64_t)tm * TILE, n0 = (int64_t)tn * TILE;
+    const int64_t m0 = (int64_t)tm * CFG::TILE + (CFG::SPLIT ? (quarter >> 1) * SIDE : 0), n0 = (int64_t)tn * CFG::TILE + (CFG::SPLIT ? (quarter & 1) * SIDE : 0);
+    if (CFG::SPLIT && (m0 >= a.M || n0 >= a.N)) return;         // a quarter outside C
 
     typedef __attribute__((ext_vector_type(4))) int rsrc_t;
     // one operand: element strides along its rows (M or N) and along K, its number of rows, the tile's first row
@@ -71,9 +81,9 @@ __global__ __launch_bounds__(CFG::T, CFG::LDS_BYTES <= 80 * 1024 ? 2 : 1) void k
     // for row L/8 the chunk whose swizzled place is L%8.  Rows contiguous: LPB lines a block, lane L fetches for line
     // L/CPL the chunk kept at L%CPL; two-byte lines are swizzled so that the four lines a transposing read touches lie
     // in different quarters of the banks (lines of 256 bytes: chunk ^ 4 (k % 4); of 128 bytes, which alternate between
-    // the halves by themselves: chunk ^ 4 (k / 2 % 2); lines of fp32 are read whole and need none).
+    // the halves by themselves: chunk ^ 4 (k / 2 % 2); of 64 bytes: none; lines of fp32 are read whole and need none).
     const int gchunk = (lane & 7) ^ swz((lane >> 3) + 8 * (wave & 1));
-    auto line_swz = [](int k) { return ES == 4 ? 0 : LINE == 256 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); };
+    auto line_swz = [](int k) { return ES == 4 || LINE == 64 ? 0 : LINE == 256 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); };
     const int lline = lane / CPL, lchunk = (lane % CPL) ^ line_swz(lline);
     const int voff_a = (int)((CFG::A_KC ? (lane >> 3) * a.a_si + gchunk * V : lline * a.a_sk + lchunk * V) * ES);
     const int voff_b = (int)((CFG::B_KC ? (lane >> 3) * a.b_sj + gchunk * V : lline * a.b_sk + lchunk * V) * ES);
@@ -180,7 +190,8 @@ __global__ __launch_bounds__(CFG::T, CFG::LDS_BYTES <= 80 * 1024 ? 2 : 1) void k
         asm volatile("" ::: "memory");
         if (s + S - 1 < nslab) issue(s + S - 1, in_stage);      // into the slab every wave has just left
 #pragma unroll
-        for (int ks = 0; ks < NK; ++ks) {
+        for (int k = 0; k < (CFG::SPLIT ? 1 : NK); ++k) {
+            const int ks = CFG::SPLIT ? wave : k;
             u32x4_t fa[TM], fb[TM];
 #pragma unroll
             for (int i = 0; i < TM; ++i) fa[i] = fragment(kc_a{}, stage, wm * 32 * TM + i * 32, ks);
@@ -205,6 +216,40 @@ __global__ __launch_bounds__(CFG::T, CFG::LDS_BYTES <= 80 * 1024 ? 2 : 1) void k
     }
     __syncthreads();
 
+    if constexpr (CFG::SPLIT) {
+        // accumulator register 4 g + c of a lane: row lane % 32, column 8 g + 4 (lane / 32) + c; one thread adds and
+        // stores four columns of a row
+        float* sum = (float*)lds;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *(f32x4_t*)(sum + (wave * 32 + lrow) * CFG::SUM_PITCH + 8 * g + 4 * lhalf) =
+                f32x4_t{acc[0][0][4 * g], acc[0][0][4 * g + 1], acc[0][0][4 * g + 2], acc[0][0][4 * g + 3]};
+        __syncthreads();
+        const int64_t gi = m0 + (t >> 3), gj = n0 + 4 * (t & 7);
+        if (gi >= a.M || gj >= a.N) return;
+        const float sc = batch_scale(a, b);
+        f32x4_t v = {0, 0, 0, 0};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v += *(const f32x4_t*)(sum + (w * 32 + (t >> 3)) * CFG::SUM_PITCH + 4 * (t & 7));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = v[c] * sc + (a.bias && gj + c < a.N ? a.bias[gj + c] : 0.0f);
+        const int64_t at = b * a.stride_c + gi * a.ldc + gj;
+        if ((flags & FAST_VEC_C) && gj + 4 <= a.N) {           // C's rows are 16-byte aligned: so are (or 8-byte, two-byte types) four columns
+            if (a.out_dtype == GEMM_F32) {
+                *(f32x4_t*)((float*)a.C + at) = v;
+            } else {
+                uint64_t w = 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w |= (uint64_t)(a.out_dtype == GEMM_BF16 ? encode_bf16(v[c]) : encode_f16(v[c])) << (16 * c);
+                *(uint64_t*)((uint16_t*)a.C + at) = w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (gj + c < a.N) store_out(a.C, at + c, v[c], a.out_dtype);
+        }
+        return;
+    }
     char* park = lds + wave * (32 * (TM * 128 + 16));
     const int64_t row0 = m0 + wm * 32 * TM, col0 = n0 + wn * 32 * TM;
     const bool vec_ok = (flags & FAST_VEC_C) != 0;

@@ -55,8 +55,8 @@ static hipError_t launch_masked_tile(const Args& a, int vec_mask)
 template <typename IN>
 static hipError_t launch_masked(const Args& a, int vec_mask)
 {
-    // element by element only what the direct-to-LDS form cannot address (fp32 2048^3: 205 against 136 us, fp16 1000^3: 31 / 8 us)
-    if (k4_direct_applies(a)) return launch_k4_direct(a, masked_tile(a));
+    // element by element only what the direct-to-LDS form cannot address (fp32 2048^3: 205 against 126 us, fp16 1000^3: 31 / 8 us)
+    if (k4_direct_applies(a)) return launch_k4_direct(a);
     return masked_tile(a) == 64 ? launch_masked_tile<IN, 64>(a, vec_mask) : launch_masked_tile<IN, MASKED_BM>(a, vec_mask);
 }
 
@@ -439,12 +439,9 @@ Geometry geometry_k4(int path, const Args& a)
             return Geometry{bt, bt, ROW_BYTES / es, 256, FastK4SmallDeep<BF16>::DEPTH, FastK4SmallDeep<BF16>::LDS_BYTES, g};
         return Geometry{bt, bt, ROW_BYTES / es, 256, 2, small ? FastK4Small<BF16>::LDS_BYTES : FastK4<BF16>::LDS_BYTES, g};
     }
+    if (k4_direct_applies(a)) return geometry_k4_direct(a);
     const int bt = masked_tile(a);
     const int64_t g = ((a.M + bt - 1) / bt) * ((a.N + bt - 1) / bt) * a.batch;
-    if (k4_direct_applies(a)) {
-        const int stages = bt == 64 ? K4_DIRECT_STAGES_64 : K4_DIRECT_STAGES_128;
-        return Geometry{bt, bt, ROW_BYTES / es, MASKED_WM * MASKED_WN * 64, stages, stages * 2 * bt * ROW_BYTES, g};
-    }
     return Geometry{bt, bt, ROW_BYTES / es, MASKED_WM * MASKED_WN * 64, 2, 4 * bt * ROW_BYTES, g};
 }
 
