@@ -114,6 +114,7 @@ inline bool dtype_pair_supported(int in, int out)
 // (gemm_api.hip) has already proven legal for these arguments.
 enum ValuPath { VALU_SCALAR = 0, VALU_VEC16 = 1, VALU_ASYNC = 4 };    // (K2/K3 paths 0..3: bitmask of operands loaded 16 bytes at a time)
 enum MfmaPath { MFMA_ELEMENTWISE = 0, MFMA_VEC16 = 1, MFMA_SKINNY = 2, MFMA_PACKED = 3, MFMA_SPLITK = 4, MFMA_SKINNY_N = 5, MFMA_VEC16_BROW = 6, MFMA_THIN_BROW = 7 };
+constexpr int MFMA_PACKED_IN_PLACE = 4;   // beside the packed path's mask of operands used in place: neither is rewritten, see k4_direct_beats_packing
 
 // Workspace of the packed K4 path: both operands rewritten as [rows][Kp], Kp = K rounded up to a slab.
 int64_t k4_packed_k(const Args& a);
@@ -165,6 +166,7 @@ hipError_t launch_k4_thin_row_major_b(const Args& a);
 struct DirectForm { int tile, parts, stages; };
 bool k4_direct_applies(const Args& a);
 DirectForm k4_direct_form(const Args& a);
+bool k4_direct_beats_packing(const Args& a);     // in place rather than through the packed path, with scratch lent
 hipError_t launch_k4_direct(const Args& a);
 
 hipError_t launch_k0(const Args& a);

@@ -248,7 +248,10 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
         } else if (can_pack && d->workspace != nullptr) {
             // the caller lent scratch: repair the violated conditions by packing, then run the fast kernel
             p.path = MFMA_PACKED | (keep << 8);
-            snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds%s%s", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "",
+            if (k4_direct_beats_packing(a)) {      // ... or, small enough, multiply what lies there as it lies there (the scratch stays unused)
+                p.path |= MFMA_PACKED_IN_PLACE << 8;
+                snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds-in-place", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "");
+            } else snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds%s%s", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "",
                      k4_fast_is_persistent(MFMA_PACKED, a) ? "(persistent)" : "",
                      k4_splits_m_tail(a) ? "+stream(M-tail)" : "");
             path = splitk_path;
@@ -259,7 +262,7 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
             path = va && vb ? "mfma32-vec16-masked" : va ? "mfma32-vec16(A)+elementwise-masked(B)"
                             : vb ? "mfma32-elementwise-masked(A)+vec16(B)" : "mfma32-elementwise-masked";
         }
-        g = geometry_k4(p.path & 0xFF, a);
+        g = (p.path & 0xFF) == MFMA_PACKED && (p.path >> 8 & MFMA_PACKED_IN_PLACE) ? geometry_k4_direct(a) : geometry_k4(p.path & 0xFF, a);
         break;
     }
     }

@@ -40,6 +40,16 @@ DirectForm k4_direct_form(const Args& a)
     return t128 <= 256 ? DirectForm{128, 1, 4} : DirectForm{128, 1, 2};
 }
 
+// Packing moves (M + N) K elements once more and adds one or two launches; the fast kernel behind it multiplies about a
+// fifth faster than the forms here.  bf16, packed against in place: 1000 x 1000 x 200 19.6 / 4.8 us, 1500 x 264 x 4000
+// 47.6 / 20.7, 2000 x 2056 x 2000 45 / 33, 4096 x 2048 x 2048 47 / 37 (one operand packed), 2048 x 2048 x 4096 64 / 47
+// (both), and the other way round 3000 x 3000 x 5000 128 / 152, 5000 x 3000 x 3000 99 / 126, 4096 x 4096 x 6000 181 / 201:
+// the line lies between 1.7e10 and 4.5e10 multiply-adds.  Measured on single products; batches keep the packed path.
+bool k4_direct_beats_packing(const Args& a)
+{
+    return a.batch == 1 && k4_direct_applies(a) && (double)a.M * (double)a.N * (double)a.K <= 2.5e10;
+}
+
 // Tiles of a product, and the workgroups they are launched as (quarters: padded to groups of eight tiles).
 static int64_t direct_tiles(const Args& a, const DirectForm& f) { return ((a.M + f.tile - 1) / f.tile) * ((a.N + f.tile - 1) / f.tile) * a.batch; }
 static int64_t direct_grid(const Args& a, const DirectForm& f) { return f.parts == 2 ? (direct_tiles(a, f) + 7) / 8 * 32 : direct_tiles(a, f); }

@@ -240,6 +240,12 @@ int k4_splitk_factor(const Args& a)
 
 size_t k4_splitk_workspace_bytes(const Args& a, int splits) { return (size_t)splits * (size_t)(a.M * a.N) * 4; }
 
+// One row of 128-tiles (at most 128 rows of A): each K range of each tile reads a part of B of its own.
+static bool k4_splitk_rotates(const Args& p)
+{
+    return p.flags == GEMM_FLAG_TILE_128 && p.M <= 128 && !k4_uses_ring(p) && !k4_small_tiles_deep(p);
+}
+
 template <typename IN>
 static hipError_t launch_splitk(const Args& a)
 {
@@ -253,7 +259,7 @@ static hipError_t launch_splitk(const Args& a)
     p.out_dtype = GEMM_F32;
     p.scale_a = p.scale_b = nullptr; p.bias = nullptr;
     p.flags = (k4_small_tiles(a) ? GEMM_FLAG_TILE_128 : GEMM_FLAG_TILE_256) | (a.flags & K4_NEUTRAL_FLAGS);   // the tile the product itself would get
-    hipError_t e = launch_fast_any<IN>(p);
+    hipError_t e = k4_splitk_rotates(p) ? launch_fast<FastCfgRot<IN>>(p) : launch_fast_any<IN>(p);
     if (e != hipSuccess) return e;
     const int64_t threads = a.M * ((a.N + 3) / 4);
     hipLaunchKernelGGL(k4_splitk_reduce<IN>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, a.stream, a, (const float*)a.workspace, splits);
@@ -335,6 +341,7 @@ static hipError_t launch_packed(const Args& a, int keep_mask)
 hipError_t launch_k4(int path, const Args& a)
 {
     const int kind = path & 0xFF, vec_mask = (path >> 8) & 3;   // (packed path: the mask of operands used in place)
+    if (kind == MFMA_PACKED && (path >> 8 & MFMA_PACKED_IN_PLACE)) return launch_k4_direct(a);
     if (kind == MFMA_PACKED) {
         switch (a.in_dtype) {
         case GEMM_BF16: return launch_packed<BF16>(a, vec_mask);

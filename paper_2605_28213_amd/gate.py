@@ -106,6 +106,8 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
         return [r"k4_stream<gl::StreamCfg<%s, %d, " % (dt, threads // 64)]
     if path.startswith("mfma16-thin"):
         return [r"k4_thin_brow<gl::ThinCfg<%s, %d, %d, " % (dt, 1 if bm <= 16 else 2 if bm <= 32 else 4, bn)]
+    if path.endswith("-in-place"):
+        return [r"k4_mfma_direct<gl::DirectCfg<%s, %d, " % (dt, bm)]
     if "direct-to-lds" in path:
         swz = "false" if flags & gemm.GEMM_FLAG_DEOPT_NO_SWIZZLE else "true"
         ovl = "false" if flags & gemm.GEMM_FLAG_DEOPT_NO_OVERLAP else "true"
@@ -119,7 +121,8 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
             # (two-byte types on 256-tiles with none of the switches multiply with the 16x16x32 instruction)
             mi16 = ("true" if in_dtype in (gen.BF16, gen.F16) and bm == 256 and not (flags & (gemm.GEMM_FLAG_DEOPT_NO_SWIZZLE |
                     gemm.GEMM_FLAG_DEOPT_NO_OVERLAP | gemm.GEMM_FLAG_MFMA_32X32)) else "false")
-            pats.append(r"k4_mfma_fast<gl::FastCfg<%s, %d, \d+, %s, %s, \d+, false, %s>" % (dt, bm, swz, ovl, mi16))
+            rot = r"|gl::FastCfgRot<%s>" % dt if "splitK" in path and bm == 128 else ""      # (one row of tiles: the rotated K walk)
+            pats.append(r"k4_mfma_fast<(gl::FastCfg<%s, %d, \d+, %s, %s, \d+, false, %s>%s)" % (dt, bm, swz, ovl, mi16, rot))
         if "packed" in path:
             pats.append(r"k4_pack_(rows|transpose)<%s>" % dt)
         if "splitK" in path:

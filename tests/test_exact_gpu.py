@@ -449,3 +449,12 @@ def test_masked_state_in_every_layout_is_exact(dtype, la, lb):
         q = run_exact(inp, "masked", exact_path=False)
         t64, t128 = (-(-M // t) * -(-N // t) * batch for t in (64, 128))
         assert q.bm == (128 if dtype != gen.F32 and t64 > 96 and t128 >= 128 else 64)
+
+
+@pytest.mark.parametrize("dtype", [gen.BF16, gen.F16])
+@pytest.mark.parametrize("la,lb", [(ROW, ROW), (COL, ROW), (COL, COL), (ROW, COL)])
+def test_small_products_with_scratch_lent_are_read_in_place_and_exact(dtype, la, lb):
+    """Up to 2.5e10 multiply-adds the operands are multiplied as they lie there although scratch is lent."""
+    for (M, N, K) in [(130, 100, 70), (520, 700, 264), (1500, 1700, 203)]:
+        inp = int_inputs(dtype, M, N, K, la, lb, lda=(K if la == ROW else M) + 3, ldb=(N if lb == ROW else K) + 5, ldc=N + 1, seed=M, biased=True)
+        run_exact(inp, "mfma32-packed+direct-to-lds-in-place", lend=True)
