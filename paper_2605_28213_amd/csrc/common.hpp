@@ -114,6 +114,7 @@ inline bool dtype_pair_supported(int in, int out)
 // (gemm_api.hip) has already proven legal for these arguments.
 enum ValuPath { VALU_SCALAR = 0, VALU_VEC16 = 1, VALU_ASYNC = 4 };    // (K2/K3 paths 0..3: bitmask of operands loaded 16 bytes at a time)
 enum MfmaPath { MFMA_ELEMENTWISE = 0, MFMA_VEC16 = 1, MFMA_SKINNY = 2, MFMA_PACKED = 3, MFMA_SPLITK = 4, MFMA_SKINNY_N = 5, MFMA_VEC16_BROW = 6, MFMA_THIN_BROW = 7 };
+constexpr int MFMA_FEW_TILES = 4;         // beside MFMA_VEC16's mask: the product has too few tiles for the fast kernel, see k4_direct_takes_few_tiles
 constexpr int MFMA_PACKED_IN_PLACE = 4;   // beside the packed path's mask of operands used in place: neither is rewritten, see k4_direct_beats_packing
 
 // Workspace of the packed K4 path: both operands rewritten as [rows][Kp], Kp = K rounded up to a slab.
@@ -167,6 +168,8 @@ struct DirectForm { int tile, parts, stages; };
 bool k4_direct_applies(const Args& a);
 DirectForm k4_direct_form(const Args& a);
 bool k4_direct_beats_packing(const Args& a);     // in place rather than through the packed path, with scratch lent
+bool k4_direct_takes_few_tiles(const Args& a);   // instead of the fast kernel, whose conditions hold
+hipError_t launch_k4_few_tiles(const Args& a);
 hipError_t launch_k4_direct(const Args& a);
 
 hipError_t launch_k0(const Args& a);
@@ -187,6 +190,7 @@ Geometry geometry_valu_tiled(int variant, int path, const Args& a);
 Geometry geometry_k3_async(const Args& a);
 Geometry geometry_k4(int path, const Args& a);
 Geometry geometry_k4_direct(const Args& a);
+Geometry geometry_k4_few_tiles(const Args& a);
 Geometry geometry_k4_conv(const Args& a);
 
 }  // namespace gl

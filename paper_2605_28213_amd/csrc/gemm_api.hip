@@ -211,7 +211,7 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
             path = "mfma16-stream(small-N)";
             required &= ~(uint32_t)GEMM_COND_TILE_DIV_K;
         } else if (!f32 && va && vb && kdiv && rows_fit) {
-            p.path = MFMA_VEC16 | (3 << 8);
+            p.path = MFMA_VEC16 | (3 << 8) | (k4_direct_takes_few_tiles(a) ? MFMA_FEW_TILES << 8 : 0);
             snprintf(splitk_path, sizeof(splitk_path), "mfma32-direct-to-lds%s%s", k4_fast_is_persistent(MFMA_VEC16, a) ? "(persistent)" : "",
                      k4_splits_m_tail(a) ? "+stream(M-tail)" : "");
             path = splitk_path;
@@ -262,7 +262,9 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
             path = va && vb ? "mfma32-vec16-masked" : va ? "mfma32-vec16(A)+elementwise-masked(B)"
                             : vb ? "mfma32-elementwise-masked(A)+vec16(B)" : "mfma32-elementwise-masked";
         }
-        g = (p.path & 0xFF) == MFMA_PACKED && (p.path >> 8 & MFMA_PACKED_IN_PLACE) ? geometry_k4_direct(a) : geometry_k4(p.path & 0xFF, a);
+        const int kind = p.path & 0xFF;
+        g = kind == MFMA_PACKED && (p.path >> 8 & MFMA_PACKED_IN_PLACE) ? geometry_k4_direct(a)
+            : kind == MFMA_VEC16 && (p.path >> 8 & MFMA_FEW_TILES) ? geometry_k4_few_tiles(a) : geometry_k4(kind, a);
         break;
     }
     }

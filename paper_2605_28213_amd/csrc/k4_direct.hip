@@ -50,15 +50,29 @@ bool k4_direct_beats_packing(const Args& a)
     return a.batch == 1 && k4_direct_applies(a) && (double)a.M * (double)a.N * (double)a.K <= 2.5e10;
 }
 
-// Tiles of a product, and the workgroups they are launched as (quarters: padded to groups of eight tiles).
+// Tiles of a product, and the workgroups they are launched as (parts: padded to groups of eight tiles).
 static int64_t direct_tiles(const Args& a, const DirectForm& f) { return ((a.M + f.tile - 1) / f.tile) * ((a.N + f.tile - 1) / f.tile) * a.batch; }
-static int64_t direct_grid(const Args& a, const DirectForm& f) { return f.parts == 2 ? (direct_tiles(a, f) + 7) / 8 * 32 : direct_tiles(a, f); }
+static int64_t direct_grid(const Args& a, const DirectForm& f) { return f.parts > 1 ? (direct_tiles(a, f) + 7) / 8 * 8 * f.parts * f.parts : direct_tiles(a, f); }
 
-Geometry geometry_k4_direct(const Args& a)
+// stages: slabs in flight beyond the one in use
+static Geometry geometry_of(const Args& a, const DirectForm& f)
 {
-    const DirectForm f = k4_direct_form(a);
-    return Geometry{f.tile, f.tile, ROW_BYTES / elem_size(a.in_dtype), 256, f.stages, f.stages * 2 * (f.tile / f.parts) * ROW_BYTES, direct_grid(a, f)};
+    return Geometry{f.tile, f.tile, ROW_BYTES / elem_size(a.in_dtype), 256, f.stages - 1, f.stages * 2 * (f.tile / f.parts) * ROW_BYTES, direct_grid(a, f)};
 }
+
+Geometry geometry_k4_direct(const Args& a) { return geometry_of(a, k4_direct_form(a)); }
+
+// Products that meet the fast kernel's conditions but have few tiles: its 128-tiles leave most CUs idle, so a 128-tile is
+// shared by sixteen workgroups of 32 x 32 (fp16 392 x 304 x 320: the fast kernel takes 11.4 us, quarters of 64-tiles 6.6 us
+// on the same sizes unaligned).  The line is that of the quarters, 96 tiles of 64; where split-K applies the product
+// stays with the kernel that the ranges run on.
+constexpr DirectForm FEW_TILES{128, 4, 4};
+bool k4_direct_takes_few_tiles(const Args& a)
+{
+    const int64_t t64 = ((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch;
+    return elem_size(a.in_dtype) == 2 && t64 <= 96 && k4_direct_applies(a) && k4_small_tiles(a) && k4_splitk_factor(a) == 1;
+}
+Geometry geometry_k4_few_tiles(const Args& a) { return geometry_of(a, FEW_TILES); }
 
 template <typename CFG>
 static hipError_t launch_cfg(const Args& a)
@@ -93,6 +107,14 @@ static hipError_t launch_form(const Args& a)
         if (f.tile == 64) return launch_layout<IN, 64, 1, 4>(a);
         return f.stages == 4 ? launch_layout<IN, 128, 1, 4>(a) : launch_layout<IN, 128, 1, 2>(a);
     }
+}
+
+hipError_t launch_k4_few_tiles(const Args& a)
+{
+    if (a.a_sk != 1 || a.b_sk != 1) return hipErrorInvalidValue;
+    if (a.in_dtype == GEMM_BF16) return launch_cfg<DirectCfg<BF16, FEW_TILES.tile, FEW_TILES.parts, FEW_TILES.stages, true, true>>(a);
+    if (a.in_dtype == GEMM_F16) return launch_cfg<DirectCfg<F16, FEW_TILES.tile, FEW_TILES.parts, FEW_TILES.stages, true, true>>(a);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_k4_direct(const Args& a)

@@ -22,20 +22,20 @@
 
 namespace gl {
 
-// A_KC, B_KC: K is contiguous in that operand.  A tile of 64 or 128 belongs to a workgroup of 2 x 2 waves, or (PARTS = 2,
-// 64-tiles) to four workgroups that take a 32 x 32 quarter each: its four waves then take one of a slab's four k-steps
+// A_KC, B_KC: K is contiguous in that operand.  A tile of 64 or 128 belongs to a workgroup of 2 x 2 waves, or (PARTS > 1)
+// to PARTS x PARTS workgroups that take 32 x 32 of it each: a workgroup's four waves then take one of a slab's four k-steps
 // each and add their sums in LDS at the end, so that a product with few tiles has work for every CU.
 template <typename IN, int TILE_, int PARTS_, int STAGES_, bool A_KC_, bool B_KC_>
 struct DirectCfg {
     using In = IN;
     static constexpr int TILE = TILE_, PARTS = PARTS_, STAGES = STAGES_, T = 256;
-    static constexpr bool A_KC = A_KC_, B_KC = B_KC_, SPLIT = PARTS_ == 2;
+    static constexpr bool A_KC = A_KC_, B_KC = B_KC_, SPLIT = PARTS_ > 1;
     static constexpr int SIDE = TILE_ / PARTS_;           // rows and columns of a workgroup
     static constexpr int REGION = SIDE * ROW_BYTES, STAGE = 2 * REGION, LDS_BYTES = STAGES_ * STAGE;
     static constexpr int TM = SPLIT ? 1 : SIDE / 64;      // 32 x 32 accumulator tiles per wave and direction
     static constexpr int SUM_PITCH = 36;                  // floats per row of a wave's partial sums (SPLIT)
     static_assert(IN::BYTES == 2 || IN::BYTES == 4, "fp32 and the two-byte types");
-    static_assert(PARTS_ == 1 || SIDE == 32, "quarters of a 64-tile");
+    static_assert(PARTS_ == 1 || (SIDE == 32 && (PARTS_ == 2 || PARTS_ == 4)), "parts are 32 x 32");
     static_assert((SPLIT ? 4 * 32 * SUM_PITCH * 4 : 4 * 32 * (TM * 128 + 16)) <= LDS_BYTES, "the epilogue reuses the slabs");
 };
 
@@ -56,14 +56,16 @@ __global__ __launch_bounds__(CFG::T, CFG::LDS_BYTES <= 80 * 1024 ? 2 : 1) void k
     const int wm = CFG::SPLIT ? 0 : wave >> 1, wn = CFG::SPLIT ? 0 : wave & 1;
     int64_t b;
     int tm, tn;
-    // (workgroup ids are dealt to the 8 XCDs in turn: a tile's quarters are 8 ids apart, on the same XCD, one after the
+    // (workgroup ids are dealt to the 8 XCDs in turn: a tile's parts are 8 ids apart, on the same XCD, one after the
     // other; the grid is padded to whole groups of 8 tiles, and a workgroup past the last tile leaves as a whole)
-    const int pid = CFG::SPLIT ? (int)((blockIdx.x >> 5) * 8 + (blockIdx.x & 7)) : (int)blockIdx.x, quarter = (int)(blockIdx.x >> 3) & 3;
-    if (CFG::SPLIT && pid >= total) return;
+    constexpr int PARTS = CFG::PARTS;
+    const int id = (int)blockIdx.x, part = PARTS == 1 ? 0 : (id >> 3) % (PARTS * PARTS);
+    const int pid = PARTS == 1 ? id : (id >> 3) / (PARTS * PARTS) * 8 + (id & 7);
+    if (PARTS > 1 && pid >= total) return;
     tile_of<8>(pid, total, tiles_m, tiles_n, b, tm, tn);
     b = __builtin_amdgcn_readfirstlane((int)b);
-    const int64_t m0 = (int64_t)tm * CFG::TILE + (CFG::SPLIT ? (quarter >> 1) * SIDE : 0), n0 = (int64_t)tn * CFG::TILE + (CFG::SPLIT ? (quarter & 1) * SIDE : 0);
-    if (CFG::SPLIT && (m0 >= a.M || n0 >= a.N)) return;         // a quarter outside C
+    const int64_t m0 = (int64_t)tm * CFG::TILE + part / PARTS * SIDE, n0 = (int64_t)tn * CFG::TILE + part % PARTS * SIDE;
+    if (PARTS > 1 && (m0 >= a.M || n0 >= a.N)) return;          // a part outside C
 
     typedef __attribute__((ext_vector_type(4))) int rsrc_t;
     // one operand: element strides along its rows (M or N) and along K, its number of rows, the tile's first row

@@ -342,6 +342,7 @@ hipError_t launch_k4(int path, const Args& a)
 {
     const int kind = path & 0xFF, vec_mask = (path >> 8) & 3;   // (packed path: the mask of operands used in place)
     if (kind == MFMA_PACKED && (path >> 8 & MFMA_PACKED_IN_PLACE)) return launch_k4_direct(a);
+    if (kind == MFMA_VEC16 && (path >> 8 & MFMA_FEW_TILES)) return launch_k4_few_tiles(a);
     if (kind == MFMA_PACKED) {
         switch (a.in_dtype) {
         case GEMM_BF16: return launch_packed<BF16>(a, vec_mask);

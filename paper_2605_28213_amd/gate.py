@@ -115,6 +115,8 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
             pats.append(r"k4_mfma_ring<gl::RingCfg<%s, \d+, true>" % dt)
         elif "(persistent)" in path:
             pats.append(r"k4_mfma_ring<gl::RingCfg<%s, \d+, false>" % dt)
+        elif bm == 128 and stages == 3:
+            pats.append(r"k4_mfma_direct<gl::DirectCfg<%s, 128, 4, 4, true, true>" % dt)     # few tiles: each shared by sixteen workgroups
         elif bm == 128 and stages == 4:
             pats.append(r"k4_mfma_fast<gl::FastCfgDeep<%s> >" % dt)     # 128-tiles, at most one per CU, long K: nine-region ring
         else:

@@ -458,3 +458,12 @@ def test_small_products_with_scratch_lent_are_read_in_place_and_exact(dtype, la,
     for (M, N, K) in [(130, 100, 70), (520, 700, 264), (1500, 1700, 203)]:
         inp = int_inputs(dtype, M, N, K, la, lb, lda=(K if la == ROW else M) + 3, ldb=(N if lb == ROW else K) + 5, ldc=N + 1, seed=M, biased=True)
         run_exact(inp, "mfma32-packed+direct-to-lds-in-place", lend=True)
+
+
+@pytest.mark.parametrize("dtype", [gen.BF16, gen.F16])
+def test_few_tiles_of_the_direct_to_lds_path_are_exact(dtype):
+    """Up to 96 tiles of 64: every 128-tile shared by sixteen workgroups.  Edges inside the first and the last part, one
+    slab up to more than the ring holds, a batch whose tiles do not fill the padded grid."""
+    for (M, N, ns, nb) in [(97, 129, 1, 1), (128, 128, 3, 1), (130, 289, 4, 1), (300, 257, 5, 2), (641, 500, 13, 1), (100, 161, 31, 7)]:
+        q = run_exact(int_inputs(dtype, M, N, slabs(dtype, ns), batch=nb, ldc=N + 3, seed=ns, biased=True), "mfma32-direct-to-lds")
+        assert (q.bm, q.bn, q.stages) == (128, 128, 3) and q.grid % 128 == 0
