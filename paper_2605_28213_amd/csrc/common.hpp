@@ -109,6 +109,9 @@ inline bool dtype_pair_supported(int in, int out)
     }
 }
 
+// Whether one launch holds this many workgroups: the threads of a launch are counted in 32 bits.
+inline bool grid_launches(int64_t workgroups, int64_t threads) { return workgroups < ((int64_t)1 << 32) / threads; }
+
 // ---- host-side launchers, one per translation unit ---------------------------------------------
 // Each returns hipSuccess or the launch error.  `path` selects a code path that the caller
 // (gemm_api.hip) has already proven legal for these arguments.

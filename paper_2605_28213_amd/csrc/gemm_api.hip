@@ -90,14 +90,15 @@ int validate(int variant, const gemm_desc_t* d, const void* A, const void* B, co
     return GEMM_OK;
 }
 
-// Grid limits of the launchers (65535 workgroups along y/z, 2^31-1 along x).
+// Grid limits of the launchers (65535 workgroups along y/z, 2^31-1 along x).  K4's grids are one-dimensional, and what
+// bounds them, the threads of a launch, depends on the path: checked on the plan's geometry once that is known.
 bool grid_fits(int variant, const gemm_desc_t* d)
 {
     const int64_t lim = 65535;
     if (variant == GEMM_K0_NAIVE) return (d->M + 15) / 16 <= lim;
     if (variant == GEMM_K1_LDS_TILED) return (d->M + 63) / 64 <= lim;
     if (variant == GEMM_K2_VECTORIZED || variant == GEMM_K3_PIPELINED) return (d->M + 127) / 128 <= lim;
-    // K4: one-dimensional grid over (batch, tile); the smallest tile of its paths is 128 x 128
+    // K4: the kernels count their tiles, 128 x 128 or larger on every path that takes this many, in an int
     return ((d->M + 127) / 128) * ((d->N + 127) / 128) * d->batch < ((int64_t)1 << 31);
 }
 
@@ -265,6 +266,7 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
         const int kind = p.path & 0xFF;
         g = kind == MFMA_PACKED && (p.path >> 8 & MFMA_PACKED_IN_PLACE) ? geometry_k4_direct(a)
             : kind == MFMA_VEC16 && (p.path >> 8 & MFMA_FEW_TILES) ? geometry_k4_few_tiles(a) : geometry_k4(kind, a);
+        if (!grid_launches(g.grid, g.threads)) { p.status = GEMM_ERR_BAD_ARG; return p; }
         break;
     }
     }

@@ -3,15 +3,21 @@
 
 namespace gl {
 
+// Tiles of a product, and the workgroups they are launched as (parts: padded to groups of eight tiles).
+static int64_t direct_tiles(const Args& a, const DirectForm& f) { return ((a.M + f.tile - 1) / f.tile) * ((a.N + f.tile - 1) / f.tile) * a.batch; }
+static int64_t direct_grid(const Args& a, const DirectForm& f) { return f.parts > 1 ? (direct_tiles(a, f) + 7) / 8 * 8 * f.parts * f.parts : direct_tiles(a, f); }
+
 // What the form asks for beyond the masked kernel: offsets that fit the loads' 32 bits (rows of a K-contiguous operand
 // up to 4 MiB, the k lines of the other kind below 2 GiB with the last slab's overshoot), and, for two-byte types, the
 // element after an odd-length last row mapped (SLACK in the kernel).
+// The grid has to be launchable: a launch holds fewer than 2^32 threads, 2^24 workgroups of 256, and what 64-tiles
+// exceed the masked kernel's 128-tiles may still hold.
 bool k4_direct_applies(const Args& a)
 {
     if (a.in_dtype == GEMM_FP8_E4M3 || a.flags != 0 || a.K <= 0) return false;
     const int es = elem_size(a.in_dtype);
     const int64_t ke = ROW_BYTES / es;
-    if (((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch >= ((int64_t)1 << 29)) return false;      // (the grid, quarters included)
+    if (!grid_launches(direct_grid(a, k4_direct_form(a)), 256)) return false;
     auto fits = [&](const void* p, int64_t batch_stride, int64_t sr, int64_t sk, int64_t rows) {
         const bool kc = sk == 1;
         if (kc ? sr * es > ((int64_t)1 << 22) || a.K * es > ((int64_t)1 << 30) : (a.K + 2 * ke) * sk * es >= ((int64_t)1 << 31)) return false;
@@ -49,10 +55,6 @@ bool k4_direct_beats_packing(const Args& a)
 {
     return a.batch == 1 && k4_direct_applies(a) && (double)a.M * (double)a.N * (double)a.K <= 2.5e10;
 }
-
-// Tiles of a product, and the workgroups they are launched as (parts: padded to groups of eight tiles).
-static int64_t direct_tiles(const Args& a, const DirectForm& f) { return ((a.M + f.tile - 1) / f.tile) * ((a.N + f.tile - 1) / f.tile) * a.batch; }
-static int64_t direct_grid(const Args& a, const DirectForm& f) { return f.parts > 1 ? (direct_tiles(a, f) + 7) / 8 * 8 * f.parts * f.parts : direct_tiles(a, f); }
 
 // stages: slabs in flight beyond the one in use
 static Geometry geometry_of(const Args& a, const DirectForm& f)

@@ -118,6 +118,25 @@ def test_fp32_runs_the_expert_state_on_its_masked_kernel_only():
     assert "packed" not in gemm.gemm_query(gemm.GEMM_K4_MFMA, lent).path
 
 
+@pytest.mark.parametrize("dtype", [gemm.GEMM_F32, gemm.GEMM_BF16, gemm.GEMM_F16, gemm.GEMM_FP8_E4M3])
+@pytest.mark.parametrize("M,N,K,batch", [(64, 16320, 3, 65535), (64, 16384, 3, 65535), (64, 16385, 3, 65535), (1, 16400, 3, 65535), (1, 32768, 3, 65535),
+                                         (1, (1 << 30) - 64, 1, 1), (1, 1 << 30, 1, 1), (256, 256, 3, 65535), (2048, 2048, 3, 65535)])
+def test_a_planned_grid_can_be_launched(dtype, M, N, K, batch):
+    """A launch holds fewer than 2^32 threads.  Column-major A, nothing aligned: a product whose 64-tiles exceed that
+    runs on 128-tiles, and only one whose 128-tiles exceed it is refused."""
+    out = gemm.GEMM_BF16 if dtype == gemm.GEMM_FP8_E4M3 else dtype
+    q = gemm.gemm_query(gemm.GEMM_K4_MFMA, gemm.make_desc(M, N, K, dtype, out, gemm.GEMM_COL_MAJOR,
+                                                          gemm.GEMM_ROW_MAJOR if K > 1 else gemm.GEMM_COL_MAJOR, lda=M + 1,
+                                                          ldb=(N if K > 1 else K) + 1, batch=batch, stride_a=0, stride_b=0))
+    t128 = -(-M // 128) * -(-N // 128) * batch
+    assert q.status == (gemm.GEMM_OK if t128 < 1 << 24 else gemm.GEMM_ERR_BAD_ARG)
+    if q.status == gemm.GEMM_OK:
+        assert q.grid * q.threads < 1 << 32 and q.grid >= t128
+        t64 = -(-M // 64) * -(-N // 64) * batch
+        if dtype == gemm.GEMM_F32:
+            assert (q.bm, q.grid) == ((64, t64) if t64 < 1 << 24 else (128, t128))
+
+
 def test_query_reports_paths_and_conditions_for_the_five_workloads():
     from paper_2605_28213_amd import inputs as gen
     def q(v, name, A=None, B=None):

@@ -116,6 +116,27 @@ def test_largest_batch_count():
     assert gemm.gemm_query(4, d).status == gemm.GEMM_ERR_BAD_ARG
 
 
+def test_more_64_tiles_than_a_launch_holds_run_on_128_tiles():
+    """fp32, 65 535 x 257 tiles of 64 (a launch holds 2^24 - 1 workgroups of 256 threads): 65 535 rows of 16 400
+    columns with a shared B, small integers, every output against the exact product."""
+    M, N, K, b = 1, 16400, 3, 65535
+    gen_ = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randint(-4, 5, (b, K), generator=gen_, device="cuda").float()
+    B = torch.randint(-4, 5, (K, N), generator=gen_, device="cuda").float()
+    C = torch.full((b, N), -1000.0, device="cuda")
+    d = gemm.make_desc(M, N, K, gen.F32, gen.F32, ROW, ROW, batch=b, stride_a=K, stride_b=0, stride_c=N)
+    q = gemm.gemm_query(4, d, A, B, C)
+    assert (q.status, q.bm, q.grid) == (gemm.GEMM_OK, 128, 129 * b)
+    assert gemm.gemm_run_ex(4, d, A, B, C) == gemm.GEMM_OK, gemm.gemm_last_launch_error()
+    torch.cuda.synchronize()
+    for i in range(0, b, 8192):
+        a = A[i: i + 8192]
+        want = a[:, 0:1] * B[0] + a[:, 1:2] * B[1] + a[:, 2:3] * B[2]
+        assert torch.equal(C[i: i + 8192], want)
+    del C
+    torch.cuda.empty_cache()
+
+
 def test_gather_with_activations_just_below_2_gib():
     """The implicit-GEMM state addresses the activations with 32-bit byte offsets and needs them below
     2^31 bytes: 255 images of 256 x 256 x 64 fp16 are 2 139 095 040 bytes.  Every image is the same seeded
