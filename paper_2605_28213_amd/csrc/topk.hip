@@ -550,8 +550,9 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
         p.threads = SEL_T; q.passes = (int32_t)(d->k < 0x7FFFFFFF ? d->k : 0x7FFFFFFF); q.lds_bytes = SEL_MAX_N + 48;
         break;
     case TOPK_T1_RADIX_SELECT:
-        // 4096 groups need an element each (17000 elements, k = 8000, beyond the filter: 74 -> 19 us all the same)
-        if (d->n > LONG_GROUPS) {
+        // 4096 groups need an element each (17000 elements, k = 8000, beyond the filter: 74 -> 19 us all the same);
+        // a launch holds fewer than 2^32 threads, so 2^22 rows and more stay with 256 lanes each
+        if (d->n > LONG_GROUPS && d->batch < ((int64_t)1 << 32) / LONG_T) {
             const bool filter = d->k <= LONG_MAX_K;
             path = filter ? "group-maxima filter + radix-select(11+11+10), 1024 lanes" : "radix-select(11+11+10, streaming, 1024 lanes)";
             p.threads = LONG_T; q.passes = filter ? 2 : 5; q.lds_bytes = sizeof(LongShared);

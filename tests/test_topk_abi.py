@@ -50,6 +50,14 @@ def test_struct_layout_matches_the_header_as_plain_c(tmp_path):
     assert [int(x) for x in out[2:]] == want
 
 
+@pytest.mark.parametrize("n", [4097, 8192, 16384, 100000])
+@pytest.mark.parametrize("batch", [(1 << 22) - 1, 1 << 22, (1 << 24) - 1])
+def test_rows_of_the_streaming_state_fit_a_launch(n, batch):
+    """A launch holds fewer than 2^32 threads: long rows in such numbers that 1024 lanes each exceed that run on 256."""
+    q = topk.topk_query(1, topk.make_desc(batch, n, 7))
+    assert q.status == gemm.GEMM_OK and q.grid == batch and q.grid * q.threads < 1 << 32
+
+
 def test_plans_and_refusals():
     d = topk.make_desc(64, 4096, 512)
     q0, q1, q2 = (topk.topk_query(v, d) for v in range(3))
