@@ -8,7 +8,8 @@
  *     T0 selection        k rounds of a workgroup-wide arg-max over the not yet taken elements
  *     T1 radix select     the k-th largest key by four 8-bit histogram passes over the row (most
  *                         significant digit first), then one ordered compaction pass; rows beyond 4096
- *                         elements by a filter on 4096 group maxima first (k <= 2048), or by 11 + 11 + 10 bits
+ *                         elements (5000 from 513 rows on) by 11 + 11 + 10 bits on 1024 lanes, beyond
+ *                         12288 elements (k <= 2048) by a filter on 4096 group maxima first
  *     T2 resident coarse + refine   the row's keys stay in registers (one load); an 11-bit coarse
  *                         histogram finds the threshold's bin, two refine passes (11 + 10 bits) over
  *                         the candidates in that bin finish it; compaction from the registers

@@ -251,10 +251,11 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
 }
 
 // ---- T1 on long rows ------------------------------------------------------------------------------
-// A row too long to be counted by 256 lanes at a stride.  One workgroup of 1024 lanes per row (no scratch is lent, so
-// rows are not split over workgroups); what bounds it is what one CU can fetch, so the row is read twice (the form with
-// 256 lanes and five passes took 460 us on 8 x 131072, k = 64; this one 27.5, 18.5 of them for k = 1, where the second
-// read is one lane's; 128 x 200000, k = 100: 1426 -> 40; 64 x 16384, k = 512: 67 -> 18) and everything else works on few keys:
+// One workgroup of 1024 lanes per row (no scratch is lent, so rows are not split over workgroups), 16 bytes per lane and
+// load; what bounds it is what one CU can fetch.  The general form reads the row five times: three histogram passes and
+// two of ordered compaction.  The filter reads it twice (8 x 131072, k = 64: 256 lanes took 460 us, the general form 94,
+// this one 27.5, 18.5 of them for k = 1, where the second read is one lane's; 128 x 200000, k = 100: 1426 -> 40) and
+// everything else works on few keys:
 //   1. each lane keeps the largest value of four interleaved groups of elements (4096 groups in all);
 //   2. the k-th largest of the 4096 maxima is a lower bound of the row's k-th largest value (k groups each hold an
 //      element at least that large): two 11-bit digits of it, the rest zero, are bound enough;
@@ -262,12 +263,18 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
 //      listed in LDS (k = 64 of 131072 normal values: about 65; k = 2048: about 2840 of the 4096 there is room for);
 //   4. radix select on the list, a counting sort of it by index, ordered compaction.
 // A list that overflows (long runs of values equal to the threshold, rows that put the large values into few groups)
-// or k above half the groups takes the general form below: three histogram passes over the row and two passes of
-// ordered compaction, 16 bytes per lane and load.
+// or k above half the groups takes the general form.
+// Which rows come here (times relative to 256 lanes and five passes, normal values unless noted):
+//   up to 512 rows, every length: the general form 0.58 at 4097 elements and k = 64, rows of one value 0.7 to 0.95;
+//   more rows, beyond 5000 elements: the workgroups of 256 share the CUs better, 1024 rows of 4097 take 1.05 and 8192
+//   rows 1.32 (of one value 1.7), of 5000 0.70 and 0.85 (1.13), of 6000 0.60 and 0.66 (1.05).
+// The filter pays from 12288 elements on: general / filter 8192 elements, k = 512, 0.34 / 0.40; 12288 0.30 / 0.31;
+// 20000 0.26 / 0.24; 32768 0.23 / 0.17; and where the list overflows its two reads are lost.
 constexpr int LONG_T = 1024;
 constexpr int LONG_GROUPS = 4 * LONG_T;
 constexpr int LONG_CAP = 4096;                  // listed elements: 4 per lane
 constexpr int LONG_MAX_K = LONG_GROUPS / 2;
+constexpr int64_t LONG_MANY_ROWS = 512, LONG_MANY_N = 5000, LONG_FILTER_N = 12288;     // (4096 groups need an element each)
 typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));      // rows start at any element
 
 // f(four values, index of the first, how many of them exist) for every run of four that belongs to this lane,
@@ -503,12 +510,14 @@ __device__ bool long_row_filtered(const TopkArgs& a, const float* row, LongShare
     return true;
 }
 
+__host__ __device__ inline bool long_row_takes_filter(int64_t n, int64_t k) { return n > LONG_FILTER_N && k <= LONG_MAX_K; }
+
 __global__ __launch_bounds__(LONG_T) void topk_long(TopkArgs a)
 {
     __shared__ LongShared sh;
     const float* row = a.x + (int64_t)blockIdx.x * a.ld;
     if (threadIdx.x == 0) { sh.digit = 0; sh.left = 0; sh.listed = 0; }      // a row of NaNs may leave a digit unfound
-    if (a.k <= LONG_MAX_K && long_row_filtered(a, row, sh)) return;
+    if (long_row_takes_filter(a.n, a.k) && long_row_filtered(a, row, sh)) return;
     long_row_general(a, row, sh);
 }
 
@@ -550,10 +559,9 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
         p.threads = SEL_T; q.passes = (int32_t)(d->k < 0x7FFFFFFF ? d->k : 0x7FFFFFFF); q.lds_bytes = SEL_MAX_N + 48;
         break;
     case TOPK_T1_RADIX_SELECT:
-        // 4096 groups need an element each (17000 elements, k = 8000, beyond the filter: 74 -> 19 us all the same);
-        // a launch holds fewer than 2^32 threads, so 2^22 rows and more stay with 256 lanes each
-        if (d->n > LONG_GROUPS && d->batch < ((int64_t)1 << 32) / LONG_T) {
-            const bool filter = d->k <= LONG_MAX_K;
+        // (the lines: see topk_long; a launch holds fewer than 2^32 threads, so 2^22 rows and more stay with 256 lanes each)
+        if (d->n > (d->batch > LONG_MANY_ROWS ? LONG_MANY_N : 4096) && d->batch < ((int64_t)1 << 32) / LONG_T) {
+            const bool filter = long_row_takes_filter(d->n, d->k);
             path = filter ? "group-maxima filter + radix-select(11+11+10), 1024 lanes" : "radix-select(11+11+10, streaming, 1024 lanes)";
             p.threads = LONG_T; q.passes = filter ? 2 : 5; q.lds_bytes = sizeof(LongShared);
             break;

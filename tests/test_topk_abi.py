@@ -58,6 +58,15 @@ def test_rows_of_the_streaming_state_fit_a_launch(n, batch):
     assert q.status == gemm.GEMM_OK and q.grid == batch and q.grid * q.threads < 1 << 32
 
 
+def test_which_long_rows_go_to_which_form():
+    """256 lanes share the CUs better where there are many rows; the filter's two reads pay on long rows only."""
+    of = lambda b, n, k: topk.topk_query(1, topk.make_desc(b, n, k))
+    for b, n, k, threads, passes in [(1, 4096, 9, 256, 5), (512, 4097, 9, 1024, 5), (513, 4097, 9, 256, 5), (513, 5000, 2100, 256, 5), (513, 5001, 9, 1024, 5),
+                                     (8, 12288, 9, 1024, 5), (8, 12289, 2048, 1024, 2), (8, 12289, 2049, 1024, 5), (4096, 20000, 1, 1024, 2)]:
+        q = of(b, n, k)
+        assert (q.threads, q.passes, "filter" in q.path) == (threads, passes, passes == 2), (b, n, k, q)
+
+
 def test_plans_and_refusals():
     d = topk.make_desc(64, 4096, 512)
     q0, q1, q2 = (topk.topk_query(v, d) for v in range(3))

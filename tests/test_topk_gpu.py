@@ -136,11 +136,11 @@ def test_gate_table_of_the_paper_shape():
     assert rows[2]["median_us"] < rows[0]["median_us"] and rows[1]["median_us"] < rows[0]["median_us"]
 
 
-@pytest.mark.parametrize("n,k", [(4097, 1), (4097, 2048), (4098, 2049), (8191, 64), (32768, 2048), (70003, 4097), (131072, 64), (262147, 700)])
+@pytest.mark.parametrize("n,k", [(4097, 1), (12288, 512), (12289, 1), (12289, 2048), (4097, 2048), (4098, 2049), (8191, 64), (32768, 2048), (70003, 4097), (131072, 64), (262147, 700)])
 @pytest.mark.parametrize("values", ["normal", "ascending", "few", "zeros", "neginf"])
 def test_long_rows(n, k, values):
-    """Rows beyond 4096 elements: a list of candidates that suffices, one that overflows (equal values) and k beyond
-    the filter; every length modulo 4, every row start modulo 16 bytes (odd ld)."""
+    """Rows beyond 4096 elements: without the filter (up to 12288) and with it, a list of candidates that suffices, one
+    that overflows (equal values) and k beyond the filter; every length modulo 4, every row start modulo 16 bytes (odd ld)."""
     rng = np.random.default_rng(n + k)
     ld = n | 1
     x = rng.standard_normal((3, ld)).astype(np.float32)
@@ -157,5 +157,18 @@ def test_long_rows(n, k, values):
     assert rc == gemm.GEMM_OK and q.threads == 1024
     # the oracle counts ranks in O(n^2); a stable sort of the negated row is the same selection (one of the oracle's pins)
     ridx = np.sort(np.argsort(-x[:, :n], axis=1, kind="stable")[:, :k], axis=1)
+    np.testing.assert_array_equal(idx, ridx)
+    np.testing.assert_array_equal(val.view(np.uint32), np.take_along_axis(x, ridx, 1).view(np.uint32))
+
+
+@pytest.mark.parametrize("b,n,threads", [(512, 4099, 1024), (513, 4099, 256), (513, 5000, 256), (513, 5001, 1024)])
+def test_many_long_rows(b, n, threads):
+    """Both sides of the lines beyond which many rows keep 256 lanes each, one row in four of tied values."""
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((b, n + 1)).astype(np.float32)
+    x[::4] = np.round(x[::4])
+    rc, idx, val, q = run_state(1, x, n, 300)
+    assert rc == gemm.GEMM_OK and q.threads == threads
+    ridx = np.sort(np.argsort(-x[:, :n], axis=1, kind="stable")[:, :300], axis=1)
     np.testing.assert_array_equal(idx, ridx)
     np.testing.assert_array_equal(val.view(np.uint32), np.take_along_axis(x, ridx, 1).view(np.uint32))
