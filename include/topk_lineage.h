@@ -60,7 +60,9 @@ typedef struct {
 typedef struct {
     uint32_t required, violated, holds; /* TOPK_COND_* */
     int32_t  threads;                   /* workgroup size; one workgroup per row */
-    int32_t  passes;                    /* passes over the row's keys (histogram passes + compaction; k rounds for T0) */
+    int32_t  passes;                    /* passes over the row's keys (histogram passes + compaction; k rounds for T0);
+                                         * with T1's filter the 2 of a row whose candidates it holds: rows of equal values,
+                                         * which the query cannot know of, take 6 or 7 */
     int32_t  lds_bytes;
     int64_t  grid;
     char     path[64];

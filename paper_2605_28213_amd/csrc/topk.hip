@@ -263,7 +263,7 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
 //      listed in LDS (k = 64 of 131072 normal values: about 65; k = 2048: about 2840 of the 4096 there is room for);
 //   4. radix select on the list, a counting sort of it by index, ordered compaction.
 // A list that overflows (long runs of values equal to the threshold, rows that put the large values into few groups)
-// or k above half the groups takes the general form.
+// or k above half the groups takes the general form, after one of the filter's reads or both: six or seven passes.
 // Which rows come here (times relative to 256 lanes and five passes, normal values unless noted):
 //   up to 512 rows, every length: the general form 0.58 at 4097 elements and k = 64, rows of one value 0.7 to 0.95;
 //   more rows, beyond 5000 elements: the workgroups of 256 share the CUs better, 1024 rows of 4097 take 1.05 and 8192
@@ -274,6 +274,7 @@ constexpr int LONG_T = 1024;
 constexpr int LONG_GROUPS = 4 * LONG_T;
 constexpr int LONG_CAP = 4096;                  // listed elements: 4 per lane
 constexpr int LONG_MAX_K = LONG_GROUPS / 2;
+constexpr int LONG_MAX_REACH = LONG_GROUPS / 4 * 3;
 constexpr int64_t LONG_MANY_ROWS = 512, LONG_MANY_N = 5000, LONG_FILTER_N = 12288;     // (4096 groups need an element each)
 typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));      // rows start at any element
 
@@ -423,6 +424,13 @@ __device__ bool long_row_filtered(const TopkArgs& a, const float* row, LongShare
     for (int e = 0; e < 4; ++e) key[e] = key_of(top[e]);
     int remaining = (int)a.k;
     const uint32_t bound = select_key(sh, key, LONG_GROUPS, 2, remaining);
+    // groups whose maxima reach the bound: each puts an element on the list at least, and far more of them than k means
+    // that a run of equal values is the threshold (2048 x 12289 zeros, k = 64: 428 -> 407 us,
+    // 383 with 256 lanes and five passes; 64 x 131072: 395 -> 392, 595)
+    if ((int)a.k - remaining + sh.hist[sh.digit] > LONG_MAX_REACH) {
+        __syncthreads();                        // (the general form clears the histogram)
+        return false;
+    }
     bool full = false;
     if (key[0] >= bound || key[1] >= bound || key[2] >= bound || key[3] >= bound)
         // (four values are tested at once: with a test per element 8 x 131072, k = 64 took 40 us)
@@ -562,7 +570,7 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
         // (the lines: see topk_long; a launch holds fewer than 2^32 threads, so 2^22 rows and more stay with 256 lanes each)
         if (d->n > (d->batch > LONG_MANY_ROWS ? LONG_MANY_N : 4096) && d->batch < ((int64_t)1 << 32) / LONG_T) {
             const bool filter = long_row_takes_filter(d->n, d->k);
-            path = filter ? "group-maxima filter + radix-select(11+11+10), 1024 lanes" : "radix-select(11+11+10, streaming, 1024 lanes)";
+            path = filter ? "group-maxima filter, else radix-select(11+11+10), 1024 lanes" : "radix-select(11+11+10, streaming, 1024 lanes)";
             p.threads = LONG_T; q.passes = filter ? 2 : 5; q.lds_bytes = sizeof(LongShared);
             break;
         }
