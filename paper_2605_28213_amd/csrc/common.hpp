@@ -170,7 +170,7 @@ hipError_t launch_k4_thin_row_major_b(const Args& a);
 struct DirectForm { int tile, parts, stages; };
 bool k4_direct_applies(const Args& a);
 DirectForm k4_direct_form(const Args& a);
-bool k4_direct_beats_packing(const Args& a);     // in place rather than through the packed path, with scratch lent
+bool k4_direct_beats_packing(const Args& a, int keep_mask);     // in place rather than through the packed path, with scratch lent
 bool k4_direct_takes_few_tiles(const Args& a);   // instead of the fast kernel, whose conditions hold
 hipError_t launch_k4_few_tiles(const Args& a);
 hipError_t launch_k4_direct(const Args& a);

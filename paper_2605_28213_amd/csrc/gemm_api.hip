@@ -249,7 +249,7 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
         } else if (can_pack && d->workspace != nullptr) {
             // the caller lent scratch: repair the violated conditions by packing, then run the fast kernel
             p.path = MFMA_PACKED | (keep << 8);
-            if (k4_direct_beats_packing(a)) {      // ... or, small enough, multiply what lies there as it lies there (the scratch stays unused)
+            if (k4_direct_beats_packing(a, keep)) {      // ... or, small enough, multiply what lies there as it lies there (the scratch stays unused)
                 p.path |= MFMA_PACKED_IN_PLACE << 8;
                 snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds-in-place", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "");
             } else snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds%s%s", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "",

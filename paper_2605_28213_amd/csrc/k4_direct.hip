@@ -1,6 +1,8 @@
 // Launcher of K4's masked state in its direct-to-LDS form.
 #include "k4_direct.hpp"
 
+#include <algorithm>
+
 namespace gl {
 
 // Tiles of a product, and the workgroups they are launched as (parts: padded to groups of eight tiles).
@@ -46,14 +48,39 @@ DirectForm k4_direct_form(const Args& a)
     return t128 <= 256 ? DirectForm{128, 1, 4} : DirectForm{128, 1, 2};
 }
 
-// Packing moves (M + N) K elements once more and adds one or two launches; the fast kernel behind it multiplies about a
-// fifth faster than the forms here.  bf16, packed against in place: 1000 x 1000 x 200 19.6 / 4.8 us, 1500 x 264 x 4000
-// 47.6 / 20.7, 2000 x 2056 x 2000 45 / 33, 4096 x 2048 x 2048 47 / 37 (one operand packed), 2048 x 2048 x 4096 64 / 47
-// (both), and the other way round 3000 x 3000 x 5000 128 / 152, 5000 x 3000 x 3000 99 / 126, 4096 x 4096 x 6000 181 / 201:
-// the line lies between 1.7e10 and 4.5e10 multiply-adds.  Measured on single products; batches keep the packed path.
-bool k4_direct_beats_packing(const Args& a)
+// Packing moves (M + N) K elements once more and adds one or two launches; the fast kernel behind it multiplies faster
+// than the forms here: by a tenth on rows aligned to 16 bytes, by half on rows aligned to an element only, more where K
+// is contiguous in both operands and where K is long (rows far apart, read 128 bytes at a time).  1195 products of 0.1 to
+// 26 x 10^9 multiply-adds (G), M, N and K from 64 to 12000, every layout, bf16, geometric mean of repeated operands and
+// of operands rotated beyond the caches; in place / packed:
+//   at most one 64-tile per CU: 0.44 in the mean, 0.87 at worst;
+//   otherwise, up to the line / beyond it:
+//     rows aligned to           16 bytes           8                  4                  2
+//     K contiguous in both      13 G 0.75 / 1.00   10 G 0.70 / 1.06   5 G 0.61 / 0.95    3 G 0.66 / 0.98
+//     other layouts             25 G 0.71 / 0.81   16 G 0.69 / 0.90   13 G 0.68 / 0.88   8 G 0.67 / 1.01
+//     K beyond 4800             10 G 0.78 / 0.92   6 G 0.92 / 0.95    5 G - / 0.96       5 G - / 1.00
+//   where one operand is packed that has at most a quarter of the other's rows, which is cheap, 10 G 0.64 / 0.97 (and
+//   0.6 G at a 64th: 32 x 16384 x 4096 40 against 37 us, 64 x 16384 x 8192 81 / 77).
+// Beyond the lines lie the products that lose much (904 x 5071 x 4317 with odd rows 99 to 116 us against 70): of the 877
+// up to them one is slower than packed by more than a twentieth in the mean, 26 in one of the two measurements, 1.19 at
+// worst.  Measured on single products; batches keep the packed path.
+bool k4_direct_beats_packing(const Args& a, int keep_mask)
 {
-    return a.batch == 1 && k4_direct_applies(a) && (double)a.M * (double)a.N * (double)a.K <= 2.5e10;
+    if (a.batch != 1 || !k4_direct_applies(a)) return false;
+    const double work = (double)a.M * (double)a.N * (double)a.K;
+    const int64_t packed = keep_mask == 1 ? a.N : a.M, kept = keep_mask == 1 ? a.M : a.N;
+    double limit = 25e9;
+    if (keep_mask != 0 && packed * 4 <= kept) limit = packed * 64 <= kept ? 0.6e9 : 10e9;
+    if (((a.M + 63) / 64) * ((a.N + 63) / 64) > K4_RING_WORKGROUPS) {
+        const int es = elem_size(a.in_dtype);
+        const bool ka = a.a_sk == 1, kb = a.b_sk == 1;
+        const uint64_t low = (uint64_t)(uintptr_t)a.A | (uint64_t)(uintptr_t)a.B | (uint64_t)((ka ? a.a_si : a.a_sk) * es) | (uint64_t)((kb ? a.b_sj : a.b_sk) * es);
+        const int align = low % 16 == 0 ? 0 : low % 8 == 0 ? 1 : low % 4 == 0 ? 2 : 3;
+        static const double BOTH_KC[4] = {13e9, 10e9, 5e9, 3e9}, OTHER[4] = {25e9, 16e9, 13e9, 8e9}, LONG_K[4] = {10e9, 6e9, 5e9, 5e9};
+        limit = std::min(limit, (ka && kb ? BOTH_KC : OTHER)[align]);
+        if (a.K > 4800) limit = std::min(limit, LONG_K[align]);
+    }
+    return work <= limit;
 }
 
 // stages: slabs in flight beyond the one in use

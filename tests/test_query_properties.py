@@ -175,3 +175,40 @@ def test_vector_load_simplification_belongs_to_k2_and_k3(p, variant):
         assert both.status == gemm.GEMM_ERR_BAD_ARG
     else:
         assert q.status == gemm.GEMM_ERR_BAD_ARG
+
+
+ROW, COL = gemm.GEMM_ROW_MAJOR, gemm.GEMM_COL_MAJOR
+IN_PLACE_LINES = [  # (M, N, K, layouts, multiple of elements that leading dimensions are odd multiples of, in place)
+    (1024, 1024, 20000, ROW, ROW, 1, True), (1024, 1024, 20000, COL, COL, 8, True),         # one 64-tile per CU: always (measured 0.72, 0.64 of packed)
+    (1040, 1040, 20000, ROW, ROW, 1, False),
+    (2600, 2600, 1900, ROW, COL, 8, True), (2600, 2600, 1940, ROW, COL, 8, False),          # K contiguous in both: 13, 10, 5, 3 x 10^9
+    (2000, 2000, 2490, ROW, COL, 4, True), (2000, 2000, 2510, ROW, COL, 4, False),
+    (2000, 2000, 1240, ROW, COL, 2, True), (2000, 2000, 1260, ROW, COL, 2, False),
+    (2000, 2000, 740, ROW, COL, 1, True), (2000, 2000, 760, ROW, COL, 1, False),
+    (2048, 2048, 4096, COL, ROW, 8, True), (2900, 2900, 2960, COL, ROW, 8, True), (2900, 2900, 2980, COL, ROW, 8, False),
+    (2000, 2000, 3990, ROW, ROW, 4, True), (2000, 2000, 4010, ROW, ROW, 4, False),          # other layouts: 25, 16, 13, 8
+    (2000, 2000, 3240, COL, COL, 2, True), (2000, 2000, 3260, COL, COL, 2, False),
+    (2000, 2000, 1990, COL, ROW, 1, True), (2000, 2000, 2010, COL, ROW, 1, False),
+    (1400, 1400, 4800, COL, ROW, 1, False), (1200, 1400, 4800, COL, ROW, 4, True), (1400, 1400, 5000, COL, ROW, 8, True), (1500, 1400, 5000, COL, ROW, 8, False),   # long K
+    (1200, 1000, 5000, ROW, ROW, 4, True), (1300, 1000, 5000, ROW, ROW, 4, False),
+    (4096, 1000, 2432, ROW, ROW, 8, True), (4096, 1000, 2496, ROW, ROW, 8, False),          # B alone is packed, A has four times its rows: 10
+    (64, 16384, 512, COL, COL, 8, True), (64, 16384, 1024, COL, COL, 8, False),             # A alone, B has 256 times: 0.6
+]
+
+
+def test_packed_or_in_place_by_size_layout_and_alignment():
+    """With scratch lent the operands are multiplied where they lie on the side of each line where that is faster."""
+    for dt in (gemm.GEMM_BF16, gemm.GEMM_F16):
+        for (M, N, K, la, lb, al, in_place) in IN_PLACE_LINES:
+            ld = lambda x: next(y for y in range(x, x + 17) if y % (2 * al if al < 8 else 8) == (al if al < 8 else 0))
+            p = dict(M=M, N=N, K=K, dt=dt, out=dt, la=la, lb=lb, lda=ld(K if la == ROW else M), ldb=ld(N if lb == ROW else K), ldc=N, batch=1)
+            need = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p)).workspace_bytes
+            assert need > 0
+            q = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p, workspace=4096, workspace_bytes=need))
+            assert q.status == gemm.GEMM_OK and ("in-place" in q.path) == in_place, (M, N, K, la, lb, al, q.path)
+    # an operand's address counts as its rows do
+    p = dict(M=2000, N=2000, K=2400, dt=gemm.GEMM_BF16, out=gemm.GEMM_BF16, la=COL, lb=ROW, lda=2000, ldb=2000, ldc=2000, batch=1)
+    need = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p)).workspace_bytes
+    for A, B, in_place in [(4096, 4096, True), (4098, 4096, False), (4096, 4098, False), (4100, 4096, True)]:
+        q = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p, workspace=4096, workspace_bytes=need), A, B)
+        assert ("in-place" in q.path) == in_place, (A, B, q.path)
