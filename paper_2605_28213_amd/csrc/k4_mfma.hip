@@ -240,32 +240,6 @@ int k4_splitk_factor(const Args& a)
 
 size_t k4_splitk_workspace_bytes(const Args& a, int splits) { return (size_t)splits * (size_t)(a.M * a.N) * 4; }
 
-// One row of 128-tiles (at most 128 rows of A): each K range of each tile reads a part of B of its own.
-static bool k4_splitk_rotates(const Args& p)
-{
-    return p.flags == GEMM_FLAG_TILE_128 && p.M <= 128 && !k4_uses_ring(p) && !k4_small_tiles_deep(p);
-}
-
-template <typename IN>
-static hipError_t launch_splitk(const Args& a)
-{
-    const int splits = k4_splitk_factor(a);
-    Args p = a;
-    p.batch = splits;
-    p.K = a.K / splits;
-    p.stride_a = p.K;                       // K is contiguous in both operands: the next range starts K/splits elements on
-    p.stride_b = p.K;
-    p.C = a.workspace; p.ldc = a.N; p.stride_c = a.M * a.N;
-    p.out_dtype = GEMM_F32;
-    p.scale_a = p.scale_b = nullptr; p.bias = nullptr;
-    p.flags = (k4_small_tiles(a) ? GEMM_FLAG_TILE_128 : GEMM_FLAG_TILE_256) | (a.flags & K4_NEUTRAL_FLAGS);   // the tile the product itself would get
-    hipError_t e = k4_splitk_rotates(p) ? launch_fast<FastCfgRot<IN>>(p) : launch_fast_any<IN>(p);
-    if (e != hipSuccess) return e;
-    const int64_t threads = a.M * ((a.N + 3) / 4);
-    hipLaunchKernelGGL(k4_splitk_reduce<IN>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, a.stream, a, (const float*)a.workspace, splits);
-    return hipGetLastError();
-}
-
 // The arguments the fast kernel is launched with on each of its three paths, as far as the choice between its
 // persistent and its one-tile-per-workgroup form depends on them (mirrors launch_packed, launch_splitk and
 // launch_fast_split).
@@ -282,6 +256,39 @@ static Args fast_kernel_args(int kind, const Args& a)
     if (kind == MFMA_PACKED) p.K = k4_packed_k(a);
     if (k4_splits_m_tail(p)) p.M = p.M - p.M % 256;
     return p;
+}
+
+// Whether the K ranges run with a rotated K walk (FastCfgRot): one row of 128-tiles (at most 128 rows of A: each range of
+// each tile reads a part of B of its own) and a B of at least 192 MiB, more than stays in the 256 MiB Infinity Cache from
+// one pass to the next: then every pass asks the memory channels, in step without the rotation.  In step / rotated, 128
+// rows, operands rotated over 700 MB: bf16 16384^2 (512 MiB) 149 / 120 us, 8192 x 16384 (256) 89 / 73, 28672 x 4096 (224)
+// 80 / 71; e4m3 16384^2 (256) 88 / 77, 12288 x 16384 (192) 72 / 66; leading dimensions 64 or 128 elements longer 1.04 to
+// 0.74 of the time.  Below the line there is nothing to gain and something to lose: 8192^2 (128 MiB) 47 / 47 so, but 34 / 40
+// with the same B again; 2048 x 4096 (16) 16.1 / 16.7.
+bool k4_splitk_rotates(const Args& a)
+{
+    const Args p = fast_kernel_args(MFMA_SPLITK, a);
+    return p.flags == GEMM_FLAG_TILE_128 && a.M <= 128 && a.N * a.K * elem_size(a.in_dtype) >= (int64_t)192 << 20 && !k4_uses_ring(p) && !k4_small_tiles_deep(p);
+}
+
+template <typename IN>
+static hipError_t launch_splitk(const Args& a)
+{
+    const int splits = k4_splitk_factor(a);
+    Args p = a;
+    p.batch = splits;
+    p.K = a.K / splits;
+    p.stride_a = p.K;                       // K is contiguous in both operands: the next range starts K/splits elements on
+    p.stride_b = p.K;
+    p.C = a.workspace; p.ldc = a.N; p.stride_c = a.M * a.N;
+    p.out_dtype = GEMM_F32;
+    p.scale_a = p.scale_b = nullptr; p.bias = nullptr;
+    p.flags = (k4_small_tiles(a) ? GEMM_FLAG_TILE_128 : GEMM_FLAG_TILE_256) | (a.flags & K4_NEUTRAL_FLAGS);   // the tile the product itself would get
+    hipError_t e = k4_splitk_rotates(a) ? launch_fast<FastCfgRot<IN>>(p) : launch_fast_any<IN>(p);
+    if (e != hipSuccess) return e;
+    const int64_t threads = a.M * ((a.N + 3) / 4);
+    hipLaunchKernelGGL(k4_splitk_reduce<IN>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, a.stream, a, (const float*)a.workspace, splits);
+    return hipGetLastError();
 }
 
 bool k4_fast_is_persistent(int kind, const Args& a) { return k4_uses_ring(fast_kernel_args(kind, a)); }

@@ -323,6 +323,21 @@ def test_split_k_form_is_exact(dtype):
 
 
 @pytest.mark.parametrize("dtype", DTYPES)
+def test_split_k_form_with_a_rotated_k_walk_is_exact(dtype):
+    """One row of tiles and a B of 192 MiB: every tile starts its K walk at a slab of its own and wraps round.  The
+    oracle is a product of integers in fp32, exact in any order (sums stay below 2^24)."""
+    M, N, K = 101, 12301, slabs(dtype, 128)
+    inp = int_inputs(dtype, M, N, K, ldc=N + 3, seed=11)
+    d = gemm.make_desc(M, N, K, dtype, gen.F32, ROW, COL, ldc=N + 3, workspace=4096, workspace_bytes=1 << 40)
+    assert gemm.gemm_query(K4, d).path == "mfma32-direct-to-lds+splitK(4,rotated)"
+    torch_type = {gen.BF16: torch.bfloat16, gen.F16: torch.float16, gen.E4M3: torch.float8_e4m3fn}[dtype]
+    A, B = (torch.from_numpy(x.view(np.uint8)).view(torch_type).float().reshape(-1, K) for x in (inp.A, inp.B))
+    rc, C, _ = util.run_config(K4, inp, lend_workspace=True)
+    assert rc == gemm.GEMM_OK
+    np.testing.assert_array_equal(C[0, :, :N], (A @ B.T).numpy())
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
 @pytest.mark.parametrize("la,lb,path", [(ROW, ROW, "mfma32-packed+direct-to-lds"), (COL, ROW, "mfma32-packed+direct-to-lds"),
                                         (COL, COL, "mfma32-packed+direct-to-lds"), (ROW, COL, "mfma32-packed+direct-to-lds")])
 def test_packed_path_is_exact(dtype, la, lb, path):
