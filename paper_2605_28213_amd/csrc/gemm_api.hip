@@ -222,8 +222,8 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
                 pack_bytes = k4_splitk_workspace_bytes(a, splits);
                 if (d->workspace != nullptr) {
                     p.path = MFMA_SPLITK;
-                    snprintf(splitk_path, sizeof(splitk_path), "mfma32-direct-to-lds%s+splitK(%d%s)",
-                             k4_fast_is_persistent(MFMA_SPLITK, a) ? "(persistent)" : "", splits, k4_splitk_rotates(a) ? ",rotated" : "");
+                    snprintf(splitk_path, sizeof(splitk_path), "mfma32-direct-to-lds%s+splitK(%d)%s",
+                             k4_fast_is_persistent(MFMA_SPLITK, a) ? "(persistent)" : "", splits, k4_splitk_rotates(a) ? "(rotated)" : "");
                     path = splitk_path;
                 }
             }

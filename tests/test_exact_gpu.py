@@ -329,7 +329,7 @@ def test_split_k_form_with_a_rotated_k_walk_is_exact(dtype):
     M, N, K = 101, 12301, slabs(dtype, 128)
     inp = int_inputs(dtype, M, N, K, ldc=N + 3, seed=11)
     d = gemm.make_desc(M, N, K, dtype, gen.F32, ROW, COL, ldc=N + 3, workspace=4096, workspace_bytes=1 << 40)
-    assert gemm.gemm_query(K4, d).path == "mfma32-direct-to-lds+splitK(4,rotated)"
+    assert gemm.gemm_query(K4, d).path == "mfma32-direct-to-lds+splitK(4)(rotated)"
     torch_type = {gen.BF16: torch.bfloat16, gen.F16: torch.float16, gen.E4M3: torch.float8_e4m3fn}[dtype]
     A, B = (torch.from_numpy(x.view(np.uint8)).view(torch_type).float().reshape(-1, K) for x in (inp.A, inp.B))
     rc, C, _ = util.run_config(K4, inp, lend_workspace=True)

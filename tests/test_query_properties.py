@@ -216,10 +216,10 @@ def test_packed_or_in_place_by_size_layout_and_alignment():
 
 def test_which_k_ranges_run_with_a_rotated_walk():
     """One row of 128-tiles and a B of at least 192 MiB, more than the Infinity Cache keeps from pass to pass."""
-    for (dt, M, N, K, path) in [(gemm.GEMM_BF16, 128, 16384, 16384, "+splitK(4,rotated)"), (gemm.GEMM_BF16, 128, 8192, 16384, "+splitK(8,rotated)"),
-                                (gemm.GEMM_F16, 97, 12288, 8192, "+splitK(4,rotated)"), (gemm.GEMM_F16, 97, 12287, 8192, "+splitK(4)"),
+    for (dt, M, N, K, path) in [(gemm.GEMM_BF16, 128, 16384, 16384, "+splitK(4)(rotated)"), (gemm.GEMM_BF16, 128, 8192, 16384, "+splitK(8)(rotated)"),
+                                (gemm.GEMM_F16, 97, 12288, 8192, "+splitK(4)(rotated)"), (gemm.GEMM_F16, 97, 12287, 8192, "+splitK(4)"),
                                 (gemm.GEMM_BF16, 128, 8192, 8192, "+splitK(8)"), (gemm.GEMM_BF16, 128, 2048, 4096, "+splitK(4)"),
                                 (gemm.GEMM_BF16, 129, 8192, 16384, "+splitK(4)"),
-                                (gemm.GEMM_FP8_E4M3, 128, 12288, 16384, "+splitK(4,rotated)"), (gemm.GEMM_FP8_E4M3, 128, 8192, 16384, "+splitK(8)")]:
+                                (gemm.GEMM_FP8_E4M3, 128, 12288, 16384, "+splitK(4)(rotated)"), (gemm.GEMM_FP8_E4M3, 128, 8192, 16384, "+splitK(8)")]:
         q = gemm.gemm_query(gemm.GEMM_K4_MFMA, gemm.make_desc(M, N, K, dt, gemm.GEMM_F32, ROW, COL, workspace=4096, workspace_bytes=1 << 40))
         assert q.status == gemm.GEMM_OK and q.path == "mfma32-direct-to-lds" + path, (dt, M, N, K, q.path)
