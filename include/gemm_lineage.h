@@ -149,10 +149,13 @@ typedef struct {
                                         with scratch of at least gemm_query's workspace_bytes it packs the
                                         operands (K contiguous, aligned, zero-padded K; an operand that meets
                                         the conditions by itself is used in place when K is whole slabs) and
-                                        runs the fast kernel on the copies; without scratch a product with A and
+                                        runs the fast kernel on the copies, or, where that is faster (small
+                                        products of bf16 and fp16), multiplies both operands where they lie and
+                                        leaves the scratch alone, which is asked for and checked all the same;
+                                        without scratch a product with A and
                                         B row-major and at least 256 tiles of 256 x 256 (bf16, fp16) is multiplied
-                                        in place by the persistent kernel (gemm_query names the path), any other
-                                        by the masked kernel.  (2) The
+                                        in place by the persistent kernel, any other in the masked state
+                                        (gemm_query names the path).  (2) The
                                         fast path applies but the product has too few tiles to fill the chip
                                         and a long K (batch 1, 17 or more rows): with scratch it splits K into
                                         ranges that run side by side and adds their fp32 partial products in a
@@ -174,8 +177,11 @@ typedef struct {
     int32_t  stages;          /* LDS buffers in flight */
     int32_t  lds_bytes;       /* static + dynamic LDS per workgroup */
     int64_t  grid;            /* workgroups launched */
-    size_t   workspace_bytes; /* scratch the packed or split-K path of K4 uses for this call (0: no path would use any) */
-    char     path[64];        /* name of the code path gemm_run_ex would take */
+    size_t   workspace_bytes; /* scratch to lend for the packed or split-K path of K4 (0: no path would use any; asked for
+                                 also where the product is then multiplied in place, which `path` shows) */
+    char     path[64];        /* name of the code path gemm_run_ex would take (K4's masked state: "vec16" and "elementwise"
+                                 say whether an operand's rows are aligned to 16 bytes with K contiguous or to an element
+                                 only, "(direct-to-lds)" that its loads go to LDS 16 bytes at a time all the same) */
 } gemm_query_t;
 
 /*

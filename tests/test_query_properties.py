@@ -137,7 +137,9 @@ def test_expert_state_paths_and_scratch(p):
         assert q.workspace_bytes == p["batch"] * ((0 if a_ok else p["M"]) + (0 if b_ok else p["N"])) * kp * es
         lent = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p, workspace=4096, workspace_bytes=q.workspace_bytes))
         tag = "(B)" if a_ok else "(A)" if b_ok else ""
-        assert lent.status == gemm.GEMM_OK and lent.path.startswith("mfma32-packed%s+direct-to-lds" % tag)
+        in_place = lent.path == q.path and q.path.endswith("(direct-to-lds)")       # (with scratch lent as without: the lines have a test of their own)
+        assert lent.status == gemm.GEMM_OK and (in_place or lent.path.startswith("mfma32-packed%s+direct-to-lds" % tag))
+        assert not in_place or (es == 2 and p["batch"] == 1)
         small = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p, workspace=4096, workspace_bytes=q.workspace_bytes - 1))
         assert small.status == gemm.GEMM_ERR_WORKSPACE
         odd = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p, workspace=4100, workspace_bytes=q.workspace_bytes))
@@ -203,15 +205,15 @@ def test_packed_or_in_place_by_size_layout_and_alignment():
             ld = lambda x: next(y for y in range(x, x + 17) if y % (2 * al if al < 8 else 8) == (al if al < 8 else 0))
             p = dict(M=M, N=N, K=K, dt=dt, out=dt, la=la, lb=lb, lda=ld(K if la == ROW else M), ldb=ld(N if lb == ROW else K), ldc=N, batch=1)
             need = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p)).workspace_bytes
-            assert need > 0
+            assert need > 0 and gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p)).path.endswith("(direct-to-lds)")
             q = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p, workspace=4096, workspace_bytes=need))
-            assert q.status == gemm.GEMM_OK and ("in-place" in q.path) == in_place, (M, N, K, la, lb, al, q.path)
+            assert q.status == gemm.GEMM_OK and q.path.endswith("(direct-to-lds)") == in_place and ("packed" in q.path) != in_place, (M, N, K, la, lb, al, q.path)
     # an operand's address counts as its rows do
     p = dict(M=2000, N=2000, K=2400, dt=gemm.GEMM_BF16, out=gemm.GEMM_BF16, la=COL, lb=ROW, lda=2000, ldb=2000, ldc=2000, batch=1)
     need = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p)).workspace_bytes
     for A, B, in_place in [(4096, 4096, True), (4098, 4096, False), (4096, 4098, False), (4100, 4096, True)]:
         q = gemm.gemm_query(gemm.GEMM_K4_MFMA, make(p, workspace=4096, workspace_bytes=need), A, B)
-        assert ("in-place" in q.path) == in_place, (A, B, q.path)
+        assert q.path.endswith("(direct-to-lds)") == in_place and ("packed" in q.path) != in_place, (A, B, q.path)
 
 
 def test_which_k_ranges_run_with_a_rotated_walk():

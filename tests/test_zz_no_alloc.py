@@ -57,10 +57,10 @@ def test_split_k_on_the_static_scratch_twice_the_second_call_smaller():
 
 
 def test_packed_path_on_the_static_scratch_twice_the_second_call_smaller():
-    big = gen.Config("static_packed_big", 1500, 1203, 1999, gen.F16, gen.F16, ROW, ROW, "uniform", lda=2001, ldb=1205, ldc=1207)
+    big = gen.Config("static_packed_big", 1500, 1203, 1999, gen.F16, gen.F16, ROW, ROW, "uniform", batch=2, lda=2001, ldb=1205, ldc=1207)
     small = gen.Config("static_packed_small", 300, 270, 203, gen.E4M3, gen.BF16, COL, ROW, "uniform", batch=2, lda=303, ldb=275)
     for cfg, seed in ((big, 2), (small, 3)):
-        got, want, inp = both_ways(cfg, seed, "packed")
+        got, want, inp = both_ways(cfg, seed, "mfma32-packed+direct-to-lds")
         assert torch.equal(got, want), cfg.name
         C_ref, D = oracle.gemm(cfg.in_dtype, cfg.layout_a, cfg.layout_b, cfg.M, cfg.N, cfg.K, inp.A, inp.lda, inp.B, inp.ldb,
                                batch=cfg.batch, stride_a=inp.stride_a, stride_b=inp.stride_b)
