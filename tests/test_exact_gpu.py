@@ -419,10 +419,62 @@ def test_streaming_kernel_on_few_columns_is_exact(dtype):
 
 @pytest.mark.parametrize("dtype", DTYPES + [gen.F32])
 def test_masked_kernel_is_exact(dtype):
-    """No scratch, ragged K, odd leading dimensions: the masked kernel in both of its tile sizes."""
+    """No scratch, ragged K, odd leading dimensions: the masked state in both of its tile sizes.  e4m3 runs the
+    element-by-element kernel, the other types their direct-to-LDS form (the element-by-element one: next test)."""
     for (M, N, K) in [(259, 130, 1000), (1100, 2100, 203)]:
         inp = int_inputs(dtype, M, N, K, ROW, ROW, lda=K + 1, ldb=N + 3, seed=K)
         run_exact(inp, "masked", exact_path=False)
+
+
+@pytest.mark.parametrize("dtype", [gen.BF16, gen.F16])
+@pytest.mark.parametrize("la,lb", [(ROW, ROW), (COL, ROW), (COL, COL), (ROW, COL)])
+def test_element_by_element_kernel_on_operands_ending_at_the_end_of_a_page_is_exact(dtype, la, lb):
+    """Odd-length last rows whose operand ends a 4 KiB page: 64-tiles and (from 256 of them) 128-tiles, one slab less an
+    element up to five, NaN in the gaps between rows."""
+    for (M, N, K, batch, bm) in [(131, 197, 63, 1, 64), (99, 65, 305, 3, 64), (2051, 2101, 67, 1, 128)]:
+        inp = int_inputs(dtype, M, N, K, la, lb, batch=batch, ldc=N + 1, seed=K, biased=True)
+        dA, dB = at_page_end(inp.A, True), at_page_end(inp.B, True)
+        d = gemm.make_desc(M, N, K, dtype, gen.F32, la, lb, ldc=N + 1, batch=batch)
+        q = gemm.gemm_query(K4, d, dA, dB)
+        assert q.path == "mfma32-elementwise-masked" and q.bm == bm, q
+        C_ref, _ = oracle_for(inp)
+        rc, C, _ = util.run_config(K4, inp, dA=dA, dB=dB)
+        assert rc == gemm.GEMM_OK, gemm.gemm_status_string(rc)
+        np.testing.assert_array_equal(C[:, :, :N], C_ref)
+
+
+def spread_rows(arr, rows, ext, ld, dtype):
+    """Dense raw rows on the GPU, `ld` elements apart, NaN between them."""
+    flat = torch.full((rows * ld,), float("nan"), dtype={gen.F32: torch.float32, gen.BF16: torch.bfloat16, gen.F16: torch.float16}[dtype], device="cuda")
+    flat.view(rows, ld)[:, :ext] = torch.from_numpy(np.ascontiguousarray(arr).view(np.uint8)).cuda().view(flat.dtype).view(rows, ext)
+    return flat
+
+
+@pytest.mark.parametrize("dtype", [gen.F32, gen.BF16, gen.F16])
+@pytest.mark.parametrize("over", [0, 1])
+def test_masked_state_at_the_addressing_limits_of_its_direct_to_lds_form_is_exact(dtype, over):
+    """Rows of 4 MiB, and k lines that span 2 GiB with two slabs of overshoot: the direct-to-LDS form at its limits, the
+    element-by-element kernel an element beyond them (both tile sizes of it)."""
+    es, K = gen.ELEM_BYTES[dtype], 70
+    row, line = (1 << 22) // es, ((1 << 31) - 1) // es // (K + 2 * 128 // es)
+    for (M, N, la, lb, lda, ldb, bm) in [(130, 67, ROW, ROW, row + over, 67, 64), (67, 130, COL, COL, 67, row + over, 64),
+                                         (130, 67, COL, COL, line + over, K, 64), (67, 130, ROW, ROW, K, line + over, 64),
+                                         (70, 32800, ROW, ROW, row + over, 32800, 128)]:
+        inp = int_inputs(dtype, M, N, K, la, lb, seed=M)
+        C_ref, _ = oracle_for(inp)
+        dA = spread_rows(inp.A, *((M, K) if la == ROW else (K, M)), lda, dtype)
+        dB = spread_rows(inp.B, *((K, N) if lb == ROW else (N, K)), ldb, dtype)
+        dC = torch.full((M, N), float("nan"), device="cuda")
+        d = gemm.make_desc(M, N, K, dtype, gen.F32, la, lb, lda=lda, ldb=ldb)
+        q = gemm.gemm_query(K4, d, dA, dB, dC)
+        assert "masked" in q.path and q.path.endswith("(direct-to-lds)") == (over == 0), q.path
+        if over:
+            assert q.bm == bm
+        assert gemm.gemm_run_ex(K4, d, dA, dB, dC) == gemm.GEMM_OK
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(dC.cpu().numpy(), C_ref[0])
+        del dA, dB, dC
+        torch.cuda.empty_cache()
 
 
 def test_headline_shape_full_size_is_exact():

@@ -7,6 +7,7 @@ the problem.
 """
 import math
 
+import pytest
 from hypothesis import given, settings, strategies as st
 
 from paper_2605_28213_amd import gemm
@@ -225,3 +226,43 @@ def test_which_k_ranges_run_with_a_rotated_walk():
                                 (gemm.GEMM_FP8_E4M3, 128, 12288, 16384, "+splitK(4)(rotated)"), (gemm.GEMM_FP8_E4M3, 128, 8192, 16384, "+splitK(8)")]:
         q = gemm.gemm_query(gemm.GEMM_K4_MFMA, gemm.make_desc(M, N, K, dt, gemm.GEMM_F32, ROW, COL, workspace=4096, workspace_bytes=1 << 40))
         assert q.status == gemm.GEMM_OK and q.path == "mfma32-direct-to-lds" + path, (dt, M, N, K, q.path)
+
+
+def _direct_form(M, N, K, dt, la, lb, A=4096, B=4096, **kw):
+    out = gemm.GEMM_BF16 if dt == gemm.GEMM_FP8_E4M3 else dt
+    q = gemm.gemm_query(gemm.GEMM_K4_MFMA, gemm.make_desc(M, N, K, dt, out, la, lb, **kw), A, B)
+    assert q.status == gemm.GEMM_OK and "masked" in q.path, q.path
+    return q.path.endswith("(direct-to-lds)")
+
+
+@pytest.mark.parametrize("dt", [gemm.GEMM_F32, gemm.GEMM_BF16, gemm.GEMM_F16])
+def test_addressing_limits_of_the_masked_states_direct_to_lds_form(dt):
+    """Rows of 4 MiB where K is contiguous, 2 GiB of k lines (with two slabs of overshoot) where it is not: both sides
+    of each limit, for either operand."""
+    es = ES[dt]
+    row = (1 << 22) // es
+    assert _direct_form(70, 65, 33, dt, ROW, ROW, lda=row, ldb=65) and not _direct_form(70, 65, 33, dt, ROW, ROW, lda=row + 1, ldb=65)
+    assert _direct_form(70, 65, 33, dt, COL, COL, lda=71, ldb=row) and not _direct_form(70, 65, 33, dt, COL, COL, lda=71, ldb=row + 1)
+    for K in (1, 70, 1000):
+        line = ((1 << 31) - 1) // es // (K + 2 * 128 // es)
+        assert _direct_form(70, 65, K, dt, COL, COL, lda=line, ldb=K + 1) and not _direct_form(70, 65, K, dt, COL, COL, lda=line + 1, ldb=K + 1)
+        assert _direct_form(70, 65, K, dt, ROW, ROW, lda=K + 1, ldb=line) and not _direct_form(70, 65, K, dt, ROW, ROW, lda=K + 1, ldb=line + 1)
+    assert not _direct_form(70, 65, 33, gemm.GEMM_FP8_E4M3, ROW, ROW)
+
+
+@pytest.mark.parametrize("dt", [gemm.GEMM_F32, gemm.GEMM_BF16, gemm.GEMM_F16])
+@pytest.mark.parametrize("la", [ROW, COL])
+@pytest.mark.parametrize("lb", [ROW, COL])
+@pytest.mark.parametrize("batch", [1, 3])
+def test_an_odd_last_row_at_the_end_of_a_page_keeps_the_element_by_element_kernel(dt, la, lb, batch):
+    """Two-byte rows are loaded as dwords from their first element, so an odd-length last row reaches one element past
+    the operand: refused where that may not be mapped, whatever the layout and whichever operand."""
+    es = ES[dt]
+    for odd in (0, 1):
+        M, N, K = 130 + odd, 70 + odd, 40 + odd
+        ra, ea, rb, eb = (M, K, K, N) if (la, lb) == (ROW, ROW) else (M, K, N, K) if (la, lb) == (ROW, COL) else (K, M, K, N) if lb == ROW else (K, M, N, K)
+        kw = dict(lda=ea + 2, ldb=eb + 2, batch=batch, stride_a=ra * (ea + 2), stride_b=rb * (eb + 2))
+        end = lambda rows, ext: ((batch - 1) * rows * (ext + 2) + (rows - 1) * (ext + 2) + ext) * es
+        at = lambda rows, ext, off: (1 << 20) - end(rows, ext) + off
+        for A, B, tail in [(at(ra, ea, 0), 4096, True), (4096, at(rb, eb, 0), True), (at(ra, ea, -es), 4096, False), (4096, at(rb, eb, 4), False)]:
+            assert _direct_form(M, N, K, dt, la, lb, A, B, **kw) == (not (tail and odd and es == 2)), (A, B, odd)
