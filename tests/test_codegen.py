@@ -138,6 +138,37 @@ def test_static_scratch_array_is_a_visible_device_symbol(tmp_path):
     assert re.search(r"\.size\s+%s, %d\b" % (re.escape(m.group(1)), mib << 20), text)
 
 
+def check_wait_states_of_inline_loads(text, at_least):
+    """Every direct load issued from inline assembly keeps the wait states gfx9 does not interlock (and the compiler's
+    hazard pass does not place inside inline assembly): one after the scalar write of M0, and five after a vector
+    instruction that wrote a scalar register the load reads as descriptor or offset (a scalar spill reload is one)."""
+    code = [l.strip() for l in text.split("\n")]
+    code = [l for l in code if l and not l.startswith((";", ".", "//")) and not l.endswith(":")]
+    loads = [i for i, l in enumerate(code) if l.startswith("buffer_load_dwordx4") and l.endswith("lds")]
+    assert len(loads) >= at_least
+    checked = 0
+    for i in loads:
+        assert code[i - 1].startswith("s_nop") and code[i - 2].startswith("s_mov_b32 m0"), code[i - 3:i + 1]
+        m = re.match(r"buffer_load_dwordx4 v\d+, s\[(\d+):(\d+)\], (s\d+|vcc_lo|vcc_hi) offen lds", code[i])
+        assert m, code[i]
+        used = {"s%d" % r for r in range(int(m.group(1)), int(m.group(2)) + 1)} | {m.group(3)}
+        waited, j = 0, i - 1
+        while waited < 5 and j >= 0:
+            ins = code[j]
+            w = re.match(r"(v_readlane_b32|v_readfirstlane_b32) (s\d+|vcc_lo|vcc_hi),", ins)
+            assert not (w and w.group(2) in used), (code[j:i + 1], "a scalar register written by a vector instruction is read %d wait states later" % waited)
+            if used & {"vcc_lo", "vcc_hi"}:     # (the implicit destination of the short compare and carry forms)
+                assert not re.match(r"v_(cmp|cmpx|add_co|sub_co|subrev_co|addc_co|subb_co|div_scale)", ins), code[j:i + 1]
+            w = re.match(r"v_\S+ (s\[(\d+):(\d+)\]|s\d+),", ins)       # any other vector instruction with a scalar destination
+            if w:
+                regs = {w.group(1)} if w.group(2) is None else {"s%d" % r for r in range(int(w.group(2)), int(w.group(3)) + 1)}
+                assert not (regs & used), code[j:i + 1]
+            waited += (int(ins.split()[1]) + 1) if ins.startswith("s_nop") else 1
+            j -= 1
+        checked += 1
+    assert checked == len(loads)
+
+
 def test_persistent_kernel_slab_loop(tmp_path):
     """The persistent form of the 256-tile kernel: the middle-slab loop holds one slab (64 or 32 matrix instructions,
     32 fragment reads, 16 direct loads issued from inline assembly, one barrier, the one hand-placed vmcnt wait),
@@ -168,34 +199,7 @@ def test_persistent_kernel_slab_loop(tmp_path):
         meta = metadata(text, prefix)
         assert meta["agpr"] == 256 and meta["lds"] == 160 * 1024
         assert meta["vgpr_spill"] == (0 if dtype != "4E4M3" else meta["vgpr_spill"]) and meta["vgpr_spill"] <= 2
-    # Every direct load issued from inline assembly keeps the wait states gfx9 does not interlock (and the compiler's
-    # hazard pass does not place inside inline assembly): one after the scalar write of M0, and five after a vector
-    # instruction that wrote a scalar register the load reads as descriptor or offset (a scalar spill reload is one).
-    code = [l.strip() for l in text.split("\n")]
-    code = [l for l in code if l and not l.startswith((";", ".", "//")) and not l.endswith(":")]
-    loads = [i for i, l in enumerate(code) if l.startswith("buffer_load_dwordx4") and l.endswith("lds")]
-    assert len(loads) > 100
-    checked = 0
-    for i in loads:
-        assert code[i - 1].startswith("s_nop") and code[i - 2].startswith("s_mov_b32 m0"), code[i - 3:i + 1]
-        m = re.match(r"buffer_load_dwordx4 v\d+, s\[(\d+):(\d+)\], (s\d+|vcc_lo|vcc_hi) offen lds", code[i])
-        assert m, code[i]
-        used = {"s%d" % r for r in range(int(m.group(1)), int(m.group(2)) + 1)} | {m.group(3)}
-        waited, j = 0, i - 1
-        while waited < 5 and j >= 0:
-            ins = code[j]
-            w = re.match(r"(v_readlane_b32|v_readfirstlane_b32) (s\d+|vcc_lo|vcc_hi),", ins)
-            assert not (w and w.group(2) in used), (code[j:i + 1], "a scalar register written by a vector instruction is read %d wait states later" % waited)
-            if used & {"vcc_lo", "vcc_hi"}:     # (the implicit destination of the short compare and carry forms)
-                assert not re.match(r"v_(cmp|cmpx|add_co|sub_co|subrev_co|addc_co|subb_co|div_scale)", ins), code[j:i + 1]
-            w = re.match(r"v_\S+ (s\[(\d+):(\d+)\]|s\d+),", ins)       # any other vector instruction with a scalar destination
-            if w:
-                regs = {w.group(1)} if w.group(2) is None else {"s%d" % r for r in range(int(w.group(2)), int(w.group(3)) + 1)}
-                assert not (regs & used), code[j:i + 1]
-            waited += (int(ins.split()[1]) + 1) if ins.startswith("s_nop") else 1
-            j -= 1
-        checked += 1
-    assert checked == len(loads)
+    check_wait_states_of_inline_loads(text, 100)
     # the form that reads a row-major B in place: per slab 16 fragment reads of A and 32 transposing reads of B
     for dtype, mfma in (("4BF16", "v_mfma_f32_32x32x16_bf16"), ("3F16", "v_mfma_f32_32x32x16_f16")):
         prefix = "_ZN2gl12k4_mfma_ringINS_7RingCfgINS_" + dtype + "ELi8ELb1E"
@@ -207,3 +211,29 @@ def test_persistent_kernel_slab_loop(tmp_path):
         assert count("buffer_load_dwordx4") == 16 and count("s_barrier") == 1
         meta = metadata(text, prefix)
         assert meta["vgpr_spill"] == 0 and meta["scratch"] == 0 and meta["lds"] == 160 * 1024
+
+
+def test_masked_states_direct_to_lds_form(tmp_path):
+    """Every instantiation: nothing spilled, no scratch, the LDS of its ring, resources that stay in scalar registers (one
+    that the compiler takes for lane-dependent would be read lane by lane in a loop round every load), the loads'
+    hand-placed wait states, and the matrix instruction of its type."""
+    src = os.path.join(ROOT, "paper_2605_28213_amd", "csrc", "k4_direct.hip")
+    out = tmp_path / "direct.s"
+    flags = [f for f in gl_build.FLAGS if f != "-fPIC"] + gl_build.EXTRA_FLAGS.get("k4_direct.hip", [])
+    r = subprocess.run(["hipcc", *flags, "-S", "--cuda-device-only", src, "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    text = out.read_text()
+    names = re.findall(r"^(_ZN2gl14k4_mfma_directINS_9DirectCfgINS_(?:3F32|3F16|4BF16)ELi\d+ELi\d+ELi\d+ELb[01]ELb[01]E\w*):", text, flags=re.M)
+    assert len(names) == 8 + 2 * 17         # four layouts of two fp32 forms and of four two-byte ones, few tiles in one layout
+    for name in names:
+        dtype, tile, parts, stages, ka, kb = re.search(r"INS_\d(F32|F16|BF16)ELi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELb([01])E", name).groups()
+        side, stages = int(tile) // int(parts), int(stages)
+        body = re.search(r"^%s:[^\n]*\n(.*?)\.Lfunc_end" % re.escape(name), text, flags=re.S | re.M).group(1)
+        ops = [l.split()[0] for l in body.split("\n") if l.strip() and not l.strip().startswith((";", "."))]
+        count = lambda o: ops.count(o)
+        meta = metadata(text, name)
+        assert meta["vgpr_spill"] == 0 and meta["scratch"] == 0 and meta["lds"] == stages * 2 * side * 128, (name, meta)
+        assert meta["vgpr"] <= 256 and count("v_readlane_b32") == 0 and count("v_readfirstlane_b32") <= 4, name
+        assert count({"F32": "v_mfma_f32_32x32x2_f32", "F16": "v_mfma_f32_32x32x16_f16", "BF16": "v_mfma_f32_32x32x16_bf16"}[dtype]) > 0
+        assert (count("ds_read_b64_tr_b16") > 0) == (dtype != "F32" and "0" in (ka, kb)), name
+    check_wait_states_of_inline_loads(text, 8 * len(names))
