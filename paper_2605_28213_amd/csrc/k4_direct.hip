@@ -31,14 +31,18 @@ bool k4_direct_applies(const Args& a)
 }
 
 // Which form multiplies a product: by how many tiles it has for the 256 CUs.
-//   fp32 (row-major A and B; the matrix pipe bounds it, so no CU may be idle): quarters of 64-tiles up to 192 tiles
-//     (512^3, 64 tiles: 7.0 against 13.4 us; 2300 x 300 x 2300, 180: 36 / 48; 777 x 1111 x 555, 234: 17.5 / 16.2), whole
-//     64-tiles beyond, two slabs of LDS each so that five workgroups share a CU and fill each other's barriers
-//     (2048^3: 126 us against 137 with 128-tiles; 2300^3: 208 / 266; with three slabs 171 / 233).
+//   fp32 (the matrix pipe bounds it, so no CU may be idle): quarters of 64-tiles up to 192 tiles (row-major A and B:
+//     512^3, 64 tiles, 7.1 against 12.7 us; 2300 x 300 x 2300, 180, 35 / 48; 896 x 832 x 800, 182, 14.6 / 18.8;
+//     777 x 1111 x 555, 234, 15.4 / 15.0), whole 64-tiles beyond, two slabs of LDS each so that five workgroups share a CU
+//     and fill each other's barriers (2048^3 128 us against 141 with 128-tiles and 138 with four slabs; 2300^3 208 / 266 /
+//     229; 5000 x 5000 x 2000 747 / 834 / 841; 8192 x 8192 x 512 516 / 501 / 587).
 //   two-byte types (loads and barriers bound it): quarters up to 96 tiles of 64 (200 x 300 x 4000, 20: 13.4 against
 //     20.1 us; 1000^3, 256: 14.3 / 8.7), whole 64-tiles with four slabs below 128 tiles of 128, then 128-tiles: one
 //     workgroup per CU with four slabs up to 256 of them (4300 x 700 x 4300, 204: 47 against 63 us with 64-tiles and 59
 //     with two slabs; 1500^3, 144: 23.1 / 24.3 / 26.3), two with two slabs beyond (3000 x 2000 x 4000, 384: 61 against 82 us).
+// The lines were drawn on row-major operands.  In all four layouts, rows 4 or 16 bytes (fp32), 2 or 4 bytes aligned, every
+// product in each of five forms: the form chosen is within a twentieth of the best on 121 of 156 fp32 products, 1.17 at
+// worst (1000^3 with K contiguous in both: quarters 21.5 us, whole 64-tiles 25.2), and on 142 of 152 of fp16, 1.19 at worst.
 DirectForm k4_direct_form(const Args& a)
 {
     const int64_t t64 = ((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch, t128 = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
@@ -92,9 +96,12 @@ static Geometry geometry_of(const Args& a, const DirectForm& f)
 Geometry geometry_k4_direct(const Args& a) { return geometry_of(a, k4_direct_form(a)); }
 
 // Products that meet the fast kernel's conditions but have few tiles: its 128-tiles leave most CUs idle, so a 128-tile is
-// shared by sixteen workgroups of 32 x 32 (fp16 392 x 304 x 320: the fast kernel takes 11.4 us, quarters of 64-tiles 6.6 us
-// on the same sizes unaligned).  The line is that of the quarters, 96 tiles of 64; where split-K applies the product
-// stays with the kernel that the ranges run on.
+// shared by sixteen workgroups of 32 x 32.  Fast kernel / shared, bf16: 512 x 512 (64 tiles of 64) x 64 4.1 / 3.9 us, x 256
+// 6.6 / 3.9, x 1024 10.5 / 5.9; 768 x 512 (96) x 64 4.1 / 3.8, x 512 6.7 / 5.0, x 1024 10.5 / 6.5; 24 x 128 x 128 x 4096 (96)
+// 31.6 / 14.8.  The line is that of the quarters above, 96 tiles, well on the side where sharing wins: it would up to 192
+// (1024 x 768 x 64 4.2 / 4.1, x 1024 10.6 / 7.7) and loses from 224 on (1024 x 896 x 64 4.2 / 4.7, x 128 5.0 / 5.0).  A
+// product that split-K applies to stays with the kernel that the ranges run on, also where no scratch is lent for them
+// (512 x 512 x 4096 27.6 / 13.3).
 constexpr DirectForm FEW_TILES{128, 4, 4};
 bool k4_direct_takes_few_tiles(const Args& a)
 {

@@ -13,10 +13,10 @@
 // of STAGES slabs, one barrier per slab, STAGES - 1 slabs in flight.  What lies beyond K in the last slab is cleared
 // in LDS by the lanes that loaded it.
 //
-// Element by element against this form, row-major A and B: fp32 256^3 14.9 -> 8.0 us, fp32 2048^3 205 -> 136 us (126
+// Element by element against this form, row-major A and B: fp32 256^3 14.9 -> 4.9 us, fp32 2048^3 206 -> 128 us (134
 // TFLOP/s: the matrix pipe, whose fp32 instructions take 109 us at 2.4 GHz), fp16 1000^3 31.2 -> 8.1 us.  Small products
 // are bound by the latency of the first slabs and one barrier per slab, which is why the ring is filled before the
-// first wait; fp32 gives each 16-byte read 64 cycles of matrix work and needs no deeper ring.
+// first wait; where fp32 has tiles enough for five workgroups per CU, they hide it and two slabs each do.
 #pragma once
 #include "k4_kernels.hpp"
 
