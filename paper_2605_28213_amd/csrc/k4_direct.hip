@@ -60,13 +60,14 @@ DirectForm k4_direct_form(const Args& a)
 //   at most one 64-tile per CU: 0.44 in the mean, 0.87 at worst;
 //   otherwise, up to the line / beyond it:
 //     rows aligned to           16 bytes           8                  4                  2
-//     K contiguous in both      13 G 0.75 / 1.00   10 G 0.70 / 1.06   5 G 0.61 / 0.95    3 G 0.66 / 0.98
-//     other layouts             25 G 0.71 / 0.81   16 G 0.69 / 0.90   13 G 0.68 / 0.88   8 G 0.67 / 1.01
-//     K beyond 4800             10 G 0.78 / 0.92   6 G 0.92 / 0.95    5 G - / 0.96       5 G - / 1.00
+//     K contiguous in both      13 G 0.76 / 0.99   10 G 0.70 / 1.06   5 G 0.61 / 0.95    3 G 0.66 / 0.98
+//     other layouts             25 G 0.72 / 0.88   16 G 0.69 / 0.90   13 G 0.68 / 0.88   8 G 0.67 / 1.01
+//     K beyond                  6400               4800               4800               4800
+//                               10 G 0.79 / 0.94   6 G 0.92 / 0.95    5 G - / 0.96       5 G - / 1.00
 //   where one operand is packed that has at most a quarter of the other's rows, which is cheap, 10 G 0.64 / 0.97 (and
-//   0.6 G at a 64th: 32 x 16384 x 4096 40 against 37 us, 64 x 16384 x 8192 81 / 77).
-// Beyond the lines lie the products that lose much (904 x 5071 x 4317 with odd rows 99 to 116 us against 70): of the 877
-// up to them one is slower than packed by more than a twentieth in the mean, 26 in one of the two measurements, 1.19 at
+//   0.6 G at a 64th: 32 x 16384 x 4096 40 against 37 us, 16384 x 64 x 8192 81 / 77).
+// Beyond the lines lie the products that lose much (904 x 5071 x 4317 with odd rows 99 to 116 us against 70): of the 900
+// up to them one is slower than packed by more than a twentieth in the mean, 28 in one of the two measurements, 1.20 at
 // worst.  Measured on single products; batches keep the packed path.
 bool k4_direct_beats_packing(const Args& a, int keep_mask)
 {
@@ -82,7 +83,7 @@ bool k4_direct_beats_packing(const Args& a, int keep_mask)
         const int align = low % 16 == 0 ? 0 : low % 8 == 0 ? 1 : low % 4 == 0 ? 2 : 3;
         static const double BOTH_KC[4] = {13e9, 10e9, 5e9, 3e9}, OTHER[4] = {25e9, 16e9, 13e9, 8e9}, LONG_K[4] = {10e9, 6e9, 5e9, 5e9};
         limit = std::min(limit, (ka && kb ? BOTH_KC : OTHER)[align]);
-        if (a.K > 4800) limit = std::min(limit, LONG_K[align]);
+        if (a.K > (align == 0 ? 6400 : 4800)) limit = std::min(limit, LONG_K[align]);
     }
     return work <= limit;
 }

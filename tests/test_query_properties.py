@@ -192,7 +192,8 @@ IN_PLACE_LINES = [  # (M, N, K, layouts, multiple of elements that leading dimen
     (2000, 2000, 3990, ROW, ROW, 4, True), (2000, 2000, 4010, ROW, ROW, 4, False),          # other layouts: 25, 16, 13, 8
     (2000, 2000, 3240, COL, COL, 2, True), (2000, 2000, 3260, COL, COL, 2, False),
     (2000, 2000, 1990, COL, ROW, 1, True), (2000, 2000, 2010, COL, ROW, 1, False),
-    (1400, 1400, 4800, COL, ROW, 1, False), (1200, 1400, 4800, COL, ROW, 4, True), (1400, 1400, 5000, COL, ROW, 8, True), (1500, 1400, 5000, COL, ROW, 8, False),   # long K
+    (1400, 1400, 4800, COL, ROW, 1, False), (1200, 1400, 4800, COL, ROW, 4, True), (2000, 1900, 6400, COL, ROW, 8, True),   # long K
+    (1200, 1290, 6408, COL, ROW, 8, True), (1300, 1290, 6408, COL, ROW, 8, False),
     (1200, 1000, 5000, ROW, ROW, 4, True), (1300, 1000, 5000, ROW, ROW, 4, False),
     (4096, 1000, 2432, ROW, ROW, 8, True), (4096, 1000, 2496, ROW, ROW, 8, False),          # B alone is packed, A has four times its rows: 10
     (64, 16384, 512, COL, COL, 8, True), (64, 16384, 1024, COL, COL, 8, False),             # A alone, B has 256 times: 0.6
