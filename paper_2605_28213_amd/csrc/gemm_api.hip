@@ -204,11 +204,11 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
         const bool can_pack = !f32 && d->K > 0 && k4_packed_k(a) * es <= ((int64_t)1 << 22) &&
                               (d->M + d->N) * k4_packed_k(a) < ((int64_t)1 << 40);
         // the masked state: what the operands' alignment allows, and whether its direct-to-LDS form runs
-        auto name_masked = [&]() {
-            snprintf(splitk_path, sizeof(splitk_path), "mfma32-%s%s", va && vb ? "vec16-masked" : va ? "vec16(A)+elementwise-masked(B)"
-                     : vb ? "elementwise-masked(A)+vec16(B)" : "elementwise-masked", k4_direct_applies(a) ? "(direct-to-lds)" : "");
-            path = splitk_path;
-        };
+        static const char* const MASKED_PATHS[2][4] = {
+            {"mfma32-elementwise-masked", "mfma32-vec16(A)+elementwise-masked(B)", "mfma32-elementwise-masked(A)+vec16(B)", "mfma32-vec16-masked"},
+            {"mfma32-elementwise-masked(direct-to-lds)", "mfma32-vec16(A)+elementwise-masked(B)(direct-to-lds)",
+             "mfma32-elementwise-masked(A)+vec16(B)(direct-to-lds)", "mfma32-vec16-masked(direct-to-lds)"}};
+        auto masked_path = [&]() { return MASKED_PATHS[k4_direct_applies(a) ? 1 : 0][(va ? 1 : 0) | (vb ? 2 : 0)]; };
         if (skinny) {
             p.path = MFMA_SKINNY;
             path = "mfma16-stream(small-M)";
@@ -256,19 +256,20 @@ Plan make_plan(int variant, const gemm_desc_t* d, const void* A, const void* B, 
         } else if (can_pack && d->workspace != nullptr) {
             // the caller lent scratch: repair the violated conditions by packing, then run the fast kernel
             p.path = MFMA_PACKED | (keep << 8);
-            snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds%s%s", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "",
-                     k4_fast_is_persistent(MFMA_PACKED, a) ? "(persistent)" : "",
-                     k4_splits_m_tail(a) ? "+stream(M-tail)" : "");
-            path = splitk_path;
             if (k4_direct_beats_packing(a, keep)) {      // ... or multiply what lies there as it lies there (the scratch stays unused)
                 p.path |= MFMA_PACKED_IN_PLACE << 8;
-                name_masked();
+                path = masked_path();
+            } else {
+                snprintf(splitk_path, sizeof(splitk_path), "mfma32-packed%s+direct-to-lds%s%s", keep == 1 ? "(B)" : keep == 2 ? "(A)" : "",
+                         k4_fast_is_persistent(MFMA_PACKED, a) ? "(persistent)" : "",
+                         k4_splits_m_tail(a) ? "+stream(M-tail)" : "");
+                path = splitk_path;
             }
             pack_bytes = k4_packed_workspace_bytes(a, keep);
         } else {
             if (can_pack) pack_bytes = k4_packed_workspace_bytes(a, keep);   // what lending scratch would buy
             p.path = MFMA_ELEMENTWISE | (((va ? 1 : 0) | (vb ? 2 : 0)) << 8);
-            name_masked();
+            path = masked_path();
         }
         const int kind = p.path & 0xFF;
         g = kind == MFMA_PACKED && (p.path >> 8 & MFMA_PACKED_IN_PLACE) ? geometry_k4_direct(a)
