@@ -270,7 +270,7 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
 //   rows 1.32 (of one value 1.7), of 5000 0.70 and 0.85 (1.13), of 6000 0.60 and 0.66 (1.05).
 // The filter pays from 12288 elements on: general / filter 8192 elements, k = 512, 0.34 / 0.40; 12288 0.30 / 0.31;
 // 20000 0.26 / 0.24; 32768 0.23 / 0.17; and where the list overflows its two reads are lost (12288 zeros 0.65 / 0.83;
-// rows in ascending order, whose maxima come last, are the filter's best: 0.41 / 0.29).
+// rows in ascending order, whose neighbours fall into one bin of the histograms, 0.41 / 0.29).
 constexpr int LONG_T = 1024;
 constexpr int LONG_GROUPS = 4 * LONG_T;
 constexpr int LONG_CAP = 4096;                  // listed elements: 4 per lane
