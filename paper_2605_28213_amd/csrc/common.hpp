@@ -168,13 +168,19 @@ inline bool tail_element_in_last_page(const void* base, int64_t elems, int64_t l
 hipError_t launch_k4_thin_row_major_b(const Args& a);
 // The masked state's direct-to-LDS form (fp32, bf16, fp16; any layout and alignment): whether it takes a product, the
 // form it runs in (side of the tile, workgroups per tile and direction, slabs of the LDS ring) and its launcher.
-struct DirectForm { int tile, parts, stages; };
+// (wide: 128 or 256 rows of k4_wide.hpp's tiles instead, 0: none).
+struct DirectForm { int tile, parts, stages, wide = 0; };
 bool k4_direct_applies(const Args& a);
 DirectForm k4_direct_form(const Args& a);
 bool k4_direct_beats_packing(const Args& a, int keep_mask);     // in place rather than through the packed path, with scratch lent
 bool k4_direct_takes_few_tiles(const Args& a);   // instead of the fast kernel, whose conditions hold
 hipError_t launch_k4_few_tiles(const Args& a);
 hipError_t launch_k4_direct(const Args& a);
+// Wide tiles with loading waves (two-byte types, what k4_direct_applies allows): the rows of the tile (256 or 128; columns are
+// 128) when a product of at least `t128_from` 128-tiles is one round of the chip that they multiply faster, else 0.
+int k4_wide_round(const Args& a, int64_t t128_from, bool aligned);
+int k4_fast_wide(const Args& a);          // on a product that meets the fast kernel's conditions, instead of its 128-tiles
+hipError_t launch_k4_wide(const Args& a, int bm);
 
 hipError_t launch_k0(const Args& a);
 hipError_t launch_valu_tiled(int variant, int path, const Args& a);
@@ -195,6 +201,7 @@ Geometry geometry_k3_async(const Args& a);
 Geometry geometry_k4(int path, const Args& a);
 Geometry geometry_k4_direct(const Args& a);
 Geometry geometry_k4_few_tiles(const Args& a);
+Geometry geometry_k4_wide(const Args& a, int bm);
 Geometry geometry_k4_conv(const Args& a);
 
 }  // namespace gl

@@ -6,7 +6,7 @@
 namespace gl {
 
 // Tiles of a product, and the workgroups they are launched as (parts: padded to groups of eight tiles).
-static int64_t direct_tiles(const Args& a, const DirectForm& f) { return ((a.M + f.tile - 1) / f.tile) * ((a.N + f.tile - 1) / f.tile) * a.batch; }
+static int64_t direct_tiles(const Args& a, const DirectForm& f) { const int64_t cols = f.wide ? 128 : f.tile; return ((a.M + f.tile - 1) / f.tile) * ((a.N + cols - 1) / cols) * a.batch; }
 static int64_t direct_grid(const Args& a, const DirectForm& f) { return f.parts > 1 ? (direct_tiles(a, f) + 7) / 8 * 8 * f.parts * f.parts : direct_tiles(a, f); }
 
 // What the form asks for beyond the masked kernel: offsets that fit the loads' 32 bits (rows of a K-contiguous operand
@@ -40,6 +40,9 @@ bool k4_direct_applies(const Args& a)
 //     20.1 us; 1000^3, 256: 14.3 / 8.7), whole 64-tiles with four slabs below 128 tiles of 128, then 128-tiles: one
 //     workgroup per CU with four slabs up to 256 of them (4300 x 700 x 4300, 204: 47 against 63 us with 64-tiles and 59
 //     with two slabs; 1500^3, 144: 23.1 / 24.3 / 26.3), two with two slabs beyond (3000 x 2000 x 4000, 384: 61 against 82 us).
+//     From 6 slabs on, the wide tiles with loading waves take the one workgroup per CU (four slabs / wide, row-major: 2000 x
+//     2000 x 64 6.6 / 6.7, x 300 10.0 / 10.0, x 900 16.7 / 16.2; 1015 x 3863 x 1887 29.4 / 26.2; rows contiguous in both
+//     2048 x 2048 x 4096 43.1 / 34.5) and, where k4_wide_round draws the line, the products beyond.
 // The lines were drawn on row-major operands.  In all four layouts, rows 4 or 16 bytes (fp32), 2 or 4 bytes aligned, every
 // product in each of five forms: the form chosen is within a twentieth of the best on 121 of 156 fp32 products, 1.17 at
 // worst (1000^3 with K contiguous in both: quarters 21.5 us, whole 64-tiles 25.2), and on 142 of 152 of fp16, 1.19 at worst.
@@ -49,6 +52,8 @@ DirectForm k4_direct_form(const Args& a)
     if (a.in_dtype == GEMM_F32) return t64 <= 192 ? DirectForm{64, 2, 4} : DirectForm{64, 1, 2};
     if (t64 <= 96) return DirectForm{64, 2, 4};
     if (t128 < 128) return DirectForm{64, 1, 4};
+    if (a.K > 5 * (ROW_BYTES / 2))
+        if (const int bm = k4_wide_round(a, 128, false)) return DirectForm{bm, 1, 0, bm};
     return t128 <= 256 ? DirectForm{128, 1, 4} : DirectForm{128, 1, 2};
 }
 
@@ -91,25 +96,33 @@ bool k4_direct_beats_packing(const Args& a, int keep_mask)
 // stages: slabs in flight beyond the one in use
 static Geometry geometry_of(const Args& a, const DirectForm& f)
 {
+    if (f.wide) return geometry_k4_wide(a, f.wide);
     return Geometry{f.tile, f.tile, ROW_BYTES / elem_size(a.in_dtype), 256, f.stages - 1, f.stages * 2 * (f.tile / f.parts) * ROW_BYTES, direct_grid(a, f)};
 }
 
 Geometry geometry_k4_direct(const Args& a) { return geometry_of(a, k4_direct_form(a)); }
 
-// Products that meet the fast kernel's conditions but have few tiles: its 128-tiles leave most CUs idle, so a 128-tile is
-// shared by sixteen workgroups of 32 x 32.  Fast kernel / shared, bf16: 512 x 512 (64 tiles of 64) x 64 4.1 / 3.9 us, x 256
-// 6.6 / 3.9, x 1024 10.5 / 5.9; 768 x 512 (96) x 64 4.1 / 3.8, x 512 6.7 / 5.0, x 1024 10.5 / 6.5; 24 x 128 x 128 x 4096 (96)
-// 31.6 / 14.8.  The line is that of the quarters above, 96 tiles, well on the side where sharing wins: it would up to 192
-// (1024 x 768 x 64 4.2 / 4.1, x 1024 10.6 / 7.7) and loses from 224 on (1024 x 896 x 64 4.2 / 4.7, x 128 5.0 / 5.0).  A
-// product that split-K applies to stays with the kernel that the ranges run on, also where no scratch is lent for them
-// (512 x 512 x 4096 27.6 / 13.3).
-constexpr DirectForm FEW_TILES{128, 4, 4};
+// Products that meet the fast kernel's conditions but have few tiles: its 128-tiles leave most CUs idle.
+//   Up to 96 tiles of 64, a 128-tile is shared by sixteen workgroups of 32 x 32.  Fast kernel / shared, bf16: 512 x 512 (64
+//   tiles of 64) x 64 4.1 / 3.9 us, x 256 6.6 / 3.9, x 1024 10.5 / 5.9; 768 x 512 (96) x 64 4.1 / 3.8, x 512 6.7 / 5.0, x 1024
+//   10.5 / 6.5; 24 x 128 x 128 x 4096 (96) 31.6 / 14.8.  A product that split-K applies to stays with the kernel that the
+//   ranges run on, also where no scratch is lent for them (512 x 512 x 4096 27.6 / 13.3).
+//   Then, up to 128 tiles of 128 and below 32 slabs (from there on split-K may apply), whole 64-tiles.  Fast kernel / 64-tiles /
+//   wide 128-tiles: 700 x 700 (121 tiles of 64) x 256 8.3 / 4.8 / 7.0, x 1024 13.9 / 7.6 / 11.0; 1000 x 1000 (256) x 1024
+//   14.8 / 8.0 / 11.3; 1024 x 2048 (512) x 128 5.3 / 4.8 / 4.8, x 1024 14.0 / 9.8 / 10.3; 1500 x 1500 (576) x 512 10.0 / 10.0 /
+//   9.4, x 1024 15.4 / 15.1 / 11.9.
+constexpr DirectForm SHARED_TILES{128, 4, 4}, WHOLE_TILES{64, 1, 4};
+static DirectForm few_tiles_form(const Args& a)
+{
+    const int64_t t64 = ((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch, t128 = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
+    if (t64 <= 96) return k4_splitk_factor(a) == 1 ? SHARED_TILES : DirectForm{0, 0, 0};
+    return t128 <= 128 && a.K < 32 * (ROW_BYTES / 2) ? WHOLE_TILES : DirectForm{0, 0, 0};
+}
 bool k4_direct_takes_few_tiles(const Args& a)
 {
-    const int64_t t64 = ((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch;
-    return elem_size(a.in_dtype) == 2 && t64 <= 96 && k4_direct_applies(a) && k4_small_tiles(a) && k4_splitk_factor(a) == 1;
+    return elem_size(a.in_dtype) == 2 && few_tiles_form(a).tile != 0 && k4_direct_applies(a) && k4_small_tiles(a);
 }
-Geometry geometry_k4_few_tiles(const Args& a) { return geometry_of(a, FEW_TILES); }
+Geometry geometry_k4_few_tiles(const Args& a) { return geometry_of(a, few_tiles_form(a)); }
 
 template <typename CFG>
 static hipError_t launch_cfg(const Args& a)
@@ -137,6 +150,7 @@ template <typename IN>
 static hipError_t launch_form(const Args& a)
 {
     const DirectForm f = k4_direct_form(a);
+    if (f.wide) return launch_k4_wide(a, f.wide);
     if (f.parts == 2) return launch_layout<IN, 64, 2, 4>(a);
     if constexpr (IN::BYTES == 4) {
         return launch_layout<IN, 64, 1, 2>(a);
@@ -146,11 +160,18 @@ static hipError_t launch_form(const Args& a)
     }
 }
 
+template <typename IN>
+static hipError_t launch_few_tiles(const Args& a)
+{
+    if (few_tiles_form(a).parts == 1) return launch_cfg<DirectCfg<IN, WHOLE_TILES.tile, WHOLE_TILES.parts, WHOLE_TILES.stages, true, true>>(a);
+    return launch_cfg<DirectCfg<IN, SHARED_TILES.tile, SHARED_TILES.parts, SHARED_TILES.stages, true, true>>(a);
+}
+
 hipError_t launch_k4_few_tiles(const Args& a)
 {
     if (a.a_sk != 1 || a.b_sk != 1) return hipErrorInvalidValue;
-    if (a.in_dtype == GEMM_BF16) return launch_cfg<DirectCfg<BF16, FEW_TILES.tile, FEW_TILES.parts, FEW_TILES.stages, true, true>>(a);
-    if (a.in_dtype == GEMM_F16) return launch_cfg<DirectCfg<F16, FEW_TILES.tile, FEW_TILES.parts, FEW_TILES.stages, true, true>>(a);
+    if (a.in_dtype == GEMM_BF16) return launch_few_tiles<BF16>(a);
+    if (a.in_dtype == GEMM_F16) return launch_few_tiles<F16>(a);
     return hipErrorInvalidValue;
 }
 

@@ -161,11 +161,18 @@ static bool k4_small_tiles_deep(const Args& a)
     return nslab >= 32 && ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch <= 256;
 }
 
+// Two-byte types without switches: the 128-tiles of one round, and some products beyond (k4_wide_round), are multiplied by
+// the kernel whose loads have waves of their own (k4_wide.hpp).  Fast kernel / wide tiles: 714 x 774 x 448 10.2 / 8.0 us,
+// 1380 x 1968 x 2496 28.4 / 19.9, 2048^3 23.3 / 18.9, x 4096 39.8 / 32.0, 705 x 3004 x 768 13.6 / 10.2, 35 x 346 x 152 x 1024
+// 16.1 / 12.7; fewer tiles than CUs and a short K go to smaller ones (k4_direct_takes_few_tiles).
+int k4_fast_wide(const Args& a) { return a.K > 0 && k4_small_tiles(a) ? k4_wide_round(a, 1, true) : 0; }
+
 // The expert instantiation, or one of its validated simplifications when the caller asks for it.
 template <typename IN>
 static hipError_t launch_fast_any(const Args& a)
 {
     if (k4_uses_ring(a)) return launch_k4_ring(a);
+    if (const int bm = k4_fast_wide(a)) return launch_k4_wide(a, bm);
     const bool noswz = a.flags & GEMM_FLAG_DEOPT_NO_SWIZZLE, noovl = a.flags & GEMM_FLAG_DEOPT_NO_OVERLAP;
     if (noswz && noovl) return launch_fast<FastCfg<IN, 256, 8, false, false>>(a);
     if (noswz) return launch_fast<FastCfg<IN, 256, 8, false, true>>(a);
@@ -450,6 +457,8 @@ Geometry geometry_k4(int path, const Args& a)
         if (k4_fast_is_persistent(kind, a)) g = K4_RING_WORKGROUPS;      // persistent workgroups, several tiles each
         // stages: slabs in flight beyond the one in use
         const Args p = fast_kernel_args(kind, a);
+        if (!k4_uses_ring(p))
+            if (const int bm = k4_fast_wide(p)) return geometry_k4_wide(p, bm);
         if (k4_small_tiles(p) && !k4_uses_ring(p) && !(p.flags & (GEMM_FLAG_DEOPT_NO_SWIZZLE | GEMM_FLAG_DEOPT_NO_OVERLAP)) && k4_small_tiles_deep(p))
             return Geometry{bt, bt, ROW_BYTES / es, 256, FastK4SmallDeep<BF16>::DEPTH, FastK4SmallDeep<BF16>::LDS_BYTES, g};
         return Geometry{bt, bt, ROW_BYTES / es, 256, 2, small ? FastK4Small<BF16>::LDS_BYTES : FastK4<BF16>::LDS_BYTES, g};

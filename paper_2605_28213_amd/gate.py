@@ -106,6 +106,8 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
         return [r"k4_stream<gl::StreamCfg<%s, %d, " % (dt, threads // 64)]
     if path.startswith("mfma16-thin"):
         return [r"k4_thin_brow<gl::ThinCfg<%s, %d, %d, " % (dt, 1 if bm <= 16 else 2 if bm <= 32 else 4, bn)]
+    if path.endswith("(direct-to-lds)") and threads == 512:
+        return [r"k4_mfma_wide<gl::WideCfg<%s, %d, " % (dt, bm)]
     if path.endswith("(direct-to-lds)"):
         return [r"k4_mfma_direct<gl::DirectCfg<%s, %d, " % (dt, bm)]
     if "direct-to-lds" in path:
@@ -115,6 +117,10 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
             pats.append(r"k4_mfma_ring<gl::RingCfg<%s, \d+, true>" % dt)
         elif "(persistent)" in path:
             pats.append(r"k4_mfma_ring<gl::RingCfg<%s, \d+, false>" % dt)
+        elif threads == 512:
+            pats.append(r"k4_mfma_wide<gl::WideCfg<%s, %d, true, true>" % (dt, bm))         # wide tiles with loading waves
+        elif "(few-tiles)" in path and bm == 64:
+            pats.append(r"k4_mfma_direct<gl::DirectCfg<%s, 64, 1, 4, true, true>" % dt)
         elif "(few-tiles)" in path:
             pats.append(r"k4_mfma_direct<gl::DirectCfg<%s, 128, 4, 4, true, true>" % dt)     # each shared by sixteen workgroups
         elif bm == 128 and stages == 4:

@@ -1,0 +1,74 @@
+"""K4's wide tiles with loading waves: every layout, both tile heights, K of one slab up to more than the rings hold.
+
+Operands are small integers, so the products are exact in fp32 in any order of the sum (|sum| <= 9 K < 2^24) and compared
+for equality; what surrounds the operands is NaN and what surrounds C must stay as it was."""
+import pytest
+import torch
+
+from paper_2605_28213_amd import gemm
+
+pytestmark = pytest.mark.gpu
+K4, ROW, COL = gemm.GEMM_K4_MFMA, gemm.GEMM_ROW_MAJOR, gemm.GEMM_COL_MAJOR
+TYPES = {gemm.GEMM_BF16: torch.bfloat16, gemm.GEMM_F16: torch.float16}
+
+
+def framed(rows, cols, pad, batch, dtype, gen):
+    n = batch * rows * (cols + pad)
+    flat = torch.full((n + 8,), float("nan"), device="cuda", dtype=dtype)
+    start = 8 if (flat.data_ptr() + 2 * (n - pad)) % 4096 == 0 else 0       # (an odd last row that ends a page goes to another kernel)
+    x = flat[start : start + n].view(batch, rows, cols + pad)
+    x[:, :, :cols] = torch.randint(-3, 4, (batch, rows, cols), generator=gen, device="cuda").to(dtype)
+    return x
+
+
+def check(dt, M, N, K, la, lb, batch, pads, expect, biased, out32):
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    td, pa, pb, pc = TYPES[dt], *pads
+    A = framed(*((M, K) if la == ROW else (K, M)), pa, batch, td, gen)
+    B = framed(*((K, N) if lb == ROW else (N, K)), pb, batch, td, gen)
+    ot = torch.float32 if out32 else td
+    C = torch.full((batch, M, N + pc), 7.0, device="cuda", dtype=ot)
+    bias = torch.randint(-5, 6, (N,), generator=gen, device="cuda").float() if biased else None
+    d = gemm.make_desc(M, N, K, dt, gemm.GEMM_F32 if out32 else dt, la, lb, lda=A.shape[2], ldb=B.shape[2], ldc=N + pc, batch=batch,
+                       stride_a=A[0].numel(), stride_b=B[0].numel(), stride_c=C[0].numel(), bias=bias)
+    q = gemm.gemm_query(K4, d, A, B, C)
+    assert (q.threads, q.bm, q.bn) == (512, expect, 128), (q, M, N, K)
+    assert gemm.gemm_run_ex(K4, d, A, B, C) == gemm.GEMM_OK
+    torch.cuda.synchronize()
+    for i in range(batch):
+        a, b = A[i, :, : (K if la == ROW else M)].float(), B[i, :, : (N if lb == ROW else K)].float()
+        ref = (a if la == ROW else a.t()) @ (b if lb == ROW else b.t())
+        if biased:
+            ref = ref + bias
+        assert torch.equal(C[i, :, :N], ref.to(ot)), (M, N, K, la, lb, i)
+    assert torch.equal(C[:, :, N:], torch.full_like(C[:, :, N:], 7.0))
+
+
+@pytest.mark.parametrize("dt", list(TYPES))
+@pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5, 6, 9, 11])
+def test_aligned_operands_in_every_length_of_the_rings(dt, slabs):
+    """More than 128 tiles of 128; rows and columns end inside a tile (1 row and 1 column past it, or all but one)."""
+    M, N = (1409, 1537) if slabs % 2 else (1535, 1407)
+    check(dt, M, N, 64 * slabs, ROW, COL, 1, (0, 8, 0), 128, slabs == 3, slabs % 2 == 0)
+
+
+@pytest.mark.parametrize("dt", list(TYPES))
+@pytest.mark.parametrize("la,lb", [(ROW, ROW), (COL, ROW), (COL, COL), (ROW, COL)])
+@pytest.mark.parametrize("K", [321, 384, 447, 640])
+def test_any_layout_alignment_and_k_on_128_tiles(dt, la, lb, K):
+    """K of 1, 63 and 64 elements in its last slab, rows aligned to an element; a batch whose C rows are odd."""
+    check(dt, 1409, 1535, K, la, lb, 1, (1, 3, 1), 128, K == 447, False)
+    check(dt, 127, 129, K, la, lb, 70, (8, 0, 0), 128, False, True)
+
+
+@pytest.mark.parametrize("la,lb", [(ROW, ROW), (COL, ROW), (COL, COL), (ROW, COL)])
+def test_any_layout_on_256_tiles(la, lb):
+    """176 tiles of 256 x 128 (the fewest), rows and columns ending inside them; 24 slabs, one element in the last, and more."""
+    check(gemm.GEMM_F16, 2561, 1921, 24 * 64 - 63, la, lb, 1, (1, 2, 3), 256, True, False)
+    check(gemm.GEMM_BF16, 2815, 2047, 26 * 64 + 8, la, lb, 1, (0, 0, 1), 256, False, True)
+
+
+@pytest.mark.parametrize("dt", list(TYPES))
+def test_aligned_operands_on_256_tiles(dt):
+    check(dt, 2561, 1928, 16 * 64, ROW, COL, 1, (0, 0, 0), 256, False, False)
+    check(dt, 200, 100, 18 * 64, ROW, COL, 177, (64, 0, 4), 256, True, True)
