@@ -127,6 +127,7 @@ size_t k4_packed_workspace_bytes(const Args& a, int keep_mask);   // keep_mask: 
 // is cut into (1: not applicable), and the fp32 scratch the partial products need.
 int k4_splitk_factor(const Args& a);
 size_t k4_splitk_workspace_bytes(const Args& a, int splits);
+int k4_splitk_wide(const Args& a);        // the ranges that the wide tiles with loading waves run (neighbours may be joined), 0: the fast kernel
 bool k4_splitk_rotates(const Args& a);    // its ranges run with a rotated K walk
 // True when the fast kernel's launcher hands a thin remainder of rows (M % 256 in 1..64, where that saves a
 // round of the chip) to the streaming kernel.
@@ -181,6 +182,7 @@ hipError_t launch_k4_direct(const Args& a);
 int k4_wide_round(const Args& a, int64_t t128_from, bool aligned);
 int k4_fast_wide(const Args& a);          // on a product that meets the fast kernel's conditions, instead of its 128-tiles
 hipError_t launch_k4_wide(const Args& a, int bm);
+hipError_t launch_k4_wide_ranges(const Args& a, bool stream_b);     // split-K: ranges as batch items, fp32 partial sums to a.C
 
 hipError_t launch_k0(const Args& a);
 hipError_t launch_valu_tiled(int variant, int path, const Args& a);

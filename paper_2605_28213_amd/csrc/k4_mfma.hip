@@ -278,10 +278,32 @@ bool k4_splitk_rotates(const Args& a)
     return p.flags == GEMM_FLAG_TILE_128 && a.M <= 128 && a.N * a.K * elem_size(a.in_dtype) >= (int64_t)192 << 20 && !k4_uses_ring(p) && !k4_small_tiles_deep(p);
 }
 
+// The ranges on wide tiles with loading waves, whose K walk always starts at a slab of the tile's own, where they fit one
+// round of the chip: 128-tiles of k4_mfma_fast / wide, operands rotated over three sets, bf16 unless noted: 100 x 4096 x 4096
+// 19.8 / 16.4 us, 128 x 4096 x 16384 (fp16) 61.6 / 42.1, 128 x 16384 x 2048 27.6 / 23.0, 128 x 1024 x 16384 23.3 / 20.6,
+// 256 x 2048 x 8192 23.0 / 20.5, 300 x 300 x 8192 20.6 / 17.3, e4m3 128 x 4096 x 8192 21.7 / 20.1; the same operands again
+// 1.06 to 1.25.  More ranges than one round stay with k4_mfma_fast (110 x 8192^2, 512 of them, 47.6 / 47.0).
+// A B that streams from HBM (k4_splitk_rotates) is read past the caches' replacement, and neighbouring ranges are joined until
+// they fit one round, so that each of the 256 CUs keeps 64 KB of B in flight and half of the partial sums are written:
+// 128 x 16384 x 16384 in 4 ranges 115, in 2 joined pairs 119, with nt loads 105 (before: 121); e4m3 78.6 / 63.4;
+// 128 x 8192 x 16384 76.3 / 57.1, 128 x 28672 x 4096 72.3 / 59.1.  (B alone, read by 256 workgroups in this pattern: 85 us in
+// the caches' order, 78 us with nt.  On a B that stays in the Infinity Cache nt costs: 100 x 4096 x 4096 16.4 / 20.6.)
+int k4_splitk_wide(const Args& a)
+{
+    const int splits = k4_splitk_factor(a);
+    const int64_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+    if (splits < 2 || a.flags != 0 || !k4_small_tiles(a)) return 0;
+    if (!k4_splitk_rotates(a)) return tiles * splits <= 256 ? splits : 0;
+    int ranges = 1;
+    for (int r = 2; r <= splits; ++r)
+        if (splits % r == 0 && tiles * r <= 256) ranges = r;
+    return ranges;
+}
+
 template <typename IN>
 static hipError_t launch_splitk(const Args& a)
 {
-    const int splits = k4_splitk_factor(a);
+    const int wide = k4_splitk_wide(a), splits = wide ? wide : k4_splitk_factor(a);
     Args p = a;
     p.batch = splits;
     p.K = a.K / splits;
@@ -291,7 +313,7 @@ static hipError_t launch_splitk(const Args& a)
     p.out_dtype = GEMM_F32;
     p.scale_a = p.scale_b = nullptr; p.bias = nullptr;
     p.flags = (k4_small_tiles(a) ? GEMM_FLAG_TILE_128 : GEMM_FLAG_TILE_256) | (a.flags & K4_NEUTRAL_FLAGS);   // the tile the product itself would get
-    hipError_t e = k4_splitk_rotates(a) ? launch_fast<FastCfgRot<IN>>(p) : launch_fast_any<IN>(p);
+    hipError_t e = wide ? launch_k4_wide_ranges(p, k4_splitk_rotates(a)) : k4_splitk_rotates(a) ? launch_fast<FastCfgRot<IN>>(p) : launch_fast_any<IN>(p);
     if (e != hipSuccess) return e;
     const int64_t threads = a.M * ((a.N + 3) / 4);
     hipLaunchKernelGGL(k4_splitk_reduce<IN>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, a.stream, a, (const float*)a.workspace, splits);
@@ -457,6 +479,11 @@ Geometry geometry_k4(int path, const Args& a)
         if (k4_fast_is_persistent(kind, a)) g = K4_RING_WORKGROUPS;      // persistent workgroups, several tiles each
         // stages: slabs in flight beyond the one in use
         const Args p = fast_kernel_args(kind, a);
+        if (const int ranges = kind == MFMA_SPLITK ? k4_splitk_wide(a) : 0) {
+            Args r = a;
+            r.batch = ranges;
+            return geometry_k4_wide(r, 128);
+        }
         if (!k4_uses_ring(p))
             if (const int bm = k4_fast_wide(p)) return geometry_k4_wide(p, bm);
         if (k4_small_tiles(p) && !k4_uses_ring(p) && !(p.flags & (GEMM_FLAG_DEOPT_NO_SWIZZLE | GEMM_FLAG_DEOPT_NO_OVERLAP)) && k4_small_tiles_deep(p))

@@ -31,6 +31,23 @@ hipError_t launch_k4_wide(const Args& a, int bm)
     return hipErrorInvalidValue;
 }
 
+// K ranges as batch items, partial sums in fp32
+template <typename IN>
+static hipError_t launch_ranges(const Args& a, bool stream_b)
+{
+    return stream_b ? launch_cfg<WideCfg<IN, 128, true, true, 19, true>>(a) : launch_cfg<WideCfg<IN, 128, true, true, 19, false>>(a);
+}
+
+hipError_t launch_k4_wide_ranges(const Args& a, bool stream_b)
+{
+    switch (a.in_dtype) {
+    case GEMM_BF16: return launch_ranges<BF16>(a, stream_b);
+    case GEMM_F16: return launch_ranges<F16>(a, stream_b);
+    case GEMM_FP8_E4M3: return launch_ranges<E4M3>(a, stream_b);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 // Tiles of one round of the chip, in the order tried; both sides in us, row-major operands unless noted.
 //   128 x 128, at most one per CU: the caller's line (k4_direct_form, k4_fast_wide) says from how many.
 //   256 x 128, 176 to 256 of them (fewer leave CUs idle that two 128-tiles each would use), with a K long enough for the
@@ -54,7 +71,7 @@ Geometry geometry_k4_wide(const Args& a, int bm)
     const int64_t g = (a.M + bm - 1) / bm * ((a.N + 127) / 128) * a.batch;
     const bool kc = a.a_sk == 1 && a.b_sk == 1;
     const int lds = bm == 256 ? WideCfg<BF16, 256, true, true>::LDS_BYTES : kc ? WideCfg<BF16, 128, true, true>::LDS_BYTES : WideCfg<BF16, 128, false, false>::LDS_BYTES;
-    return Geometry{bm, 128, ROW_BYTES / 2, 512, bm == 256 ? 2 : 4, lds, g};
+    return Geometry{bm, 128, ROW_BYTES / elem_size(a.in_dtype), 512, bm == 256 ? 2 : 4, lds, g};
 }
 
 }  // namespace gl

@@ -23,10 +23,14 @@ namespace gl {
 
 // 256 x 128: three slabs of both operands (144 KB), every loading wave loads both.  128 x 128: five slabs (160 KB); with K
 // contiguous in both operands two waves load four slabs of A and two load five of B (nine regions, 144 KB).
-template <typename IN, int BM_, bool A_KC_, bool B_KC_>
+// ROT, NT: K ranges of a thin product (see k4_splitk_wide): the K walk starts ROT slabs later from one tile to the next, and B,
+// which nobody reads twice, is loaded past the caches' replacement (nt) so that A stays in the L2s.  e4m3 comes in this form
+// only: its chunk of 16 bytes is two v_mfma_f32_16x16x32_fp8_fp8.
+template <typename IN, int BM_, bool A_KC_, bool B_KC_, int ROT_ = 0, bool NT_ = false>
 struct WideCfg {
     using In = IN;
-    static constexpr bool A_KC = A_KC_, B_KC = B_KC_, ROLES = BM_ == 128 && A_KC_ && B_KC_;
+    static constexpr int ROT = ROT_;
+    static constexpr bool A_KC = A_KC_, B_KC = B_KC_, NT = NT_, ROLES = BM_ == 128 && A_KC_ && B_KC_;
     static constexpr int BM = BM_, BN = 128, WM = 2, WN = 2, T = 512;
     static constexpr int TMI = BM / WM / 16, TNI = BN / WN / 16;
     static constexpr int REGION_A = BM * ROW_BYTES, REGION_B = BN * ROW_BYTES;
@@ -34,8 +38,16 @@ struct WideCfg {
     static constexpr int BASE_B = SA * REGION_A, LDS_BYTES = BASE_B + SB * REGION_B;
     static constexpr int LW = ROLES ? 2 : 4;                                           // waves that load an operand
     static constexpr int LDA = BM / 8 / LW, LDB = BN / 8 / LW;                         // direct loads per such wave and slab
-    static_assert(IN::BYTES == 2 && (BM_ == 128 || BM_ == 256), "two-byte types");
+    static_assert((IN::BYTES == 2 || (IN::BYTES == 1 && ROT_ != 0)) && (BM_ == 128 || BM_ == 256), "two-byte types; e4m3 for K ranges");
+    static_assert(ROT_ == 0 || ROLES, "K ranges have K contiguous in both operands");
 };
+
+template <typename IN>
+__device__ __forceinline__ void wide_step(const u32x4_t& a, const u32x4_t& b, f32x4_t& c)
+{
+    if constexpr (IN::BYTES == 2) mfma_step16<IN>(a, b, c);
+    else mfma16<IN>(a, b, c);
+}
 
 template <typename CFG>
 __global__ __launch_bounds__(CFG::T) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -43,9 +55,9 @@ void k4_mfma_wide(Args a, int tiles_m, int tiles_n, int flags)
 {
     using IN = typename CFG::In;
     constexpr int BM = CFG::BM, BN = CFG::BN, TMI = CFG::TMI, TNI = CFG::TNI, SA = CFG::SA, SB = CFG::SB, REGION_A = CFG::REGION_A, REGION_B = CFG::REGION_B, BASE_B = CFG::BASE_B;
-    constexpr int ES = 2, KE = ROW_BYTES / ES, V = 8, LDA = CFG::LDA, LDB = CFG::LDB, LW = CFG::LW;
+    constexpr int ES = IN::BYTES, KE = ROW_BYTES / ES, V = 16 / ES, LDA = CFG::LDA, LDB = CFG::LDB, LW = CFG::LW;
     constexpr int LINE_A = BM * ES, LINE_B = BN * ES;     // rows-contiguous form: bytes of one k
-    constexpr int SLACK = 2;                              // the dword of an odd-length last row (see tail_element_in_last_page)
+    constexpr int SLACK = ES == 2 ? 2 : 0;                            // the dword of an odd-length last row (see tail_element_in_last_page)
     __shared__ __attribute__((aligned(1024))) char lds[CFG::LDS_BYTES];
 
     const int t = threadIdx.x, lane = t & 63;
@@ -85,17 +97,23 @@ void k4_mfma_wide(Args a, int tiles_m, int tiles_n, int flags)
     const int slab_a = CFG::A_KC ? ROW_BYTES : (int)(KE * a.a_sk * ES), slab_b = CFG::B_KC ? ROW_BYTES : (int)(KE * a.b_sk * ES);
     using lptr = __attribute__((address_space(3))) char*;
     const int lds0 = (int)(uint32_t)(uintptr_t)(lptr)lds;
+    const int rot = CFG::ROT != 0 && nslab > 0 ? (int)((unsigned)(tm * tiles_n + tn) * CFG::ROT % (unsigned)nslab) : 0;
     // this wave's loads of slab s of an operand into the region at byte `reg`
     auto issue = [&](auto isa_, int s, int reg) __attribute__((always_inline)) {
         constexpr bool isa = decltype(isa_)::value;
         const int voff = isa ? voff_a : voff_b;
         const rsrc_t rsrc = isa ? rsrc_a : rsrc_b;
+        int k = s;
+        if constexpr (CFG::ROT != 0) k = s + rot >= nslab ? s + rot - nslab : s + rot;
 #pragma unroll
         for (int n = 0; n < (isa ? LDA : LDB); ++n) {
             const int i = isa ? block_of(LPB_A, CFG::A_KC, n) : block_of(LPB_B, CFG::B_KC, n);
-            const int dst = lds0 + reg + i * 1024, soff = isa ? s * slab_a + i * blk_a : s * slab_b + i * blk_b;
+            const int dst = lds0 + reg + i * 1024, soff = isa ? k * slab_a + i * blk_a : k * slab_b + i * blk_b;
             // (the wait states k4_ring.hpp explains: one after M0, five after a scalar register written by a vector instruction)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+            if constexpr (!isa && CFG::NT)
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+            else
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
         }
     };
 
@@ -144,7 +162,7 @@ void k4_mfma_wide(Args a, int tiles_m, int tiles_n, int flags)
 #pragma unroll
             for (int jj = 0; jj < TNI; ++jj) {
                 const int j = (i & 1) ? TNI - 1 - jj : jj;
-                if (i * TNI + jj >= lo && i * TNI + jj < hi) mfma_step16<IN>(fb[slot][j], fa[slot][i], acc[i][j]);
+                if (i * TNI + jj >= lo && i * TNI + jj < hi) wide_step<IN>(fb[slot][j], fa[slot][i], acc[i][j]);
             }
     };
 
@@ -244,8 +262,8 @@ void k4_mfma_wide(Args a, int tiles_m, int tiles_n, int flags)
         if (interior) store_tiles_staged<OUT, true, TMI, TNI>(a, b, acc, row0, col0, lane, park, vec_ok);
         else store_tiles_staged<OUT, false, TMI, TNI>(a, b, acc, row0, col0, lane, park, vec_ok);
     };
-    if (a.out_dtype == GEMM_F32) store(std::integral_constant<int, GEMM_F32>{});
-    else store(std::integral_constant<int, IN::ID>{});
+    if (CFG::ROT != 0 || a.out_dtype == GEMM_F32) store(std::integral_constant<int, GEMM_F32>{});      // (K ranges: partial sums)
+    else if constexpr (CFG::ROT == 0) store(std::integral_constant<int, IN::ID>{});
 }
 
 }  // namespace gl

@@ -107,7 +107,7 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
     if path.startswith("mfma16-thin"):
         return [r"k4_thin_brow<gl::ThinCfg<%s, %d, %d, " % (dt, 1 if bm <= 16 else 2 if bm <= 32 else 4, bn)]
     if path.endswith("(direct-to-lds)") and threads == 512:
-        return [r"k4_mfma_wide<gl::WideCfg<%s, %d, " % (dt, bm)]
+        return [r"k4_mfma_wide<gl::WideCfg<%s, %d, (true|false), (true|false), 0, " % (dt, bm)]
     if path.endswith("(direct-to-lds)"):
         return [r"k4_mfma_direct<gl::DirectCfg<%s, %d, " % (dt, bm)]
     if "direct-to-lds" in path:
@@ -118,7 +118,9 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
         elif "(persistent)" in path:
             pats.append(r"k4_mfma_ring<gl::RingCfg<%s, \d+, false>" % dt)
         elif threads == 512:
-            pats.append(r"k4_mfma_wide<gl::WideCfg<%s, %d, true, true>" % (dt, bm))         # wide tiles with loading waves
+            # wide tiles with loading waves: a whole product, or K ranges with a rotated walk
+            walk = "19, true" if "(rotated)" in path else "19, false" if "splitK" in path else "0, false"
+            pats.append(r"k4_mfma_wide<gl::WideCfg<%s, %d, true, true, %s>" % (dt, bm, walk))
         elif "(few-tiles)" in path and bm == 64:
             pats.append(r"k4_mfma_direct<gl::DirectCfg<%s, 64, 1, 4, true, true>" % dt)
         elif "(few-tiles)" in path:

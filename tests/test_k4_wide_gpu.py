@@ -72,3 +72,26 @@ def test_any_layout_on_256_tiles(la, lb):
 def test_aligned_operands_on_256_tiles(dt):
     check(dt, 2561, 1928, 16 * 64, ROW, COL, 1, (0, 0, 0), 256, False, False)
     check(dt, 200, 100, 18 * 64, ROW, COL, 177, (64, 0, 4), 256, True, True)
+
+
+@pytest.mark.parametrize("dt,td", [(gemm.GEMM_BF16, torch.bfloat16), (gemm.GEMM_F16, torch.float16), (gemm.GEMM_FP8_E4M3, torch.float8_e4m3fn)])
+@pytest.mark.parametrize("M,N,slabs", [(97, 98, 32), (128, 129, 51), (257, 300, 96), (128, 10000, 48)])
+def test_k_ranges_with_a_rotated_walk(dt, td, M, N, slabs):
+    """Split-K on wide tiles: ranges of 16 slabs and more, one tile and many, rows and columns ending inside a tile."""
+    K = slabs * (128 if dt == gemm.GEMM_FP8_E4M3 else 64)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, B = (torch.randint(-3, 4, (r, K), generator=gen, device="cuda").float() for r in (M, N))
+    a8, b8 = A.to(td), B.to(td)
+    C = torch.full((M, N + 3), 7.0, device="cuda")
+    bias = torch.randint(-5, 6, (N,), generator=gen, device="cuda").float()
+    d = gemm.make_desc(M, N, K, dt, gemm.GEMM_F32, ROW, COL, ldc=N + 3, bias=bias)
+    need = gemm.gemm_query(K4, d, a8, b8, C).workspace_bytes
+    assert need > 0
+    ws = torch.full((need + 256,), 255, dtype=torch.uint8, device="cuda")
+    d.workspace, d.workspace_bytes = ws.data_ptr(), need
+    q = gemm.gemm_query(K4, d, a8, b8, C)
+    assert q.threads == 512 and "+splitK(" in q.path and q.grid <= 256, q
+    for _ in range(2):
+        assert gemm.gemm_run_ex(K4, d, a8, b8, C) == gemm.GEMM_OK
+        torch.cuda.synchronize()
+        assert torch.equal(C[:, :N], A @ B.t() + bias) and bool((C[:, N:] == 7.0).all()) and bool((ws[need:] == 255).all())
