@@ -25,30 +25,57 @@ __device__ __forceinline__ uint32_t key_of(float v)
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// Inclusive prefix sum of v over the workgroup's T threads; *total receives the sum over all of them.
-// `wsum` is T/64 ints of LDS.  Two barriers; safe to call back to back.
+// Inclusive prefix sum over the wave, by data-parallel moves: rows of 16 first, then the last lane of a row to the next row
+// and of the lower half to the upper one.
+__device__ __forceinline__ int row_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);      // row_shr:1, 2, 4, 8; lanes that have no source add 0
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    return v;
+}
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v = row_scan(v);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);      // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// The workgroup's part of a prefix sum whose waves have done theirs (`s`, inclusive): one barrier.  `wsum` is T/64 ints of
+// LDS that nobody reads any more.
+template <int T>
+__device__ __forceinline__ int join_scan(int s, int* wsum, int* total)
+{
+    static_assert(T / 64 <= 16, "the waves' sums are one row of lanes");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (lane == 63) wsum[wave] = s;
+    __syncthreads();
+    const int sums = row_scan(lane < T / 64 ? wsum[lane] : 0);
+    *total = __builtin_amdgcn_readlane(sums, T / 64 - 1);
+    return s + (wave > 0 ? __builtin_amdgcn_readlane(sums, wave - 1) : 0);
+}
+
+// Inclusive prefix sum of v over the workgroup's T threads; *total receives the sum over all of them.  Two barriers; safe to
+// call back to back.  (With shuffles, and the waves' sums added up one by one, a scan took 1700 cycles of a 12 000-cycle
+// selection; most instructions of these kernels run once, from a cold instruction cache, so short code counts.)
 template <int T>
 __device__ __forceinline__ int block_scan(int v, int* wsum, int* total)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int s = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(s, o, 64);
-        if (lane >= o) s += u;
-    }
+    const int s = wave_scan(v);
     __syncthreads();                      // the previous call's readers are done with wsum
-    if (lane == 63) wsum[wave] = s;
-    __syncthreads();
-    int base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < T / 64; ++w) {
-        const int ws = wsum[w];
-        if (w < wave) base += ws;
-        tot += ws;
-    }
-    *total = tot;
-    return s + base;
+    return join_scan<T>(s, wsum, total);
+}
+
+// Where this lane's `n` entries go in a list whose length is *length, in no particular order; all lanes of the wave take part.
+// (One addition per wave: hundreds of lanes that add to one word of LDS wait for each other.)
+__device__ __forceinline__ int take_places(int n, int* length)
+{
+    const int s = wave_scan(n);
+    int first = 0;
+    if ((threadIdx.x & 63) == 63 && s > 0) first = atomicAdd(length, s);
+    return __builtin_amdgcn_readlane(first, 63) + s - n;
 }
 
 // Ordered compaction shared by all states.  Each thread owns a contiguous run of elements [lo, hi) and
@@ -137,10 +164,11 @@ __global__ __launch_bounds__(SEL_T) void topk_selection(TopkArgs a)
 }
 
 // The digit d of a histogram of nb bins with  #(keys with a larger digit) < remaining <= #(keys with digit >= d),
-// and how many of the keys with that digit are still wanted.  The caller has a barrier between the counting and
-// this call; both results are readable by every thread on return.
+// how many of the keys with that digit are still wanted, and how many there are.  The caller has a barrier between the
+// counting and this call; the results are readable by every thread on return.
+struct Digit { int digit, left, count; };
 template <int T>
-__device__ __forceinline__ void pick_digit(const int* hist, int nb, int remaining, int* wsum, int* digit, int* left)
+__device__ __forceinline__ void pick_digit(const int* hist, int nb, int remaining, int* wsum, Digit* out)
 {
     const int tid = threadIdx.x;
     const int ch = nb >= T ? nb / T : 1;                   // bins per thread, a contiguous chunk
@@ -149,20 +177,56 @@ __device__ __forceinline__ void pick_digit(const int* hist, int nb, int remainin
     if (active)
         for (int c = 0; c < ch; ++c) s += hist[tid * ch + c];
     int total;
-    const int incl = block_scan<T>(s, wsum, &total);
+    const int incl = join_scan<T>(wave_scan(s), wsum, &total);
     const int above = total - incl;                         // keys in the chunks above this thread's
     if (active && above < remaining && remaining <= above + s) {
         int acc = above;
         for (int d = tid * ch + ch - 1; d >= tid * ch; --d) {
             if (acc + hist[d] >= remaining) {
-                *digit = d;
-                *left = remaining - acc;
+                *out = Digit{d, remaining - acc, hist[d]};
                 break;
             }
             acc += hist[d];
         }
     }
     __syncthreads();
+}
+
+// The keys that share the k-th largest one's first digit, listed in LDS: once they are few, one wave finishes, six bits a
+// step, in a histogram of one bin per lane, while the others wait at one barrier; it stops as soon as all that are left are
+// taken.  Taken are the keys above `thr` and the first `equal` of those that equal it.
+// (T2, which used to make two more histogram passes of five barriers each: 64 rows x 4096, k = 512, 7.2 -> 5.0 us, 1204 cycles
+// of loads, 1400 of counting, 1100 for the digit, 1400 for the list, 2300 here and 900 of compaction; 64 x 1024, k = 64, 8.7 ->
+// 4.5, of which 2 were additions of elements that do not exist to one bin; 128 x 16384, k = 1000, 20.7 -> 9.8; 4 x 9000, k = 100,
+// 22.7 -> 7.7; 4000 x 1000, k = 10, 93 -> 30.)
+constexpr int FEW_KEYS = 512;
+struct Cut { uint32_t thr; int equal; };
+
+// called by a whole wave; `count` <= FEW_KEYS keys that agree in the bits from `shift` up, which are `prefix`'s
+__device__ __forceinline__ Cut cut_of_listed(const uint32_t* keys, volatile int* h, int count, int remaining, uint32_t prefix, int shift)
+{
+    constexpr int ITEMS = FEW_KEYS / 64;
+    const int lane = threadIdx.x & 63;
+    uint32_t key[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) key[j] = j * 64 + lane < count ? keys[j * 64 + lane] : ~prefix;
+    int size = count;
+    while (shift > 0 && (size != remaining || prefix == 0)) {
+        const int low = shift < 6 ? 0 : shift - 6;
+        h[lane] = 0;                                        // (one wave: LDS serves its requests in order)
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j)
+            if (key[j] >> shift == prefix >> shift) atomicAdd((int*)&h[63 - ((key[j] >> low) & 63)], 1);      // (bits from `shift` up are the same in all)
+        __builtin_amdgcn_wave_barrier();
+        const int mine = h[lane], incl = wave_scan(mine);   // lane l: the digit 63 - l
+        const int at = __ffsll((unsigned long long)__ballot(incl >= remaining)) - 1;
+        size = __builtin_amdgcn_readlane(mine, at);
+        remaining -= __builtin_amdgcn_readlane(incl, at) - size;
+        prefix = ((prefix >> low | 63u) - (uint32_t)at) << low;
+        shift = low;
+    }
+    return size == remaining && prefix != 0 ? Cut{prefix - 1, 0} : Cut{prefix, remaining};
 }
 
 // ---- T1 / T2: radix select ----------------------------------------------------------------------
@@ -177,7 +241,10 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
     constexpr int BITS[4] = {B0, B1, B2, B3};
     __shared__ int hist[1 << MAXB];
     __shared__ int wsum[T / 64];
-    __shared__ int found_digit, found_remaining;
+    __shared__ Digit found;
+    __shared__ uint32_t few[RESIDENT ? FEW_KEYS : 1];
+    __shared__ int bins[64], listed;
+    __shared__ Cut cut;
     const float* row = a.x + (int64_t)blockIdx.x * a.ld;
     const int tid = threadIdx.x;
     const int64_t n = a.n;
@@ -186,8 +253,11 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
     // Elements past n are held as the pattern whose key is 0, below every non-NaN key.
     constexpr uint32_t PAD_BITS = 0xFFFFFFFFu;
     uint32_t held[RESIDENT ? ITEMS : 1];
+    int mine = 0;                                           // the thread's elements that exist
     if constexpr (RESIDENT) {
         static_assert(ITEMS % 4 == 0, "16-byte loads");
+        const int64_t left = n - (int64_t)tid * ITEMS;
+        mine = left < 0 ? 0 : left < ITEMS ? (int)left : ITEMS;
 #pragma unroll
         for (int j = 0; j < ITEMS; j += 4) {
             const int64_t i = (int64_t)tid * ITEMS + j;
@@ -200,6 +270,7 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
             }
         }
     }
+    if (tid == 0) { found = Digit{0, 0, 0}; listed = 0; }
 
     uint32_t prefix = 0, mask = 0;
     int remaining = (int)a.k, shift = 32;
@@ -210,10 +281,11 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
         for (int i = tid; i < nb; i += T) hist[i] = 0;
         __syncthreads();
         if constexpr (RESIDENT) {
+            // (what does not exist is not counted: thousands of additions to one bin of LDS would wait for each other)
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j) {
                 const uint32_t key = key_of(__uint_as_float(held[j]));
-                if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & (nb - 1)], 1);
+                if (j < mine && (key & mask) == prefix) atomicAdd(&hist[(key >> shift) & (nb - 1)], 1);
             }
         } else {
             for (int64_t i = tid; i < n; i += T) {
@@ -222,25 +294,62 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
             }
         }
         __syncthreads();
-        pick_digit<T>(hist, nb, remaining, wsum, &found_digit, &found_remaining);
-        prefix |= (uint32_t)found_digit << shift;
+        pick_digit<T>(hist, nb, remaining, wsum, &found);
+        prefix |= (uint32_t)found.digit << shift;
         mask |= (uint32_t)(nb - 1) << shift;
-        remaining = found_remaining;
+        remaining = found.left;
+        if constexpr (RESIDENT) {
+            const int count = found.count;
+            if (p + 1 < NPASS && count <= FEW_KEYS) {
+                int in_digit = 0;
+#pragma unroll
+                for (int j = 0; j < ITEMS; ++j) in_digit += j < mine && (key_of(__uint_as_float(held[j])) & mask) == prefix;
+                int at = take_places(in_digit, &listed);
+#pragma unroll
+                for (int j = 0; j < ITEMS; ++j) {
+                    const uint32_t key = key_of(__uint_as_float(held[j]));
+                    if (j < mine && (key & mask) == prefix) few[at++] = key;
+                }
+                __syncthreads();
+                if (tid < 64) {
+                    const Cut c = cut_of_listed(few, bins, count, remaining, prefix, shift);
+                    if (tid == 0) cut = c;
+                }
+                __syncthreads();
+                prefix = cut.thr;
+                remaining = cut.equal;
+                break;
+            }
+        }
     }
-    // prefix is now the k-th largest key; `remaining` of the elements equal to it are taken
+    // taken: the elements whose keys lie above prefix, and the first `remaining` of those equal to it
     const uint32_t thr = prefix;
     if constexpr (RESIDENT) {
-        const int64_t lo = (int64_t)tid * ITEMS < n ? (int64_t)tid * ITEMS : n, hi = lo + ITEMS < n ? lo + ITEMS : n;
-        const int64_t base = (int64_t)tid * ITEMS;
-        auto bits_of = [&](int64_t i) {
-            uint32_t b = PAD_BITS;
+        int gt = 0, eq = 0;
 #pragma unroll
-            for (int j = 0; j < ITEMS; ++j) b = (i - base == j) ? held[j] : b;       // register select, no scratch
-            return b;
-        };
-        compact<T>(a, lo, hi, remaining, wsum,
-                   [&](int64_t i) { const uint32_t key = key_of(__uint_as_float(bits_of(i))); return key > thr ? 2 : key == thr ? 1 : 0; },
-                   [&](int64_t i) { return __uint_as_float(bits_of(i)); });
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint32_t key = key_of(__uint_as_float(held[j]));
+            gt += j < mine && key > thr;
+            eq += j < mine && key == thr;
+        }
+        int total;
+        const int both = block_scan<T>(gt | (eq << 16), wsum, &total) - (gt | (eq << 16));
+        int g = both & 0xFFFF, e = (int)((uint32_t)both >> 16);
+        if (gt + eq == 0) return;
+        int32_t* idx = a.idx + (int64_t)blockIdx.x * a.k;
+        float* val = a.val + (int64_t)blockIdx.x * a.k;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint32_t key = key_of(__uint_as_float(held[j]));
+            const bool above = j < mine && key > thr, equal = j < mine && key == thr;
+            const int pos = g + (e < remaining ? e : remaining);
+            if ((above || (equal && e < remaining)) && pos < a.k) {         // (pos < k: always true for NaN-free rows)
+                idx[pos] = tid * ITEMS + j;
+                val[pos] = __uint_as_float(held[j]);
+            }
+            g += above;
+            e += equal;
+        }
     } else {
         const int64_t seg = (n + T - 1) / T;
         const int64_t lo = tid * seg < n ? tid * seg : n, hi = lo + seg < n ? lo + seg : n;
@@ -254,7 +363,8 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
 // One workgroup of 1024 lanes per row (no scratch is lent, so rows are not split over workgroups), 16 bytes per lane and
 // load; what bounds it is what one CU can fetch.  The general form reads the row five times: three histogram passes and
 // two of ordered compaction.  The filter reads it twice (8 x 131072, k = 64: 256 lanes took 460 us, the general form 94,
-// this one 27.5, 18.5 of them for k = 1, where the second read is one lane's; 128 x 200000, k = 100: 1426 -> 40) and
+// this one 27.5, 23 since its
+// scans are short, 18.5 and 16 of them for k = 1, where the second read is one lane's; 128 x 200000, k = 100: 1426 -> 40) and
 // everything else works on few keys:
 //   1. each lane keeps the largest value of four interleaved groups of elements (4096 groups in all);
 //   2. the k-th largest of the 4096 maxima is a lower bound of the row's k-th largest value (k groups each hold an
@@ -311,7 +421,11 @@ struct LongShared {
     uint16_t bucketed[LONG_CAP], ordered[LONG_CAP];
     int wsum[LONG_T / 64];
     int wcount[2][LONG_T / 64];
-    int digit, left, listed;
+    int bins[64];
+    uint32_t few_keys[FEW_KEYS];
+    Digit found;
+    Cut cut;
+    int listed, few;
 };
 
 // the k-th largest of the keys held, digit by digit from the top; `passes` digits of 11, 11, 10 bits, the rest zero
@@ -330,12 +444,38 @@ __device__ __forceinline__ uint32_t select_key(LongShared& sh, const uint32_t (&
         for (int j = 0; j < ITEMS; ++j)
             if (j * LONG_T + tid < count && (key[j] & mask) == prefix) atomicAdd(&sh.hist[(key[j] >> shift) & (nb - 1)], 1);
         __syncthreads();
-        pick_digit<LONG_T>(sh.hist, nb, remaining, sh.wsum, &sh.digit, &sh.left);
-        prefix |= (uint32_t)sh.digit << shift;
+        pick_digit<LONG_T>(sh.hist, nb, remaining, sh.wsum, &sh.found);
+        prefix |= (uint32_t)sh.found.digit << shift;
         mask |= (uint32_t)(nb - 1) << shift;
-        remaining = sh.left;
+        remaining = sh.found.left;
     }
     return prefix;
+}
+
+// the cut between the k largest of the keys held and the rest
+template <int ITEMS>
+__device__ __forceinline__ Cut select_cut(LongShared& sh, const uint32_t (&key)[ITEMS], int count, int k)
+{
+    const int tid = threadIdx.x;
+    int remaining = k;
+    if (tid == 0) sh.few = 0;
+    const uint32_t first = select_key(sh, key, count, 1, remaining);
+    const int in_digit = sh.found.count;
+    if (in_digit > FEW_KEYS) {
+        remaining = k;
+        const uint32_t thr = select_key(sh, key, count, 3, remaining);
+        return Cut{thr, remaining};
+    }
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+        if (j * LONG_T + tid < count && key[j] >> 21 == first >> 21) sh.few_keys[atomicAdd(&sh.few, 1)] = key[j];
+    __syncthreads();
+    if (tid < 64) {
+        const Cut c = cut_of_listed(sh.few_keys, sh.bins, in_digit, remaining, first, 21);
+        if (tid == 0) sh.cut = c;
+    }
+    __syncthreads();
+    return sh.cut;
 }
 
 // any k, any values: every pass reads the row
@@ -357,10 +497,10 @@ __device__ void long_row_general(const TopkArgs& a, const float* row, LongShared
             }
         });
         __syncthreads();
-        pick_digit<LONG_T>(sh.hist, nb, remaining, sh.wsum, &sh.digit, &sh.left);
-        prefix |= (uint32_t)sh.digit << shift;
+        pick_digit<LONG_T>(sh.hist, nb, remaining, sh.wsum, &sh.found);
+        prefix |= (uint32_t)sh.found.digit << shift;
         mask |= (uint32_t)(nb - 1) << shift;
-        remaining = sh.left;
+        remaining = sh.found.left;
     }
     // ordered compaction: a wave owns a contiguous run of whole 256-element steps
     const int64_t seg = (a.n + LONG_GROUPS - 1) / LONG_GROUPS * 256;
@@ -428,7 +568,7 @@ __device__ bool long_row_filtered(const TopkArgs& a, const float* row, LongShare
     // groups whose maxima reach the bound: each puts an element on the list at least, and far more of them than k means
     // that a run of equal values is the threshold (2048 x 12289 zeros, k = 64: 428 -> 407 us,
     // 383 with 256 lanes and five passes; 64 x 131072: 395 -> 392, 595)
-    if ((int)a.k - remaining + sh.hist[sh.digit] > LONG_MAX_REACH) {
+    if ((int)a.k - remaining + sh.found.count > LONG_MAX_REACH) {
         __syncthreads();                        // (the general form clears the histogram)
         return false;
     }
@@ -459,8 +599,9 @@ __device__ bool long_row_filtered(const TopkArgs& a, const float* row, LongShare
         key[j] = c < listed ? key_of(__uint_as_float(sh.bits[c])) : 0;
         pos[j] = c < listed ? sh.idx[c] : 0;
     }
-    remaining = (int)a.k;
-    const uint32_t thr = select_key(sh, key, listed, 3, remaining);
+    const Cut cut = select_cut(sh, key, listed, (int)a.k);
+    const uint32_t thr = cut.thr;
+    remaining = cut.equal;
     // counting sort by index: 2048 buckets of consecutive indices, then the rank among the bucket's few elements
     int shift = 0;
     while (((a.n - 1) >> shift) >= 2048) ++shift;
@@ -525,7 +666,7 @@ __global__ __launch_bounds__(LONG_T) void topk_long(TopkArgs a)
 {
     __shared__ LongShared sh;
     const float* row = a.x + (int64_t)blockIdx.x * a.ld;
-    if (threadIdx.x == 0) { sh.digit = 0; sh.left = 0; sh.listed = 0; }      // a row of NaNs may leave a digit unfound
+    if (threadIdx.x == 0) { sh.found = Digit{0, 0, 0}; sh.listed = 0; }      // a row of NaNs may leave a digit unfound
     if (long_row_takes_filter(a.n, a.k) && long_row_filtered(a, row, sh)) return;
     long_row_general(a, row, sh);
 }
