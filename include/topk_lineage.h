@@ -9,7 +9,9 @@
  *     T1 radix select     the k-th largest key by four 8-bit histogram passes over the row (most
  *                         significant digit first), then one ordered compaction pass; rows beyond 4096
  *                         elements (5000 from 513 rows on) by 11 + 11 + 10 bits on 1024 lanes, beyond
- *                         12288 elements (k <= 2048) by a filter on 4096 group maxima first
+ *                         12288 elements (k <= 2048) by a filter on 4096 group maxima first; up to 32
+ *                         rows beyond 16384 elements (49152 where k > 256) are cut into parts of 4096,
+ *                         a workgroup each, whose large elements a second kernel merges
  *     T2 resident coarse + refine   the row's keys stay in registers (one load); an 11-bit coarse
  *                         histogram finds the threshold's bin, two refine passes (11 + 10 bits) over
  *                         the candidates in that bin finish it; compaction from the registers
@@ -21,7 +23,9 @@
  * unspecified (but memory-safe) selection.
  *
  * Conventions as in gemm_lineage.h: x, idx, val are DEVICE pointers owned by the caller; descriptors
- * and query results are HOST memory; nothing is allocated, no state is kept; launches are asynchronous
+ * and query results are HOST memory; nothing is allocated, no state is kept from call to call (the parts of
+ * cut rows meet in device memory that belongs to the loaded library, 4 MiB, in slots held while the call runs;
+ * a row that finds its slot taken by a call on another stream is read uncut); launches are asynchronous
  * on the given stream; errors are gemm_status_t values; on any status other than GEMM_OK nothing was
  * launched; a state whose conditions do not hold is refused with GEMM_ERR_PRECONDITION.
  */
@@ -59,10 +63,10 @@ typedef struct {
 
 typedef struct {
     uint32_t required, violated, holds; /* TOPK_COND_* */
-    int32_t  threads;                   /* workgroup size; one workgroup per row */
+    int32_t  threads;                   /* workgroup size; one workgroup per row, or per part of a row that T1 cuts */
     int32_t  passes;                    /* passes over the row's keys (histogram passes + compaction; k rounds for T0);
-                                         * with T1's filter the 2 of a row whose candidates it holds: rows of equal values,
-                                         * which the query cannot know of, take 6 or 7 */
+                                         * with T1's filter the 2, with its parts the 1, of a row whose candidates they hold: rows
+                                         * of equal values, which the query cannot know of, take up to 8 */
     int32_t  lds_bytes;
     int64_t  grid;
     char     path[64];

@@ -7,6 +7,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <atomic>
+
 #include "../../include/topk_lineage.h"
 
 namespace {
@@ -40,6 +42,19 @@ __device__ __forceinline__ int wave_scan(int v)
     v = row_scan(v);
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);      // row_bcast:15 into rows 1 and 3
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// The wave's largest value, in lane 63.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    auto with = [&](uint32_t o) { v = o > v ? o : v; };
+    with(__builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
+    with(__builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+    with(__builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+    with(__builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+    with(__builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+    with(__builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
     return v;
 }
 
@@ -550,10 +565,86 @@ __device__ void long_row_general(const TopkArgs& a, const float* row, LongShared
     }
 }
 
+// The k largest of the `listed` elements in LDS, in index order.  Elements below the key `bound` may be missing from the list:
+// false, and nothing written, when one of the k lies below it.
+constexpr int SHORT_K = LONG_T / 4;
+__device__ bool finish_list(const TopkArgs& a, LongShared& sh, int listed, uint32_t bound)
+{
+    const int tid = threadIdx.x;
+    uint32_t key[LONG_CAP / LONG_T];
+    int total;
+    int32_t pos[LONG_CAP / LONG_T];
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
+        const int c = j * LONG_T + tid;
+        key[j] = c < listed ? key_of(__uint_as_float(sh.bits[c])) : 0;
+        pos[j] = c < listed ? sh.idx[c] : 0;
+    }
+    const Cut cut = select_cut(sh, key, listed, (int)a.k);
+    const uint32_t thr = cut.thr;
+    const int remaining = cut.equal;
+    // the smallest key taken is `thr`, or above it where none of those that equal it is taken
+    if ((remaining > 0 ? thr : thr + 1) < bound) return false;
+    int32_t* idx = a.idx + (int64_t)blockIdx.x * a.k;
+    float* val = a.val + (int64_t)blockIdx.x * a.k;
+    // counting sort by index: 2048 buckets of consecutive indices, then the rank among the bucket's few elements
+    int shift = 0;
+    while (((a.n - 1) >> shift) >= 2048) ++shift;
+    sh.hist[2 * tid] = sh.hist[2 * tid + 1] = 0;
+    __syncthreads();
+    int slot[LONG_CAP / LONG_T];
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
+        if (j * LONG_T + tid < listed) slot[j] = atomicAdd(&sh.hist[pos[j] >> shift], 1);
+    __syncthreads();
+    const int h0 = sh.hist[2 * tid], h1 = sh.hist[2 * tid + 1];
+    const int start = block_scan<LONG_T>(h0 + h1, sh.wsum, &total) - h0 - h1;
+    sh.hist[2 * tid] = start;
+    sh.hist[2 * tid + 1] = start + h0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
+        if (j * LONG_T + tid < listed) sh.bucketed[sh.hist[pos[j] >> shift] + slot[j]] = (uint16_t)(j * LONG_T + tid);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
+        if (j * LONG_T + tid < listed) {
+            const int b = pos[j] >> shift, first = sh.hist[b], last = b + 1 < 2048 ? sh.hist[b + 1] : listed;
+            int rank = 0;
+            for (int c = first; c < last; ++c) rank += sh.idx[sh.bucketed[c]] < pos[j];
+            sh.ordered[first + rank] = (uint16_t)(j * LONG_T + tid);
+        }
+    __syncthreads();
+    const int lo = tid * (LONG_CAP / LONG_T);
+    int c[LONG_CAP / LONG_T], gt = 0, eq = 0;
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
+        c[j] = lo + j < listed ? sh.ordered[lo + j] : -1;
+        key[j] = c[j] >= 0 ? key_of(__uint_as_float(sh.bits[c[j]])) : 0;
+        gt += c[j] >= 0 && key[j] > thr;
+        eq += c[j] >= 0 && key[j] == thr;
+    }
+    const int both = block_scan<LONG_T>(gt | (eq << 16), sh.wsum, &total) - (gt | (eq << 16));
+    int g = both & 0xFFFF, e = both >> 16;
+#pragma unroll
+    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
+        if (c[j] < 0) break;
+        if (key[j] > thr || (key[j] == thr && e < remaining)) {
+            const int at = g + (e < remaining ? e : remaining);
+            if (at < a.k) {
+                idx[at] = sh.idx[c[j]];
+                val[at] = __uint_as_float(sh.bits[c[j]]);
+            }
+        }
+        g += key[j] > thr;
+        e += key[j] == thr;
+    }
+    return true;
+}
+
 // k <= LONG_MAX_K; false (nothing written) when the list does not hold the row's candidates
 __device__ bool long_row_filtered(const TopkArgs& a, const float* row, LongShared& sh)
 {
-    const int tid = threadIdx.x;
     float top[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     auto larger = [](float v, float w) { return __builtin_amdgcn_fmed3f(v, w, INFINITY); };
     for_each_of_lane<8>(row, a.n, [&](float4_u v, int64_t, int) {
@@ -592,71 +683,7 @@ __device__ bool long_row_filtered(const TopkArgs& a, const float* row, LongShare
     __syncthreads();
     const int listed = sh.listed;
     if (listed > LONG_CAP || listed < a.k) return false;            // fewer than k only where NaNs hid a group's elements
-    int32_t pos[LONG_CAP / LONG_T];
-#pragma unroll
-    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
-        const int c = j * LONG_T + tid;
-        key[j] = c < listed ? key_of(__uint_as_float(sh.bits[c])) : 0;
-        pos[j] = c < listed ? sh.idx[c] : 0;
-    }
-    const Cut cut = select_cut(sh, key, listed, (int)a.k);
-    const uint32_t thr = cut.thr;
-    remaining = cut.equal;
-    // counting sort by index: 2048 buckets of consecutive indices, then the rank among the bucket's few elements
-    int shift = 0;
-    while (((a.n - 1) >> shift) >= 2048) ++shift;
-    sh.hist[2 * tid] = sh.hist[2 * tid + 1] = 0;
-    __syncthreads();
-    int slot[LONG_CAP / LONG_T];
-#pragma unroll
-    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
-        if (j * LONG_T + tid < listed) slot[j] = atomicAdd(&sh.hist[pos[j] >> shift], 1);
-    __syncthreads();
-    const int h0 = sh.hist[2 * tid], h1 = sh.hist[2 * tid + 1];
-    int total;
-    const int start = block_scan<LONG_T>(h0 + h1, sh.wsum, &total) - h0 - h1;
-    sh.hist[2 * tid] = start;
-    sh.hist[2 * tid + 1] = start + h0;
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
-        if (j * LONG_T + tid < listed) sh.bucketed[sh.hist[pos[j] >> shift] + slot[j]] = (uint16_t)(j * LONG_T + tid);
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < LONG_CAP / LONG_T; ++j)
-        if (j * LONG_T + tid < listed) {
-            const int b = pos[j] >> shift, first = sh.hist[b], last = b + 1 < 2048 ? sh.hist[b + 1] : listed;
-            int rank = 0;
-            for (int c = first; c < last; ++c) rank += sh.idx[sh.bucketed[c]] < pos[j];
-            sh.ordered[first + rank] = (uint16_t)(j * LONG_T + tid);
-        }
-    __syncthreads();
-    const int lo = tid * (LONG_CAP / LONG_T);
-    int c[LONG_CAP / LONG_T], gt = 0, eq = 0;
-#pragma unroll
-    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
-        c[j] = lo + j < listed ? sh.ordered[lo + j] : -1;
-        key[j] = c[j] >= 0 ? key_of(__uint_as_float(sh.bits[c[j]])) : 0;
-        gt += c[j] >= 0 && key[j] > thr;
-        eq += c[j] >= 0 && key[j] == thr;
-    }
-    const int both = block_scan<LONG_T>(gt | (eq << 16), sh.wsum, &total) - (gt | (eq << 16));
-    int g = both & 0xFFFF, e = both >> 16;
-    int32_t* idx = a.idx + (int64_t)blockIdx.x * a.k;
-    float* val = a.val + (int64_t)blockIdx.x * a.k;
-#pragma unroll
-    for (int j = 0; j < LONG_CAP / LONG_T; ++j) {
-        if (c[j] < 0) break;
-        if (key[j] > thr || (key[j] == thr && e < remaining)) {
-            const int at = g + (e < remaining ? e : remaining);
-            if (at < a.k) {
-                idx[at] = sh.idx[c[j]];
-                val[at] = __uint_as_float(sh.bits[c[j]]);
-            }
-        }
-        g += key[j] > thr;
-        e += key[j] == thr;
-    }
+    finish_list(a, sh, listed, 0);
     return true;
 }
 
@@ -671,6 +698,246 @@ __global__ __launch_bounds__(LONG_T) void topk_long(TopkArgs a)
     long_row_general(a, row, sh);
 }
 
+// ---- T1 on few long rows ---------------------------------------------------------------------------
+// One workgroup reads a row no faster than one CU can fetch, and most CUs have no row.  Here a row is cut into parts of 4096
+// elements (blocks of 256 in turn, so that a run of large values is shared out), a workgroup each: it keeps its elements in
+// registers, finds its own `want`-th largest and lists its elements from there up.  A second kernel, one workgroup per row,
+// finds the k largest of the lists.  Its result is checked, not assumed: what a part has not listed lies below that part's
+// bound, so the result holds if all k lie at or above the largest bound; for k <= want they always do, for more only where the
+// row's large values are spread out.  A row for which it does not hold, or one of whose parts has more elements equal to its
+// bound than there is room for, is read again by the one workgroup as if it had not been cut.
+//
+// The lists are device memory of the loaded library (one copy per GPU, held until the process ends), because the interface
+// lends no scratch.  A call's rows take consecutive slots from a ticket; the first part to arrive claims the row's slot for the
+// address of the row's output, which no other call that runs at the same time can share, later parts join it, and the second
+// kernel gives it back.  A part that finds its slot held by another call's row (more than PART_SLOTS rows in flight on several
+// streams) leaves: the second kernel then sees that not all parts came, and reads the row itself.  Nothing waits for anything.
+constexpr int PART_N = 4 * LONG_T, PART_BLOCK = 256;
+constexpr int PART_SLOTS = 128, PART_LIST = LONG_CAP, PART_MAX = 64;       // rows, elements listed per row, parts per row
+struct PartSlot {
+    unsigned long long owner;           // address of the row's indices, 0: free
+    unsigned int arrived;
+    uint2 part[PART_MAX];               // elements listed (more than there is room for: ~0) and bound of each part
+    uint2 list[PART_LIST];              // pattern and index; part i's begin at i * room
+};
+__device__ PartSlot part_slots[PART_SLOTS];
+struct PartArgs { int parts, room, want; unsigned int room_inverse, first_slot; };     // room_inverse: 2^32 / room, rounded up
+
+__global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
+{
+    __shared__ int hist[2048];
+    __shared__ int wsum[2][LONG_T / 64];
+    __shared__ uint32_t few[FEW_KEYS];
+    __shared__ int bins[64], listed, ok;
+    __shared__ Digit found;
+    __shared__ Cut cut;
+    const int tid = threadIdx.x, row_no = (int)blockIdx.x / p.parts, part = (int)blockIdx.x % p.parts;
+    const float* row = a.x + (int64_t)row_no * a.ld;
+    PartSlot& slot = part_slots[(p.first_slot + (unsigned)row_no) % PART_SLOTS];
+    // a wave's block of 256 elements, four per lane
+    const int first = ((tid >> 6) * p.parts + part) * PART_BLOCK + 4 * (tid & 63);      // (PART_MAX parts: below 2^18)
+    const int there = first >= a.n ? 0 : first + 4 <= a.n ? 4 : (int)a.n - first;
+    float4_u held = {0, 0, 0, 0};
+    if (there == 4) held = *(const float4_u*)(row + first);
+    else
+        for (int e = 0; e < there; ++e) held[e] = row[first + e];
+    if (tid == 0) {
+        const unsigned long long tag = (unsigned long long)(uintptr_t)(a.idx + (int64_t)row_no * a.k);
+        unsigned long long seen = 0;
+        ok = __hip_atomic_compare_exchange_strong(&slot.owner, &seen, tag, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || seen == tag;
+        listed = 0;
+        found = Digit{0, 0, 0};
+    }
+    hist[tid] = hist[LONG_T + tid] = 0;
+    __syncthreads();
+    if (!ok) return;
+    uint32_t key[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        key[e] = key_of(held[e]);
+        if (e < there) atomicAdd(&hist[key[e] >> 21], 1);
+    }
+    __syncthreads();
+    pick_digit<LONG_T>(hist, 2048, p.want, wsum[0], &found);
+    // the elements of the digit found and of those above it, where there is room for them; else from the want-th largest up
+    uint32_t bound = (uint32_t)found.digit << 21;         // (fewer than `want` elements: 0, all of them are listed)
+    const int count = found.count, at_least = p.want - found.left + count;
+    if (at_least > p.room && count <= FEW_KEYS) {
+        int in_digit = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) in_digit += e < there && key[e] >> 21 == bound >> 21;
+        int at = take_places(in_digit, &listed);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < there && key[e] >> 21 == bound >> 21) few[at++] = key[e];
+        __syncthreads();
+        if (tid < 64) {
+            const Cut c = cut_of_listed(few, bins, count, found.left, bound, 21);
+            if (tid == 0) cut = c;
+        }
+        __syncthreads();
+        bound = cut.equal > 0 ? cut.thr : cut.thr + 1;
+    }
+    int n = 0, total;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) n += e < there && key[e] >= bound;
+    int at = join_scan<LONG_T>(wave_scan(n), wsum[1], &total) - n;
+    if (total <= p.room && n > 0) {
+        uint2* list = slot.list + part * p.room;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < there && key[e] >= bound) list[at++] = make_uint2(__float_as_uint(held[e]), (uint32_t)(first + e));
+    }
+    if (tid == 0) {
+        slot.part[part] = make_uint2(total <= p.room ? (unsigned)total : ~0u, bound);
+        __hip_atomic_fetch_add(&slot.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+__global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
+{
+    constexpr int ITEMS = PART_LIST / LONG_T;
+    __shared__ LongShared sh;
+    __shared__ uint2 part[PART_MAX];
+    __shared__ unsigned int lowest, largest_bound, highest, too_many;
+    const int tid = threadIdx.x;
+    const float* row = a.x + (int64_t)blockIdx.x * a.ld;
+    PartSlot& slot = part_slots[(p.first_slot + blockIdx.x) % PART_SLOTS];
+    const unsigned long long tag = (unsigned long long)(uintptr_t)(a.idx + (int64_t)blockIdx.x * a.k);
+    // all that may be wanted is loaded at once: each wait is a trip to what another XCD has written
+    const unsigned long long owner = slot.owner;
+    const unsigned int arrived = slot.arrived;
+    const uint2 mine = tid < PART_MAX ? slot.part[tid] : make_uint2(0, 0);
+    uint2 entry[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) entry[j] = slot.list[j * LONG_T + tid];
+    if (tid == 0) { sh.found = Digit{0, 0, 0}; sh.listed = sh.few = 0; lowest = ~0u; largest_bound = highest = 0; too_many = 0; }
+    sh.hist[tid] = sh.hist[LONG_T + tid] = 0;
+    __syncthreads();
+    const bool held = owner == tag;
+    if (tid < PART_MAX) {
+        part[tid] = mine;
+        if (held && tid < p.parts) {
+            atomicMin(&lowest, mine.y);
+            atomicMax(&largest_bound, mine.y);
+            if (mine.x > (unsigned)p.room) too_many = 1;
+        }
+    }
+    __syncthreads();
+    // (all of the slot has been read; while it is held nobody else changes it)
+    if (held && tid == 0) {
+        __hip_atomic_store(&slot.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&slot.owner, 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (held && arrived == (unsigned)p.parts && !too_many) {
+        bool there[ITEMS];
+        uint32_t key[ITEMS], top = 0;
+        int n = 0, listed;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const unsigned i = j * LONG_T + tid, of = __umulhi(i, p.room_inverse);
+            there[j] = of < (unsigned)p.parts && i - of * p.room < part[of < PART_MAX ? of : 0].x;
+            key[j] = key_of(__uint_as_float(entry[j].x));
+            n += there[j];
+            if (there[j] && key[j] > top) top = key[j];
+        }
+        top = wave_max(top);
+        if ((tid & 63) == 63) atomicMax(&highest, top);
+        int at = join_scan<LONG_T>(wave_scan(n), sh.wsum, &listed) - n;
+        if (listed >= a.k && a.k <= SHORT_K) {
+            // The keys lie between the lowest bound and the highest key: 2047 bins over that range (a few bins of the key's
+            // top bits would hold nearly all of them, and additions to one bin wait for each other).
+            const uint32_t range = highest - lowest;
+            int shift = range < 2048 ? 0 : 21 - __clz(range);                   // range >> shift: 1024 .. 2047
+            if (range >> shift > 2046) ++shift;
+            auto place_of = [&](uint32_t k) { return k - lowest + (1u << shift); };       // (bins from 1: see cut_of_listed on 0)
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j)
+                if (there[j]) atomicAdd(&sh.hist[place_of(key[j]) >> shift], 1);
+            __syncthreads();
+            pick_digit<LONG_T>(sh.hist, 2048, (int)a.k, sh.wsum, &sh.found);
+            const uint32_t digit = sh.found.digit;
+            const int count = sh.found.count;
+            Cut c = {digit << shift, sh.found.left};
+            if (count <= FEW_KEYS) {
+                int in_digit = 0;
+#pragma unroll
+                for (int j = 0; j < ITEMS; ++j) in_digit += there[j] && place_of(key[j]) >> shift == digit;
+                int to = take_places(in_digit, &sh.few);
+#pragma unroll
+                for (int j = 0; j < ITEMS; ++j)
+                    if (there[j] && place_of(key[j]) >> shift == digit) sh.few_keys[to++] = place_of(key[j]);
+                __syncthreads();
+                if (tid < 64) {
+                    const Cut w = cut_of_listed(sh.few_keys, sh.bins, count, sh.found.left, digit << shift, shift);
+                    if (tid == 0) { sh.cut = w; sh.few = 0; }
+                }
+                __syncthreads();
+                c = sh.cut;
+                // a clean cut: the k keys above c.thr are taken, and their order by index is each one's rank among them
+                if (c.equal == 0 && c.thr + 1 + lowest - (1u << shift) >= largest_bound) {
+                    int taken = 0;
+#pragma unroll
+                    for (int j = 0; j < ITEMS; ++j) taken += there[j] && place_of(key[j]) > c.thr;
+                    int to = take_places(taken, &sh.few);
+#pragma unroll
+                    for (int j = 0; j < ITEMS; ++j)
+                        if (there[j] && place_of(key[j]) > c.thr && to < SHORT_K) {
+                            sh.bits[to] = entry[j].x;
+                            sh.idx[to++] = (int32_t)entry[j].y;
+                        }
+                    __syncthreads();
+                    const int k = (int)a.k, q = tid >> 2;           // four lanes for one
+                    if (q < k) {
+                        const int32_t index = sh.idx[q];
+                        int rank = 0;
+                        for (int i = tid & 3; i < k; i += 4) rank += sh.idx[i] < index;
+                        rank += __shfl_xor(rank, 1, 64);
+                        rank += __shfl_xor(rank, 2, 64);
+                        if ((tid & 3) == 0) {
+                            a.idx[(int64_t)blockIdx.x * a.k + rank] = index;
+                            a.val[(int64_t)blockIdx.x * a.k + rank] = __uint_as_float(sh.bits[q]);
+                        }
+                    }
+                    return;
+                }
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j)
+            if (there[j]) {
+                sh.bits[at] = entry[j].x;
+                sh.idx[at++] = (int32_t)entry[j].y;
+            }
+        __syncthreads();
+        if (listed >= a.k && finish_list(a, sh, listed, largest_bound)) return;
+        __syncthreads();
+        if (tid == 0) { sh.found = Digit{0, 0, 0}; sh.listed = 0; }
+        __syncthreads();
+    }
+    if (long_row_takes_filter(a.n, a.k) && long_row_filtered(a, row, sh)) return;
+    long_row_general(a, row, sh);
+}
+
+// Which rows are cut: up to 32 of them (beyond, one workgroup per row has enough CUs: uncut / cut, k = 16, 64 x 32768 16.1 /
+// 16.0 us, 64 x 131072 26.4 / 32.6, 128 x 131072 29.1 / 52.0), longer than the resident state takes.  Uncut / cut: 1 x 17000,
+// k = 16, 14.1 / 10.5; 24 x 24000, k = 200, 21.3 / 14.6; 8 x 131072, k = 64, 26.6 / 14.9; 1 x 200000, k = 16, 27.2 / 13.5; 24 x
+// 200000, k = 16, 34.1 / 25.1.  More than SHORT_K elements take the slower end of the second kernel, which pays on longer rows:
+// k = 500, 8 x 17000 18.0 / 18.1, 8 x 32768 21.4 / 20.0, 8 x 50000 27.0 / 20.9; k = 1500, 1 x 131072 48.0 / 23.8.
+constexpr int64_t PART_FROM_N = 16384, PART_FROM_N_MANY = 49152, PART_ROWS = 32;
+PartArgs parts_of(int64_t batch, int64_t n, int64_t k)
+{
+    const int64_t parts = (n + PART_N - 1) / PART_N;
+    if (batch < 1 || batch > PART_ROWS || n <= (k <= SHORT_K ? PART_FROM_N : PART_FROM_N_MANY) || parts > PART_MAX || k < 1) return PartArgs{};
+    const int room = (int)(PART_LIST / parts), want = room - room / 16;      // (a sixteenth is left for elements equal to the last one listed)
+    // of k elements spread at random a part holds more than this once in a million
+    const double mean = (double)k / (double)parts;
+    if (k > want && mean + 5 * __builtin_sqrt(mean) + 8 > want) return PartArgs{};
+    return PartArgs{(int)parts, room, want, (unsigned)((((uint64_t)1 << 32) + room - 1) / room), 0};
+}
+std::atomic<unsigned> part_ticket{0};
+
 constexpr int RES_ITEMS = 16;
 
 struct Plan {
@@ -679,6 +946,7 @@ struct Plan {
     TopkArgs a{};
     int threads = 0;
     int items = 0;          // T2: keys per lane
+    PartArgs parts{};       // T1: a row's parts (0: rows are not cut)
     hipStream_t stream = nullptr;
     topk_query_t q{};
 };
@@ -709,6 +977,12 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
         p.threads = SEL_T; q.passes = (int32_t)(d->k < 0x7FFFFFFF ? d->k : 0x7FFFFFFF); q.lds_bytes = SEL_MAX_N + 48;
         break;
     case TOPK_T1_RADIX_SELECT:
+        p.parts = parts_of(d->batch, d->n, d->k);
+        if (p.parts.parts > 0) {
+            path = "parts of 4096 listed and merged, else group-maxima filter";
+            p.threads = LONG_T; q.passes = 1; q.lds_bytes = 2048 * 4 + FEW_KEYS * 4 + 64 * 4 + 160;
+            break;
+        }
         // (the lines: see topk_long; a launch holds fewer than 2^32 threads, so 2^22 rows and more stay with 256 lanes each)
         if (d->n > (d->batch > LONG_MANY_ROWS ? LONG_MANY_N : 4096) && d->batch < ((int64_t)1 << 32) / LONG_T) {
             const bool filter = long_row_takes_filter(d->n, d->k);
@@ -731,7 +1005,7 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
     }
     q.required = required; q.holds = holds; q.violated = required & ~holds;
     q.threads = p.threads;
-    q.grid = p.empty ? 0 : d->batch;
+    q.grid = p.empty ? 0 : d->batch * (p.parts.parts > 0 ? p.parts.parts : 1);
     strncpy(q.path, path, sizeof(q.path) - 1);
     if (q.violated) p.status = GEMM_ERR_PRECONDITION;
     return p;
@@ -761,7 +1035,11 @@ int topk_run(int variant, const topk_desc_t* d, const float* x, int32_t* idx, fl
     const dim3 grid((unsigned)d->batch);
     if (variant == TOPK_T0_SELECTION)
         hipLaunchKernelGGL(topk_selection, grid, dim3(SEL_T), 0, p.stream, p.a);
-    else if (variant == TOPK_T1_RADIX_SELECT && p.threads == LONG_T)
+    else if (p.parts.parts > 0) {
+        p.parts.first_slot = part_ticket.fetch_add((unsigned)d->batch, std::memory_order_relaxed);
+        hipLaunchKernelGGL(topk_parts, dim3((unsigned)p.q.grid), dim3(LONG_T), 0, p.stream, p.a, p.parts);
+        hipLaunchKernelGGL(topk_merge, grid, dim3(LONG_T), 0, p.stream, p.a, p.parts);
+    } else if (variant == TOPK_T1_RADIX_SELECT && p.threads == LONG_T)
         hipLaunchKernelGGL(topk_long, grid, dim3(LONG_T), 0, p.stream, p.a);
     else if (variant == TOPK_T1_RADIX_SELECT)
         hipLaunchKernelGGL((topk_radix<256, 1, false, 4, 8, 8, 8, 8>), grid, dim3(256), 0, p.stream, p.a);

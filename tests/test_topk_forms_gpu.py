@@ -43,3 +43,47 @@ def test_resident_rows(kind, n, k):
 def by_sort(x, n, k):
     order = np.argsort(-(x[:, :n].astype(np.float64) + 0.0), axis=1, kind="stable")[:, :k]
     return np.sort(order, axis=1)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("batch,n,ld,k", [(1, 16385, 16385, 1), (3, 16640, 16641, 256), (32, 20481, 20484, 33), (2, 65537, 65537, 100), (2, 49153, 49153, 257), (1, 262144, 262144, 60)])
+def test_rows_cut_into_parts(kind, batch, n, ld, k):
+    """One element more than whole parts, rows that start at any element, the most rows and the most parts, k up to what the
+    second kernel ranks directly and one more, lists that overflow and large values that fall into one part.  Twice: the second
+    call finds the slots as the first one left them."""
+    x = rows(kind, batch, n, ld, np.random.default_rng(n + k))
+    want = by_sort(x, n, k)
+    for _ in range(2):
+        rc, idx, val, q = run_state(1, x, n, k)
+        assert rc == gemm.GEMM_OK and "parts" in q.path and q.grid == batch * -(-n // 4096), q
+        np.testing.assert_array_equal(idx, want)
+        np.testing.assert_array_equal(val.view(np.uint32), np.take_along_axis(x, want, 1).view(np.uint32))
+
+
+def test_parts_of_more_rows_than_slots_on_several_streams_and_under_a_graph():
+    """Eight streams with 32 rows each in flight at once: rows whose slot another call holds are read uncut, and every result
+    is the same; so is that of a graph, replayed among them."""
+    n, k, batch = 40000, 50, 32
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    xs = [torch.randn((batch, n), generator=gen, device="cuda") for _ in range(8)]
+    streams = [torch.cuda.Stream() for _ in xs]
+    outs = [(torch.zeros((batch, k), dtype=torch.int32, device="cuda"), torch.zeros((batch, k), device="cuda")) for _ in xs]
+    want = [torch.sort(torch.sort(x.cpu(), dim=1, descending=True, stable=True).indices[:, :k], dim=1).values for x in xs]
+    calls = [(topk.make_desc(batch, n, k, stream=s), x, *o) for s, x, o in zip(streams, xs, outs)]
+    graph = torch.cuda.CUDAGraph()
+    assert topk.topk_run(1, *calls[0]) == gemm.GEMM_OK
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=streams[0]):
+        assert topk.topk_run(1, *calls[0]) == gemm.GEMM_OK
+    for _ in range(6):
+        for idx, val in outs:
+            idx.zero_()
+            val.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(streams[0]):
+            graph.replay()
+        for c in calls[1:]:
+            assert topk.topk_run(1, *c) == gemm.GEMM_OK
+        torch.cuda.synchronize()
+        for x, (idx, val), w in zip(xs, outs, want):
+            assert torch.equal(idx.cpu().long(), w) and torch.equal(val, torch.gather(x, 1, idx.long()))
