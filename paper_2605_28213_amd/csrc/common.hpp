@@ -149,6 +149,10 @@ hipError_t launch_k4_ring(const Args& a);  // bf16, fp16, e4m3; k4_uses_ring(a) 
 // The persistent kernel on a row-major B read in place (bf16, fp16), and whether a product qualifies for it.
 bool k4_ring_takes_row_major_b(const Args& a);
 hipError_t launch_k4_ring_row_major_b(const Args& a);
+// The same kernel on a product with fewer tiles than workgroups, inside the masked state (whose conditions on the ends of
+// the operands are this kernel's): whether it is the faster form, and its launcher.
+bool k4_ring_takes_one_round(const Args& a);
+hipError_t launch_k4_ring_one_round(const Args& a);
 // Thin products (at most 64 rows) with A and B row-major, two-byte types: B is read once, in place.  The row-major-B
 // form above hands this kernel a remainder of rows that would cost it a round of tiles (the rule says when).
 bool k4_brow_splits_m_tail(const Args& a);
@@ -169,7 +173,8 @@ inline bool tail_element_in_last_page(const void* base, int64_t elems, int64_t l
 hipError_t launch_k4_thin_row_major_b(const Args& a);
 // The masked state's direct-to-LDS form (fp32, bf16, fp16; any layout and alignment): whether it takes a product, the
 // form it runs in (side of the tile, workgroups per tile and direction, slabs of the LDS ring) and its launcher.
-// (wide: 128 or 256 rows of k4_wide.hpp's tiles instead, 0: none).
+// (wide: 128 or 256 rows of k4_wide.hpp's tiles instead, WIDE_RING: the persistent kernel on a row-major B, 0: neither).
+constexpr int WIDE_RING = -1;
 struct DirectForm { int tile, parts, stages, wide = 0; };
 bool k4_direct_applies(const Args& a);
 DirectForm k4_direct_form(const Args& a);

@@ -6,7 +6,7 @@
 namespace gl {
 
 // Tiles of a product, and the workgroups they are launched as (parts: padded to groups of eight tiles).
-static int64_t direct_tiles(const Args& a, const DirectForm& f) { const int64_t cols = f.wide ? 128 : f.tile; return ((a.M + f.tile - 1) / f.tile) * ((a.N + cols - 1) / cols) * a.batch; }
+static int64_t direct_tiles(const Args& a, const DirectForm& f) { const int64_t cols = f.wide > 0 ? 128 : f.tile; return ((a.M + f.tile - 1) / f.tile) * ((a.N + cols - 1) / cols) * a.batch; }
 static int64_t direct_grid(const Args& a, const DirectForm& f) { return f.parts > 1 ? (direct_tiles(a, f) + 7) / 8 * 8 * f.parts * f.parts : direct_tiles(a, f); }
 
 // What the form asks for beyond the masked kernel: offsets that fit the loads' 32 bits (rows of a K-contiguous operand
@@ -42,7 +42,8 @@ bool k4_direct_applies(const Args& a)
 //     with two slabs; 1500^3, 144: 23.1 / 24.3 / 26.3), two with two slabs beyond (3000 x 2000 x 4000, 384: 61 against 82 us).
 //     From 6 slabs on, the wide tiles with loading waves take the one workgroup per CU (four slabs / wide, row-major: 2000 x
 //     2000 x 64 6.6 / 6.7, x 300 10.0 / 10.0, x 900 16.7 / 16.2; 1015 x 3863 x 1887 29.4 / 26.2; rows contiguous in both
-//     2048 x 2048 x 4096 43.1 / 34.5) and, where k4_wide_round draws the line, the products beyond.
+//     2048 x 2048 x 4096 43.1 / 34.5) and, where k4_wide_round draws the line, the products beyond; row-major ones beyond go to
+//     the persistent kernel's 256-tiles where k4_ring_takes_one_round does.
 // The lines were drawn on row-major operands.  In all four layouts, rows 4 or 16 bytes (fp32), 2 or 4 bytes aligned, every
 // product in each of five forms: the form chosen is within a twentieth of the best on 121 of 156 fp32 products, 1.17 at
 // worst (1000^3 with K contiguous in both: quarters 21.5 us, whole 64-tiles 25.2), and on 142 of 152 of fp16, 1.19 at worst.
@@ -52,6 +53,7 @@ DirectForm k4_direct_form(const Args& a)
     if (a.in_dtype == GEMM_F32) return t64 <= 192 ? DirectForm{64, 2, 4} : DirectForm{64, 1, 2};
     if (t64 <= 96) return DirectForm{64, 2, 4};
     if (t128 < 128) return DirectForm{64, 1, 4};
+    if (k4_ring_takes_one_round(a)) return DirectForm{256, 1, 0, WIDE_RING};
     if (a.K > 5 * (ROW_BYTES / 2))
         if (const int bm = k4_wide_round(a, 128, false)) return DirectForm{bm, 1, 0, bm};
     return t128 <= 256 ? DirectForm{128, 1, 4} : DirectForm{128, 1, 2};
@@ -96,6 +98,7 @@ bool k4_direct_beats_packing(const Args& a, int keep_mask)
 // stages: slabs in flight beyond the one in use
 static Geometry geometry_of(const Args& a, const DirectForm& f)
 {
+    if (f.wide == WIDE_RING) return Geometry{256, 256, ROW_BYTES / 2, 256, 2, 160 * 1024, K4_RING_WORKGROUPS};
     if (f.wide) return geometry_k4_wide(a, f.wide);
     return Geometry{f.tile, f.tile, ROW_BYTES / elem_size(a.in_dtype), 256, f.stages - 1, f.stages * 2 * (f.tile / f.parts) * ROW_BYTES, direct_grid(a, f)};
 }
@@ -150,6 +153,7 @@ template <typename IN>
 static hipError_t launch_form(const Args& a)
 {
     const DirectForm f = k4_direct_form(a);
+    if (f.wide == WIDE_RING) return launch_k4_ring_one_round(a);
     if (f.wide) return launch_k4_wide(a, f.wide);
     if (f.parts == 2) return launch_layout<IN, 64, 2, 4>(a);
     if constexpr (IN::BYTES == 4) {

@@ -42,6 +42,19 @@ static bool brow_shape_fits(const Args& a)
     if ((a.K + ke - 1) / ke < 3 || tiles < K4_RING_WORKGROUPS || tiles >= ((int64_t)1 << 31)) return false;
     return a.a_si * es <= ((int64_t)1 << 22) && a.K * a.b_sk * es < ((int64_t)1 << 31);
 }
+// 129 to 255 tiles leave CUs idle, but tiles of half the size need two rounds and twice the bytes from L2 to LDS.  With
+// 15 slabs and more that costs more than the idle CUs.  Row-major operands, two 128-tiles per CU / here: fp16 3300^3 (169
+// tiles) 108.3 / 77.0 us, 2900 x 2900 x 4000 (144) 117.6 / 79.6, 2816 x 3072 x 1500 47.3 / 35.8, 2310 x 3850 x 1000 (160, 16
+// slabs) 38.2 / 34.0, bf16 4096 x 2304 x 2304 57.3 / 45.1; 12 slabs 30.3 / 32.0, 11 33.6 / 32.9 (238 tiles), 7 21.3 / 25.5,
+// 4 15.5 / 22.0.
+bool k4_ring_takes_one_round(const Args& a)
+{
+    if (a.flags != 0 || elem_size(a.in_dtype) != 2 || a.a_sk != 1 || a.b_sj != 1) return false;
+    const int64_t tiles = ((a.M + 255) / 256) * ((a.N + 255) / 256) * a.batch;
+    return a.K > 14 * (ROW_BYTES / 2) && tiles > K4_RING_WORKGROUPS / 2 && tiles < K4_RING_WORKGROUPS && a.a_si * 2 <= ((int64_t)1 << 22) &&
+           a.K * a.b_sk * 2 < ((int64_t)1 << 31);
+}
+
 static bool brow_a_tail_mapped(const Args& a) { return tail_element_in_last_page(a.A, (a.batch - 1) * a.stride_a + (a.M - 1) * a.a_si + a.K, a.K, elem_size(a.in_dtype)); }
 static bool brow_b_tail_mapped(const Args& a) { return tail_element_in_last_page(a.B, (a.batch - 1) * a.stride_b + (a.K - 1) * a.b_sk + a.N, a.N, elem_size(a.in_dtype)); }
 
@@ -162,6 +175,12 @@ static hipError_t launch_brow_rows(const Args& a)
     case GEMM_F16: return launch_ring<F16, true>(a);
     default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_k4_ring_one_round(const Args& a)
+{
+    if (a.in_dtype == GEMM_BF16) return launch_ring<BF16, true>(a);
+    return a.in_dtype == GEMM_F16 ? launch_ring<F16, true>(a) : hipErrorInvalidValue;
 }
 
 hipError_t launch_k4_ring(const Args& a)

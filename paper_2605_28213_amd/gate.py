@@ -108,6 +108,8 @@ def kernel_patterns(variant: int, in_dtype: int, path: str, bm: int, bn: int, th
         return [r"k4_thin_brow<gl::ThinCfg<%s, %d, %d, " % (dt, 1 if bm <= 16 else 2 if bm <= 32 else 4, bn)]
     if path.endswith("(direct-to-lds)") and threads == 512:
         return [r"k4_mfma_wide<gl::WideCfg<%s, %d, (true|false), (true|false), 0, " % (dt, bm)]
+    if path.endswith("(direct-to-lds)") and bm == 256:
+        return [r"k4_mfma_ring<gl::RingCfg<%s, \d+, true>" % dt]
     if path.endswith("(direct-to-lds)"):
         return [r"k4_mfma_direct<gl::DirectCfg<%s, %d, " % (dt, bm)]
     if "direct-to-lds" in path:
