@@ -161,11 +161,19 @@ static bool k4_small_tiles_deep(const Args& a)
     return nslab >= 32 && ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch <= 256;
 }
 
-// Two-byte types without switches: the 128-tiles of one round, and some products beyond (k4_wide_round), are multiplied by
-// the kernel whose loads have waves of their own (k4_wide.hpp).  Fast kernel / wide tiles: 714 x 774 x 448 10.2 / 8.0 us,
+// Without switches, the 128-tiles of one round, and some products beyond (k4_wide_round), are multiplied by the kernel whose
+// loads have waves of their own (k4_wide.hpp).  Fast kernel / wide tiles, two-byte types: 714 x 774 x 448 10.2 / 8.0 us,
 // 1380 x 1968 x 2496 28.4 / 19.9, 2048^3 23.3 / 18.9, x 4096 39.8 / 32.0, 705 x 3004 x 768 13.6 / 10.2, 35 x 346 x 152 x 1024
-// 16.1 / 12.7; fewer tiles than CUs and a short K go to smaller ones (k4_direct_takes_few_tiles).
-int k4_fast_wide(const Args& a) { return a.K > 0 && k4_small_tiles(a) ? k4_wide_round(a, 1, true) : 0; }
+// 16.1 / 12.7; fewer tiles than CUs and a short K go to smaller ones (k4_direct_takes_few_tiles).  e4m3, whose fast kernel has
+// the shorter start: 20 x 400 x 300 x 640 11.3 / 9.3, 16 x 512 x 512 x 512 8.9 / 7.7, 8 x 500 x 500 x 512 9.4 / 8.4, 40 x 256 x
+// 256 x 384 6.8 / 6.0; with 8 slabs only where more than 128 tiles share the L2s' delivery: 25 x 300 x 200 x 1024 (150 tiles)
+// 10.8 / 10.5, 2 x 1024^3 (128) 8.5 / 9.0, 2 x 150 x 150 x 1024 (8) 8.4 / 9.5.
+int k4_fast_wide(const Args& a)
+{
+    if (a.K <= 0 || !k4_small_tiles(a)) return 0;
+    const bool e4m3 = a.in_dtype == GEMM_FP8_E4M3;
+    return k4_wide_round(a, e4m3 && a.K > 6 * ROW_BYTES ? 129 : 1, true);
+}
 
 // The expert instantiation, or one of its validated simplifications when the caller asks for it.
 template <typename IN>
@@ -285,7 +293,7 @@ bool k4_splitk_rotates(const Args& a)
 // 1.06 to 1.25.  More ranges than one round stay with k4_mfma_fast (110 x 8192^2, 512 of them, 47.6 / 47.0).
 // A B that streams from HBM (k4_splitk_rotates) is read past the caches' replacement, and neighbouring ranges are joined until
 // they fit one round, so that each of the 256 CUs keeps 64 KB of B in flight and half of the partial sums are written:
-// 128 x 16384 x 16384 in 4 ranges 115, in 2 joined pairs 119, with nt loads 105 (before: 121); e4m3 78.6 / 63.4;
+// 128 x 16384 x 16384 in 4 ranges 115, in 2 joined pairs 119, with nt loads 105 (before: 121); e4m3 78.6 / 62.1;
 // 128 x 8192 x 16384 76.3 / 57.1, 128 x 28672 x 4096 72.3 / 59.1.  (B alone, read by 256 workgroups in this pattern: 85 us in
 // the caches' order, 78 us with nt.  On a B that stays in the Infinity Cache nt costs: 100 x 4096 x 4096 16.4 / 20.6.)
 int k4_splitk_wide(const Args& a)

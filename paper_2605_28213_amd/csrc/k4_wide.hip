@@ -28,6 +28,7 @@ hipError_t launch_k4_wide(const Args& a, int bm)
 {
     if (a.in_dtype == GEMM_BF16) return bm == 128 ? launch_layout<BF16, 128>(a) : launch_layout<BF16, 256>(a);
     if (a.in_dtype == GEMM_F16) return bm == 128 ? launch_layout<F16, 128>(a) : launch_layout<F16, 256>(a);
+    if (a.in_dtype == GEMM_FP8_E4M3 && bm == 128 && a.a_sk == 1 && a.b_sk == 1) return launch_cfg<WideCfg<E4M3, 128, true, true>>(a);
     return hipErrorInvalidValue;
 }
 
@@ -58,11 +59,12 @@ hipError_t launch_k4_wide_ranges(const Args& a, bool stream_b)
 //     3749 x 1320 x 1232 (165, 20 slabs) 23.8 / 26.1, 1552 x 3984 x 456 (224, 8) 14.3 / 16.9.
 int k4_wide_round(const Args& a, int64_t t128_from, bool aligned)
 {
-    if (elem_size(a.in_dtype) != 2 || a.flags != 0) return 0;
-    const int64_t nslab = (a.K + ROW_BYTES / 2 - 1) / (ROW_BYTES / 2), cols = (a.N + 127) / 128 * a.batch;
+    const int es = elem_size(a.in_dtype);
+    if (a.flags != 0 || (es != 2 && !(es == 1 && aligned))) return 0;
+    const int64_t nslab = (a.K * es + ROW_BYTES - 1) / ROW_BYTES, cols = (a.N + 127) / 128 * a.batch;
     const int64_t t128 = (a.M + 127) / 128 * cols, t256 = (a.M + 255) / 256 * cols;
     if (t128 >= t128_from && t128 <= 256) return 128;
-    return t128 > 256 && t256 >= 176 && t256 <= 256 && nslab >= (aligned ? 16 : 24) ? 256 : 0;
+    return es == 2 && t128 > 256 && t256 >= 176 && t256 <= 256 && nslab >= (aligned ? 16 : 24) ? 256 : 0;
 }
 
 // (stages: slabs in flight beyond the one in use)

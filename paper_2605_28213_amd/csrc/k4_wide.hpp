@@ -24,8 +24,10 @@ namespace gl {
 // 256 x 128: three slabs of both operands (144 KB), every loading wave loads both.  128 x 128: five slabs (160 KB); with K
 // contiguous in both operands two waves load four slabs of A and two load five of B (nine regions, 144 KB).
 // ROT, NT: K ranges of a thin product (see k4_splitk_wide): the K walk starts ROT slabs later from one tile to the next, and B,
-// which nobody reads twice, is loaded past the caches' replacement (nt) so that A stays in the L2s.  e4m3 comes in this form
-// only: its chunk of 16 bytes is two v_mfma_f32_16x16x32_fp8_fp8.
+// which nobody reads twice, is loaded past the caches' replacement (nt) so that A stays in the L2s.
+//
+// e4m3 (K contiguous and aligned, 128-tiles): v_mfma_scale_f32_16x16x128 with unit scales takes a slab in one k-step, two
+// chunks per lane; fragments then alternate between two register slots from slab to slab.
 template <typename IN, int BM_, bool A_KC_, bool B_KC_, int ROT_ = 0, bool NT_ = false>
 struct WideCfg {
     using In = IN;
@@ -38,15 +40,20 @@ struct WideCfg {
     static constexpr int BASE_B = SA * REGION_A, LDS_BYTES = BASE_B + SB * REGION_B;
     static constexpr int LW = ROLES ? 2 : 4;                                           // waves that load an operand
     static constexpr int LDA = BM / 8 / LW, LDB = BN / 8 / LW;                         // direct loads per such wave and slab
-    static_assert((IN::BYTES == 2 || (IN::BYTES == 1 && ROT_ != 0)) && (BM_ == 128 || BM_ == 256), "two-byte types; e4m3 for K ranges");
+    static_assert((IN::BYTES == 2 || (IN::BYTES == 1 && ROLES)) && (BM_ == 128 || BM_ == 256), "two-byte types; e4m3 with K contiguous on 128-tiles");
     static_assert(ROT_ == 0 || ROLES, "K ranges have K contiguous in both operands");
 };
 
 template <typename IN>
-__device__ __forceinline__ void wide_step(const u32x4_t& a, const u32x4_t& b, f32x4_t& c)
+__device__ __forceinline__ void wide_step(const Frag<IN>& a, const Frag<IN>& b, f32x4_t& c)
 {
-    if constexpr (IN::BYTES == 2) mfma_step16<IN>(a, b, c);
-    else mfma16<IN>(a, b, c);
+    if constexpr (IN::BYTES == 2) {
+        mfma_step16<IN>(a.c[0], b.c[0], c);
+    } else {
+        const i32x8_t av = {(int)a.c[0].x, (int)a.c[0].y, (int)a.c[0].z, (int)a.c[0].w, (int)a.c[1].x, (int)a.c[1].y, (int)a.c[1].z, (int)a.c[1].w};
+        const i32x8_t bv = {(int)b.c[0].x, (int)b.c[0].y, (int)b.c[0].z, (int)b.c[0].w, (int)b.c[1].x, (int)b.c[1].y, (int)b.c[1].z, (int)b.c[1].w};
+        c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, c, 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
+    }
 }
 
 template <typename CFG>
@@ -55,7 +62,7 @@ void k4_mfma_wide(Args a, int tiles_m, int tiles_n, int flags)
 {
     using IN = typename CFG::In;
     constexpr int BM = CFG::BM, BN = CFG::BN, TMI = CFG::TMI, TNI = CFG::TNI, SA = CFG::SA, SB = CFG::SB, REGION_A = CFG::REGION_A, REGION_B = CFG::REGION_B, BASE_B = CFG::BASE_B;
-    constexpr int ES = IN::BYTES, KE = ROW_BYTES / ES, V = 16 / ES, LDA = CFG::LDA, LDB = CFG::LDB, LW = CFG::LW;
+    constexpr int ES = IN::BYTES, KE = ROW_BYTES / ES, V = 16 / ES, CPS = Frag<IN>::CPS, NK = 2 / CPS, LDA = CFG::LDA, LDB = CFG::LDB, LW = CFG::LW;
     constexpr int LINE_A = BM * ES, LINE_B = BN * ES;     // rows-contiguous form: bytes of one k
     constexpr int SLACK = ES == 2 ? 2 : 0;                            // the dword of an odd-length last row (see tail_element_in_last_page)
     __shared__ __attribute__((aligned(1024))) char lds[CFG::LDS_BYTES];
@@ -122,27 +129,29 @@ void k4_mfma_wide(Args a, int tiles_m, int tiles_n, int flags)
     typedef short v4s_t __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) v4s_t* tr_ptr;
     const int wrow_a = wm * (BM / 2), wrow_b = wn * (BN / 2);
-    auto fragment = [&](auto kc, auto line_, int region, int row, int i, int ks) __attribute__((always_inline)) -> u32x4_t {
+    auto fragment = [&](auto kc, auto line_, int region, int row, int i, int ks) __attribute__((always_inline)) -> Frag<IN> {
         constexpr int LINE = decltype(line_)::value;
-        u32x4_t f;
+        Frag<IN> f;
         if constexpr (decltype(kc)::value) {
-            f = *(const u32x4_t*)(lds + region + (row + lrow) * ROW_BYTES + (((4 * ks + lq) ^ swz(lrow)) << 4) + i * 16 * ROW_BYTES);
+#pragma unroll
+            for (int c = 0; c < CPS; ++c)
+                f.c[c] = *(const u32x4_t*)(lds + region + (row + lrow) * ROW_BYTES + (((CPS * (4 * ks + lq) + c) ^ swz(lrow)) << 4) + i * 16 * ROW_BYTES);
         } else {
             const int col = row + 16 * i + 4 * (lane & 3);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int off = region + (32 * ks + 8 * lq + 4 * h + kk) * LINE + (((col >> 3) ^ line_swz(8 * lq + kk)) << 4) + ((col >> 2) & 1) * 8;
                 const v4s_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(lds + off));
-                f[2 * h] = (uint32_t)(uint16_t)v[0] | ((uint32_t)(uint16_t)v[1] << 16);
-                f[2 * h + 1] = (uint32_t)(uint16_t)v[2] | ((uint32_t)(uint16_t)v[3] << 16);
+                f.c[0][2 * h] = (uint32_t)(uint16_t)v[0] | ((uint32_t)(uint16_t)v[1] << 16);
+                f.c[0][2 * h + 1] = (uint32_t)(uint16_t)v[2] | ((uint32_t)(uint16_t)v[3] << 16);
             }
         }
         return f;
     };
-    constexpr int NRD = TMI + TNI;
+    constexpr int NRD = (TMI + TNI) * CPS;
     using kc_a = std::integral_constant<bool, CFG::A_KC>;
     using kc_b = std::integral_constant<bool, CFG::B_KC>;
-    u32x4_t fa[2][TMI], fb[2][TNI];
+    Frag<IN> fa[2][TMI], fb[2][TNI];
     auto read = [&](int ra, int rb, int ks, int slot) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < TNI; ++j) fb[slot][j] = fragment(kc_b{}, std::integral_constant<int, LINE_B>{}, rb, wrow_b, j, ks);
@@ -234,22 +243,30 @@ void k4_mfma_wide(Args a, int tiles_m, int tiles_n, int flags)
     read(0, BASE_B, 0, 0);
     constexpr int PRE = 4;            // instructions of a slab's last k-step ahead of its barrier (0, 8 and 16 measured the same)
     int ra = 0, rb = BASE_B;
-    for (int s = 0; s < nslab; ++s) {
-        read(ra, rb, 1, 1);
-        mfmas(0, 0, NMF);
-        sched_kstep<NMF, NRD, 0>();
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(1, 0, PRE);
+    // one slab; with one k-step a slab its fragments are in slot `p`
+    auto slab = [&](auto parity, int s) __attribute__((always_inline)) {
+        constexpr int p = NK == 2 ? 1 : decltype(parity)::value;        // slot of the last k-step
+        if constexpr (NK == 2) {
+            read(ra, rb, 1, 1);
+            mfmas(0, 0, NMF);
+            sched_kstep<NMF, NRD, 0>();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        mfmas(p, 0, PRE);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         ra = ra == (SA - 1) * REGION_A ? 0 : ra + REGION_A;
         rb = rb == BASE_B + (SB - 1) * REGION_B ? BASE_B : rb + REGION_B;
-        if (s + 1 < nslab) read(ra, rb, 0, 0);
-        mfmas(1, PRE, NMF);
+        if (s + 1 < nslab) read(ra, rb, 0, NK == 2 ? 0 : p ^ 1);
+        mfmas(p, PRE, NMF);
         sched_kstep<NMF - PRE, NRD, 0>();
         __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int s = 0; s < nslab; ++s) {
+        slab(std::integral_constant<int, 0>{}, s);
+        if (NK == 1 && ++s < nslab) slab(std::integral_constant<int, 1>{}, s);
     }
 
     char* park = lds + wave_id * (32 * (BN / 2 * 4 + 16));
@@ -263,7 +280,7 @@ void k4_mfma_wide(Args a, int tiles_m, int tiles_n, int flags)
         else store_tiles_staged<OUT, false, TMI, TNI>(a, b, acc, row0, col0, lane, park, vec_ok);
     };
     if (CFG::ROT != 0 || a.out_dtype == GEMM_F32) store(std::integral_constant<int, GEMM_F32>{});      // (K ranges: partial sums)
-    else if constexpr (CFG::ROT == 0) store(std::integral_constant<int, IN::ID>{});
+    else if constexpr (CFG::ROT == 0) store(std::integral_constant<int, IN::BYTES == 1 ? GEMM_BF16 : IN::ID>{});
 }
 
 }  // namespace gl

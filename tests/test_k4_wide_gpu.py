@@ -102,3 +102,22 @@ def test_k_ranges_with_a_rotated_walk(dt, td, M, N, slabs):
         assert gemm.gemm_run_ex(K4, d, a8, b8, C) == gemm.GEMM_OK
         torch.cuda.synchronize()
         assert torch.equal(C[:, :N], A @ B.t() + bias) and bool((C[:, N:] == 7.0).all()) and bool((ws[need:] == 255).all())
+
+
+@pytest.mark.parametrize("M,N,slabs,batch", [(129, 300, 1, 3), (300, 257, 2, 2), (1000, 900, 3, 1), (97, 511, 5, 4), (500, 640, 6, 2), (1409, 1535, 7, 1), (200, 300, 9, 25), (130, 1030, 14, 13)])
+def test_e4m3_alternates_its_register_slots(M, N, slabs, batch):
+    """Odd and even numbers of slabs, fewer and more than the rings hold; a scale per problem (a power of two: exact)."""
+    K = 128 * slabs
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, B = (torch.randint(-3, 4, (batch, r, K), generator=gen, device="cuda").float() for r in (M, N))
+    a8, b8 = A.to(torch.float8_e4m3fn), B.to(torch.float8_e4m3fn)
+    scale = torch.tensor([2.0 ** (i % 3 - 1) for i in range(batch)], device="cuda")
+    for out, td in ((gemm.GEMM_F32, torch.float32), (gemm.GEMM_BF16, torch.bfloat16)):
+        C = torch.full((batch, M, N + 1), 7.0, device="cuda", dtype=td)
+        d = gemm.make_desc(M, N, K, gemm.GEMM_FP8_E4M3, out, ROW, COL, ldc=N + 1, batch=batch, stride_a=M * K, stride_b=N * K, stride_c=M * (N + 1), scale_b=scale)
+        q = gemm.gemm_query(K4, d, a8, b8, C)
+        assert (q.threads, q.bm, q.bn) == (512, 128, 128), q
+        assert gemm.gemm_run_ex(K4, d, a8, b8, C) == gemm.GEMM_OK
+        torch.cuda.synchronize()
+        for i in range(batch):
+            assert torch.equal(C[i, :, :N], ((A[i] @ B[i].t()) * scale[i]).to(td)) and bool((C[i, :, N:] == 7.0).all()), i
