@@ -375,12 +375,11 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
 }
 
 // ---- T1 on long rows ------------------------------------------------------------------------------
-// One workgroup of 1024 lanes per row (no scratch is lent, so rows are not split over workgroups), 16 bytes per lane and
-// load; what bounds it is what one CU can fetch.  The general form reads the row five times: three histogram passes and
-// two of ordered compaction.  The filter reads it twice (8 x 131072, k = 64: 256 lanes took 460 us, the general form 94,
-// this one 27.5, 23 since its
-// scans are short, 18.5 and 16 of them for k = 1, where the second read is one lane's; 128 x 200000, k = 100: 1426 -> 40) and
-// everything else works on few keys:
+// One workgroup of 1024 lanes per row (up to 32 rows are cut, below), 16 bytes per lane and load; what bounds it is what
+// one CU can fetch.  The general form reads the row five times: three histogram passes and two of ordered compaction.
+// The filter reads it twice (8 x 131072, k = 64, not cut: 256 lanes took 460 us, the general form 94, this one 27.5, 23
+// since its scans are short, 18.5 and 16 of them for k = 1, where the second read is one lane's; 128 x 200000, k = 100:
+// 1426 -> 40) and everything else works on few keys:
 //   1. each lane keeps the largest value of four interleaved groups of elements (4096 groups in all);
 //   2. the k-th largest of the 4096 maxima is a lower bound of the row's k-th largest value (k groups each hold an
 //      element at least that large): two 11-bit digits of it, the rest zero, are bound enough;
@@ -823,6 +822,7 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
             if (mine.x > (unsigned)p.room) too_many = 1;
         }
     }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                 // every wave's loads of the list have come (a barrier does not wait for them)
     __syncthreads();
     // (all of the slot has been read; while it is held nobody else changes it)
     if (held && tid == 0) {
