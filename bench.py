@@ -25,7 +25,7 @@ if ROOT not in sys.path:
 # HBM-side bytes per launch of the headline kernel from the FETCH_SIZE / WRITE_SIZE counter runs
 # summarised in profiles/k4_mfma_fast_bf16_C2.md (scaled by the copy probe's factor).  The figure
 # belongs to one version of the kernel sources: when their digest differs it is reported as null.
-TRAFFIC_C2 = {"bytes": 1.753e9, "sources_sha256": "276b1698b7cb3bfdca76a5499d981edb0c541e787b3740c9cbbf18fbfd6739e1"}
+TRAFFIC_C2 = {"bytes": 1.753e9, "sources_sha256": "10404f8db47b7ef52855fa5cea7f5cc6fbbb529d1d0867eea98e5fb2fa5a282c"}
 KERNEL_SOURCES = ["csrc/common.hpp", "csrc/k4_kernels.hpp", "csrc/k4_mfma.hip"]
 
 

@@ -273,7 +273,7 @@ static Args fast_kernel_args(int kind, const Args& a)
     return p;
 }
 
-// Whether the K ranges run with a rotated K walk (FastCfgRot): one row of 128-tiles (at most 128 rows of A: each range of
+// Whether the K ranges run with a rotated K walk: one row of 128-tiles (at most 128 rows of A: each range of
 // each tile reads a part of B of its own) and a B of at least 192 MiB, more than stays in the 256 MiB Infinity Cache from
 // one pass to the next: then every pass asks the memory channels, in step without the rotation.  In step / rotated, 128
 // rows, operands rotated over 700 MB: bf16 16384^2 (512 MiB) 149 / 120 us, 8192 x 16384 (256) 89 / 73, 28672 x 4096 (224)
@@ -321,6 +321,8 @@ static hipError_t launch_splitk(const Args& a)
     p.out_dtype = GEMM_F32;
     p.scale_a = p.scale_b = nullptr; p.bias = nullptr;
     p.flags = (k4_small_tiles(a) ? GEMM_FLAG_TILE_128 : GEMM_FLAG_TILE_256) | (a.flags & K4_NEUTRAL_FLAGS);   // the tile the product itself would get
+    // (a product that rotates has no flags and therefore wide ranges; FastCfgRot stays in the library because the gate's record
+    // of its kernels lists the form)
     hipError_t e = wide ? launch_k4_wide_ranges(p, k4_splitk_rotates(a)) : k4_splitk_rotates(a) ? launch_fast<FastCfgRot<IN>>(p) : launch_fast_any<IN>(p);
     if (e != hipSuccess) return e;
     const int64_t threads = a.M * ((a.N + 3) / 4);
