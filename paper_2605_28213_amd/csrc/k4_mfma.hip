@@ -273,17 +273,19 @@ static Args fast_kernel_args(int kind, const Args& a)
     return p;
 }
 
-// Whether the K ranges run with a rotated K walk: one row of 128-tiles (at most 128 rows of A: each range of
+// Whether the K ranges stream B: one row of 128-tiles (at most 128 rows of A: each range of
 // each tile reads a part of B of its own) and a B of at least 192 MiB, more than stays in the 256 MiB Infinity Cache from
-// one pass to the next: then every pass asks the memory channels, in step without the rotation.  In step / rotated, 128
+// one pass to the next: then every pass asks the memory channels, in step unless the K walk is rotated.  In step / rotated, 128
 // rows, operands rotated over 700 MB: bf16 16384^2 (512 MiB) 149 / 120 us, 8192 x 16384 (256) 89 / 73, 28672 x 4096 (224)
 // 80 / 71; e4m3 16384^2 (256) 88 / 77, 12288 x 16384 (192) 72 / 66; leading dimensions 64 or 128 elements longer 1.04 to
 // 0.74 of the time.  Below the line there is nothing to gain and something to lose: 8192^2 (128 MiB) 47 / 47 so, but 34 / 40
-// with the same B again; 2048 x 4096 (16) 16.1 / 16.7.
+// with the same B again; 2048 x 4096 (16) 16.1 / 16.7.  Ranges that fit one round of the chip as they are (few columns, a very
+// long K) keep the caches' order: with nt / without 4096 x 28672 (224) 63.2 / 64.9, 3584 x 28672 58.0 / 59.4, 3584 x 32768
+// 56.0 / 53.8.
 bool k4_splitk_rotates(const Args& a)
 {
     const Args p = fast_kernel_args(MFMA_SPLITK, a);
-    return p.flags == GEMM_FLAG_TILE_128 && a.M <= 128 && a.N * a.K * elem_size(a.in_dtype) >= (int64_t)192 << 20 && !k4_uses_ring(p) && !k4_small_tiles_deep(p);
+    return p.flags == GEMM_FLAG_TILE_128 && a.M <= 128 && a.N * a.K * elem_size(a.in_dtype) >= (int64_t)192 << 20 && ((a.N + 127) / 128) * p.batch > 256;
 }
 
 // The ranges on wide tiles with loading waves, whose K walk always starts at a slab of the tile's own, where they fit one
@@ -291,20 +293,36 @@ bool k4_splitk_rotates(const Args& a)
 // 19.8 / 16.4 us, 128 x 4096 x 16384 (fp16) 61.6 / 42.1, 128 x 16384 x 2048 27.6 / 23.0, 128 x 1024 x 16384 23.3 / 20.6,
 // 256 x 2048 x 8192 23.0 / 20.5, 300 x 300 x 8192 20.6 / 17.3, e4m3 128 x 4096 x 8192 21.7 / 20.1; the same operands again
 // 1.06 to 1.25.  More ranges than one round stay with k4_mfma_fast (110 x 8192^2, 512 of them, 47.6 / 47.0).
-// A B that streams from HBM (k4_splitk_rotates) is read past the caches' replacement, and neighbouring ranges are joined until
-// they fit one round, so that each of the 256 CUs keeps 64 KB of B in flight and half of the partial sums are written:
-// 128 x 16384 x 16384 in 4 ranges 115, in 2 joined pairs 119, with nt loads 105 (before: 121); e4m3 78.6 / 62.1;
-// 128 x 8192 x 16384 76.3 / 57.1, 128 x 28672 x 4096 72.3 / 59.1.  (B alone, read by 256 workgroups in this pattern: 85 us in
-// the caches' order, 78 us with nt.  On a B that stays in the Infinity Cache nt costs: 100 x 4096 x 4096 16.4 / 20.6.)
+// A B that streams from HBM (k4_splitk_rotates) is read past the caches' replacement, in as many ranges of whole slabs as fit
+// one round (at most the factor, for which scratch is lent), so that each CU keeps 64 KB of B in flight and few partial sums
+// are written: 128 x 16384 x 16384 in 4 ranges 115, in 2 119, with nt loads 105 (k4_mfma_fast, 4 rotated ranges: 121); e4m3
+// 78.6 / 62.1; 128 x 8192 x 16384 76.3 / 57.1, 128 x 28672 x 4096 (one range) 72.3 / 59.1.  (B alone, read by 256 workgroups in
+// this pattern: 85 us in the caches' order, 78 us with nt.  On a B that stays in the Infinity Cache nt costs: 100 x 4096 x 4096
+// 16.4 / 20.6.)  What divides the slabs counts, not what divides the factor: 16384 columns x 10240, factor 5, in one range
+// 116, in 2 75; 12800^2 (5) 131 / 80; 5120 x 20480 (8) in 4 80, in 5 72.
+// More rounds of more ranges (a workgroup's time goes with the slabs of its range) are taken where they come to less than three
+// quarters of the one round, or to four fifths of one that less than half of the CUs take part in (k4_mfma_fast, rotated / one
+// round / more): 7680 x 16000 83 / 2 ranges 88 / 5 in two rounds 83, 8192 x 13888 65 / 1 138 / 7 in two 66,
+// 12800 x 8000 59 / 1 86 / 5 in two 61, 8704 x 15232 75 / 2 88 / 7 in two 75, 14336 x 10240 107 / 1 114 / 5 in three 99, 16640 x
+// 7104 72 / 1 82 / 3 in two 70, 17408 x 12288 145 / 1 148 / 3 121, 20480 x 7104 83 / 1 85 / 3 82; on the other side 6400 x 17472
+// 70 / 3 69 / 7 in two 70, 12288 x 20480 154 / 2 149 / 5 in two 143, 16512 x 8192 102 / 1 94 / 4 in three 100, 10240 x 15232
+// 108 / 2 90 / 7 in three 99, 18432 x 8192 105 / 1 85 / 2 in two 98, 22016 x 7104 117 / 1 87 / 3 in three 107.
 int k4_splitk_wide(const Args& a)
 {
     const int splits = k4_splitk_factor(a);
-    const int64_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+    const int64_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128), nslab = a.K / (ROW_BYTES / elem_size(a.in_dtype));
     if (splits < 2 || a.flags != 0 || !k4_small_tiles(a)) return 0;
     if (!k4_splitk_rotates(a)) return tiles * splits <= 256 ? splits : 0;
-    int ranges = 1;
+    int one_round = 1;
     for (int r = 2; r <= splits; ++r)
-        if (splits % r == 0 && tiles * r <= 256) ranges = r;
+        if (nslab % r == 0 && tiles * r <= 256) one_round = r;
+    int ranges = one_round;
+    int64_t rounds = 1;
+    for (int r = one_round + 1; r <= splits; ++r) {
+        const int64_t n = (tiles * r + 255) / 256;
+        const bool shorter = tiles * one_round < 128 ? 5 * n * one_round <= 4 * r : 4 * n * one_round < 3 * r;
+        if (nslab % r == 0 && shorter && n * ranges < rounds * r) { ranges = r; rounds = n; }
+    }
     return ranges;
 }
 

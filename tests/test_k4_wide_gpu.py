@@ -104,6 +104,26 @@ def test_k_ranges_with_a_rotated_walk(dt, td, M, N, slabs):
         assert torch.equal(C[:, :N], A @ B.t() + bias) and bool((C[:, N:] == 7.0).all()) and bool((ws[need:] == 255).all())
 
 
+@pytest.mark.parametrize("dt,td", [(gemm.GEMM_F16, torch.float16), (gemm.GEMM_FP8_E4M3, torch.float8_e4m3fn)])
+@pytest.mark.parametrize("M,N,slabs,ranges", [(128, 22016, 72, 1), (97, 16380, 100, 2), (101, 10239, 161, 7), (128, 16513, 99, 3)])
+def test_k_ranges_of_a_streamed_operand(dt, td, M, N, slabs, ranges):
+    """A B of 192 MiB and more: one range, ranges that divide the slabs but not the factor, and more of them than one round; the
+    scratch past the partial sums stays as it was.  (bf16's loop is fp16's.)"""
+    K = slabs * (128 if dt == gemm.GEMM_FP8_E4M3 else 64)
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    A, B = (torch.randint(-3, 4, (r, K), generator=gen, device="cuda").to(td) for r in (M, N))
+    C = torch.full((M, N + 3), 7.0, device="cuda")
+    d = gemm.make_desc(M, N, K, dt, gemm.GEMM_F32, ROW, COL, ldc=N + 3)
+    need = gemm.gemm_query(K4, d, A, B, C).workspace_bytes
+    ws = torch.full((need + 256,), 255, dtype=torch.uint8, device="cuda")
+    d.workspace, d.workspace_bytes = ws.data_ptr(), need
+    q = gemm.gemm_query(K4, d, A, B, C)
+    assert "(rotated)" in q.path and q.grid == ranges * -(-N // 128) and need >= ranges * M * N * 4, q
+    assert gemm.gemm_run_ex(K4, d, A, B, C) == gemm.GEMM_OK
+    torch.cuda.synchronize()
+    assert torch.equal(C[:, :N], A.float() @ B.float().t()) and bool((C[:, N:] == 7.0).all()) and bool((ws[need:] == 255).all())
+
+
 @pytest.mark.parametrize("M,N,slabs,batch", [(129, 300, 1, 3), (300, 257, 2, 2), (1000, 900, 3, 1), (97, 511, 5, 4), (500, 640, 6, 2), (1409, 1535, 7, 1), (200, 300, 9, 25), (130, 1030, 14, 13)])
 def test_e4m3_alternates_its_register_slots(M, N, slabs, batch):
     """Odd and even numbers of slabs, fewer and more than the rings hold; a scale per problem (a power of two: exact)."""

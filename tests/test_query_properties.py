@@ -229,6 +229,22 @@ def test_which_k_ranges_run_with_a_rotated_walk():
         assert q.status == gemm.GEMM_OK and q.path == "mfma32-direct-to-lds" + path, (dt, M, N, K, q.path)
 
 
+def test_how_many_k_ranges_a_streamed_operand_is_read_in():
+    """Ranges of whole slabs, as many as fit one round of the 256 CUs; more of them in more rounds where one round leaves so many CUs
+    idle that it takes longer; never more than the factor that scratch is asked for.  (A count that divides the factor instead
+    leaves one range where the factor is prime.)"""
+    bf16, e4m3 = gemm.GEMM_BF16, gemm.GEMM_FP8_E4M3
+    for (dt, N, K, ranges) in [(bf16, 16384, 16384, 2), (bf16, 8192, 16384, 4), (bf16, 28672, 4096, 1), (bf16, 20480, 8192, 1), (bf16, 16512, 8192, 1),
+                               (bf16, 16384, 10240, 2), (bf16, 16384, 6400, 2), (bf16, 12800, 12800, 2), (bf16, 12288, 20480, 2), (e4m3, 16384, 20480, 2),
+                               (bf16, 5120, 20480, 5), (bf16, 5120, 27648, 6), (bf16, 8192, 13888, 7), (bf16, 12800, 8000, 5), (bf16, 8704, 15232, 7),
+                               (bf16, 16640, 7104, 3), (bf16, 17408, 12288, 3), (bf16, 20480, 7104, 3), (bf16, 22016, 7104, 1),
+                               (bf16, 6400, 17472, 3), (bf16, 10240, 15232, 2), (bf16, 9472, 13888, 7), (bf16, 14336, 9920, 5), (bf16, 7680, 16000, 5)]:
+        q = gemm.gemm_query(gemm.GEMM_K4_MFMA, gemm.make_desc(128, N, K, dt, gemm.GEMM_F32, ROW, COL, workspace=4096, workspace_bytes=1 << 40))
+        assert q.status == gemm.GEMM_OK and "(rotated)" in q.path and (q.threads, q.bm, q.bn) == (512, 128, 128), q
+        assert q.grid == ranges * (N // 128), (N, K, ranges, q)
+        assert q.workspace_bytes == int(q.path.split("splitK(")[1][0]) * 128 * N * 4 >= ranges * 128 * N * 4
+
+
 def _direct_form(M, N, K, dt, la, lb, A=4096, B=4096, **kw):
     out = gemm.GEMM_BF16 if dt == gemm.GEMM_FP8_E4M3 else dt
     q = gemm.gemm_query(gemm.GEMM_K4_MFMA, gemm.make_desc(M, N, K, dt, out, la, lb, **kw), A, B)
