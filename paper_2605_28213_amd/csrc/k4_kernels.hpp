@@ -418,7 +418,6 @@ struct FastCfg {
     using In = IN;
     static constexpr bool SWIZZLE = SWIZZLE_, OVERLAP = OVERLAP_, CONV = CONV_, MI16 = MI16_;
     static constexpr int PRE_BARRIER_MFMAS = PRE_;
-    static constexpr int ROT = 0;                        // K walk starts ROT slabs later from one tile to the next (FastCfgRot)
     static constexpr int BM = TILE_, BN = TILE_, WM = 2, WN = 2, GROUP_M = GROUP_M_;
     static constexpr int T = WM * WN * 64;
     static constexpr int TR = MI16_ ? 16 : 32;           // rows (and columns) of an accumulator tile
@@ -443,14 +442,6 @@ struct FastCfgDeep : FastCfg<IN, 128> {
     static constexpr int REGIONS = 2 * DEPTH + 1;
     static constexpr int LDS_BYTES = REGIONS * FastCfg<IN, 128>::REGION;
     static constexpr int WAVES_PER_SIMD = 1;
-};
-
-// 128-tiles whose K walk starts at a slab of the tile's own and wraps round (sums commute): where every workgroup reads
-// a strip of B that no other reads, all of them would otherwise ask at any moment for the same 128 bytes of every row,
-// a leading dimension apart, which for the leading dimensions of weights (powers of two) lie in few memory channels.
-template <typename IN>
-struct FastCfgRot : FastCfg<IN, 128> {
-    static constexpr int ROT = 19;
 };
 
 template <int N>
@@ -557,13 +548,6 @@ void k4_mfma_fast(Args a, int tiles_m, int tiles_n, int flags)
             conv_base[n] = (((img * g.H + h0) * g.W + conv_w[n]) * g.C + gchunk * V) * IN::BYTES;
         }
     }
-    // the slab whose bytes stand for slab s of the walk (s < 2 x slabs per K)
-    const int kslabs = (int)(a.K / KE), rot = CFG::ROT && kslabs > 0 ? (int)((unsigned)(tm * tiles_n + tn) * CFG::ROT % (unsigned)kslabs) : 0;
-    auto k_of = [&](int64_t s) __attribute__((always_inline)) -> int {
-        if constexpr (CFG::ROT == 0) return (int)(s * ROW_BYTES);
-        const int r = (int)s + rot;
-        return (r >= kslabs ? r - kslabs : r) * ROW_BYTES;
-    };
     // loads [lo, hi) of this wave's share of operand slab s into region `reg`
     auto issue_a = [&](int64_t s, char* reg, int lo, int hi) __attribute__((always_inline)) {
         if constexpr (CFG::CONV) {
@@ -579,14 +563,14 @@ void k4_mfma_fast(Args a, int tiles_m, int tiles_n, int flags)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lptr)(reg + (wave + n * NW) * 1024), 16, voff, 0, 0, 0);
             }
         } else {
-            const int k0 = k_of(s);
+            const int k0 = (int)(s * ROW_BYTES);
 #pragma unroll
             for (int n = lo; n < hi; ++n)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lptr)(reg + (wave + n * NW) * 1024), 16, voff_a, k0 + (wave + n * NW) * oct_a, 0, 0);
         }
     };
     auto issue_b = [&](int64_t s, char* reg, int lo, int hi) __attribute__((always_inline)) {
-        const int k0 = k_of(s);
+        const int k0 = (int)(s * ROW_BYTES);
 #pragma unroll
         for (int n = lo; n < hi; ++n)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, (lptr)(reg + (wave + n * NW) * 1024), 16, voff_b, k0 + (wave + n * NW) * oct_b, 0, 0);

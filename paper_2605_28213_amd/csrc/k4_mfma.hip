@@ -339,9 +339,7 @@ static hipError_t launch_splitk(const Args& a)
     p.out_dtype = GEMM_F32;
     p.scale_a = p.scale_b = nullptr; p.bias = nullptr;
     p.flags = (k4_small_tiles(a) ? GEMM_FLAG_TILE_128 : GEMM_FLAG_TILE_256) | (a.flags & K4_NEUTRAL_FLAGS);   // the tile the product itself would get
-    // (a product that rotates has no flags and therefore wide ranges; FastCfgRot stays in the library because the gate's record
-    // of its kernels lists the form)
-    hipError_t e = wide ? launch_k4_wide_ranges(p, k4_splitk_rotates(a)) : k4_splitk_rotates(a) ? launch_fast<FastCfgRot<IN>>(p) : launch_fast_any<IN>(p);
+    hipError_t e = wide ? launch_k4_wide_ranges(p, k4_splitk_rotates(a)) : launch_fast_any<IN>(p);
     if (e != hipSuccess) return e;
     const int64_t threads = a.M * ((a.N + 3) / 4);
     hipLaunchKernelGGL(k4_splitk_reduce<IN>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, a.stream, a, (const float*)a.workspace, splits);

@@ -23,8 +23,10 @@ namespace gl {
 
 // 256 x 128: three slabs of both operands (144 KB), every loading wave loads both.  128 x 128: five slabs (160 KB); with K
 // contiguous in both operands two waves load four slabs of A and two load five of B (nine regions, 144 KB).
-// ROT, NT: K ranges of a thin product (see k4_splitk_wide): the K walk starts ROT slabs later from one tile to the next, and B,
-// which nobody reads twice, is loaded past the caches' replacement (nt) so that A stays in the L2s.
+// ROT, NT: K ranges of a thin product (see k4_splitk_wide): the K walk starts ROT slabs later from one tile to the next and wraps
+// round (sums commute), since workgroups that each read a strip of B of their own would otherwise ask at any moment for the same
+// 128 bytes of every row, a leading dimension apart, which for those of weights (powers of two) lie in few memory channels; and
+// B, which nobody reads twice, is loaded past the caches' replacement (nt) so that A stays in the L2s.
 //
 // e4m3 (K contiguous and aligned, 128-tiles): v_mfma_scale_f32_16x16x128 with unit scales takes a slab in one k-step, two
 // chunks per lane; fragments then alternate between two register slots from slab to slab.

@@ -86,7 +86,13 @@ def test_every_state_and_path_maps_to_kernels_of_the_library():
              (4, gen.F16, "mfma32-packed+direct-to-lds+stream(M-tail)", 256, 256, 256, 0),
              (4, gen.F16, "mfma32-direct-to-lds(persistent,B-row-major)+thin(M-tail)", 256, 256, 256, 0),
              (4, gen.BF16, "mfma16-thin(B-row-major)", 32, 64, 512, 0),
-             (4, gen.BF16, "mfma32-direct-to-lds+splitK(4)", 128, 128, 256, 0), (4, gen.E4M3, "mfma32-direct-to-lds+splitK(4)(rotated)", 128, 128, 256, 0), (4, gen.BF16, "mfma16-stream(small-M)", 16, 16, 64, 0),
+             (4, gen.BF16, "mfma32-direct-to-lds+splitK(4)", 128, 128, 256, 0), (4, gen.BF16, "mfma16-stream(small-M)", 16, 16, 64, 0),
+             # wide tiles with loading waves: whole products, K ranges, a streamed B; the masked state's, and its round of 256-tiles
+             (4, gen.BF16, "mfma32-direct-to-lds", 128, 128, 512, 0), (4, gen.F16, "mfma32-direct-to-lds", 256, 128, 512, 0),
+             (4, gen.F16, "mfma32-direct-to-lds+splitK(4)", 128, 128, 512, 0), (4, gen.E4M3, "mfma32-direct-to-lds+splitK(4)(rotated)", 128, 128, 512, 0),
+             (4, gen.BF16, "mfma32-vec16(A)+elementwise-masked(B)(direct-to-lds)", 256, 128, 512, 0),
+             (4, gen.F16, "mfma32-elementwise-masked(direct-to-lds)", 256, 256, 256, 0),
+             (4, gen.BF16, "mfma32-direct-to-lds(few-tiles)", 64, 64, 256, 0),
              (4, gen.F32, "mfma32-elementwise-masked", 64, 64, 256, 0), (4, gen.F16, "mfma32-vec16-masked", 128, 128, 256, 0),
              (4, gen.F32, "mfma32-elementwise-masked(direct-to-lds)", 64, 64, 256, 0), (4, gen.BF16, "mfma32-vec16(A)+elementwise-masked(B)(direct-to-lds)", 128, 128, 256, 0),
              (4, gen.F16, "mfma32-direct-to-lds(few-tiles)", 128, 128, 256, 0)]
@@ -99,8 +105,10 @@ def test_every_state_and_path_maps_to_kernels_of_the_library():
         for p in pats:
             assert any(__import__("re").search(p, k) for k in found), (p, path)
         # the forms of one state have patterns of their own
-        assert any("k4_mfma_direct<" in k for k in found) == path.endswith(("(direct-to-lds)", "(few-tiles)"))
-        assert any("FastCfgRot<" in k for k in found) == ("rotated" in path) and any("k4_mfma_masked<" in k for k in found) == path.endswith("-masked")
+        assert any("k4_mfma_wide<" in k for k in found) == (path.startswith("mfma32") and threads == 512)
+        assert any("k4_mfma_direct<" in k for k in found) == (path.endswith(("(direct-to-lds)", "(few-tiles)")) and threads == 256 and bm < 256)
+        # (19: the step of the rotated walk, then whether B is streamed)
+        assert any(", 19, true>" in k for k in found if "k4_mfma_wide<" in k) == ("rotated" in path) and any("k4_mfma_masked<" in k for k in found) == path.endswith("-masked")
 
 
 def test_counter_files_are_read_per_launch_and_calibrated(tmp_path):
