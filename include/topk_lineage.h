@@ -65,8 +65,9 @@ typedef struct {
     uint32_t required, violated, holds; /* TOPK_COND_* */
     int32_t  threads;                   /* workgroup size; one workgroup per row, or per part of a row that T1 cuts */
     int32_t  passes;                    /* passes over the row's keys (histogram passes + compaction; k rounds for T0);
-                                         * with T1's filter the 2, with its parts the 1, of a row whose candidates they hold: rows
-                                         * of equal values, which the query cannot know of, take up to 8 */
+                                         * with T1's filter the 2, with its parts the 1, of a row whose candidates they hold, which the
+                                         * query cannot know of: rows with many equal values about the k-th largest (in parts: more
+                                         * than a part has room for, and k beyond what each part lists) take up to 8 */
     int32_t  lds_bytes;
     int64_t  grid;
     char     path[64];

@@ -207,6 +207,29 @@ __device__ __forceinline__ void pick_digit(const int* hist, int nb, int remainin
     __syncthreads();
 }
 
+// Adds a lane's elements to a histogram: at once for the wave where all that count fall into one bin (additions to one word of
+// LDS wait for each other: 4096 of them take 4 us).  All lanes of the wave take part.
+template <int N>
+__device__ __forceinline__ void count_bins(int* hist, const uint32_t (&bin)[N], const bool (&on)[N])
+{
+    const uint32_t first = __builtin_amdgcn_readfirstlane(bin[0]);
+    bool same = !on[0] || bin[0] == first;
+    if (__all(same)) {                                      // (mostly not: the other elements are not looked at)
+#pragma unroll
+        for (int e = 1; e < N; ++e) same = same && (!on[e] || bin[e] == first);
+        if (__all(same)) {
+            int n = 0;
+#pragma unroll
+            for (int e = 0; e < N; ++e) n += __popcll(__ballot(on[e]));
+            if ((threadIdx.x & 63) == 0 && n > 0) atomicAdd(&hist[first], n);
+            return;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e)
+        if (on[e]) atomicAdd(&hist[bin[e]], 1);
+}
+
 // The keys that share the k-th largest one's first digit, listed in LDS: once they are few, one wave finishes, six bits a
 // step, in a histogram of one bin per lane, while the others wait at one barrier; it stops as soon as all that are left are
 // taken.  Taken are the keys above `thr` and the first `equal` of those that equal it.
@@ -564,10 +587,9 @@ __device__ void long_row_general(const TopkArgs& a, const float* row, LongShared
     }
 }
 
-// The k largest of the `listed` elements in LDS, in index order.  Elements below the key `bound` may be missing from the list:
-// false, and nothing written, when one of the k lies below it.
+// The k largest of the `listed` elements in LDS, in index order: those that `cut` takes, where it is known.
 constexpr int SHORT_K = LONG_T / 4;
-__device__ bool finish_list(const TopkArgs& a, LongShared& sh, int listed, uint32_t bound)
+__device__ void finish_list(const TopkArgs& a, LongShared& sh, int listed, bool known, Cut cut)
 {
     const int tid = threadIdx.x;
     uint32_t key[LONG_CAP / LONG_T];
@@ -579,11 +601,9 @@ __device__ bool finish_list(const TopkArgs& a, LongShared& sh, int listed, uint3
         key[j] = c < listed ? key_of(__uint_as_float(sh.bits[c])) : 0;
         pos[j] = c < listed ? sh.idx[c] : 0;
     }
-    const Cut cut = select_cut(sh, key, listed, (int)a.k);
+    if (!known) cut = select_cut(sh, key, listed, (int)a.k);
     const uint32_t thr = cut.thr;
     const int remaining = cut.equal;
-    // the smallest key taken is `thr`, or above it where none of those that equal it is taken
-    if ((remaining > 0 ? thr : thr + 1) < bound) return false;
     int32_t* idx = a.idx + (int64_t)blockIdx.x * a.k;
     float* val = a.val + (int64_t)blockIdx.x * a.k;
     // counting sort by index: 2048 buckets of consecutive indices, then the rank among the bucket's few elements
@@ -638,7 +658,6 @@ __device__ bool finish_list(const TopkArgs& a, LongShared& sh, int listed, uint3
         g += key[j] > thr;
         e += key[j] == thr;
     }
-    return true;
 }
 
 // k <= LONG_MAX_K; false (nothing written) when the list does not hold the row's candidates
@@ -682,7 +701,7 @@ __device__ bool long_row_filtered(const TopkArgs& a, const float* row, LongShare
     __syncthreads();
     const int listed = sh.listed;
     if (listed > LONG_CAP || listed < a.k) return false;            // fewer than k only where NaNs hid a group's elements
-    finish_list(a, sh, listed, 0);
+    finish_list(a, sh, listed, false, Cut{});
     return true;
 }
 
@@ -699,28 +718,33 @@ __global__ __launch_bounds__(LONG_T) void topk_long(TopkArgs a)
 
 // ---- T1 on few long rows ---------------------------------------------------------------------------
 // One workgroup reads a row no faster than one CU can fetch, and most CUs have no row.  Here a row is cut into parts of 4096
-// elements (blocks of 256 in turn, so that a run of large values is shared out), a workgroup each: it keeps its elements in
-// registers, finds its own `want`-th largest and lists its elements from there up.  A second kernel, one workgroup per row,
-// finds the k largest of the lists.  Its result is checked, not assumed: what a part has not listed lies below that part's
-// bound, so the result holds if all k lie at or above the largest bound; for k <= want they always do, for more only where the
-// row's large values are spread out.  A row for which it does not hold, or one of whose parts has more elements equal to its
-// bound than there is room for, is read again by the one workgroup as if it had not been cut.
+// elements (blocks of 256 in turn, of 32 where a run of large values has to be shared out), a workgroup each: it keeps its elements in
+// registers, finds its own `want`-th largest, digit by digit until few keys share what has been found, and lists its elements
+// from there up; of those that equal it, if there are more than there is room for, the first.  A second kernel, one
+// workgroup per row, finds the k largest of the lists.  For k <= want they are the row's: each part has listed its `want`
+// largest, the first of equal ones first.  For more the result is checked, not assumed: what a part has not listed lies below
+// its bound (or, where equal ones were left out, not above it), so the result holds if all k lie at or above the largest bound.
+// A row for which it does not hold is read again by the one workgroup as if it had not been cut.
+// 8 x 131072, k = 64, uncut / cut: normal values 26.8 / 15.2 us, uniform ones 29.2 / 15.5, normal around -10 27.2 / 15.2, rounded to
+// bf16 26.9 / 18.7, to halves 29.2 / 21.1, one value 392 / 49, sorted 25.8 / 18.0; k = 500, more than `want`: one value 392 / 393,
+// sorted 26.0 / 23.7.  (With the part's bound no finer than the first digit where more than 512 keys share it, and equal
+// elements beyond the room sent to the uncut form, uniform values took 36 and one value 400.)
 //
 // The lists are device memory of the loaded library (one copy per GPU, held until the process ends), because the interface
 // lends no scratch.  A call's rows take consecutive slots from a ticket; the first part to arrive claims the row's slot for the
 // address of the row's output, which no other call that runs at the same time can share, later parts join it, and the second
 // kernel gives it back.  A part that finds its slot held by another call's row (more than PART_SLOTS rows in flight on several
 // streams) leaves: the second kernel then sees that not all parts came, and reads the row itself.  Nothing waits for anything.
-constexpr int PART_N = 4 * LONG_T, PART_BLOCK = 256;
+constexpr int PART_N = 4 * LONG_T;
 constexpr int PART_SLOTS = 128, PART_LIST = LONG_CAP, PART_MAX = 64;       // rows, elements listed per row, parts per row
 struct PartSlot {
     unsigned long long owner;           // address of the row's indices, 0: free
     unsigned int arrived;
-    uint2 part[PART_MAX];               // elements listed (more than there is room for: ~0) and bound of each part
+    uint2 part[PART_MAX];               // elements from the bound up (as many are listed as there is room for) and bound of each part
     uint2 list[PART_LIST];              // pattern and index; part i's begin at i * room
 };
 __device__ PartSlot part_slots[PART_SLOTS];
-struct PartArgs { int parts, room, want; unsigned int room_inverse, first_slot; };     // room_inverse: 2^32 / room, rounded up
+struct PartArgs { int parts, room, want, lanes; unsigned int room_inverse, first_slot; };     // room_inverse: 2^32 / room, rounded up
 
 __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
 {
@@ -733,8 +757,8 @@ __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
     const int tid = threadIdx.x, row_no = (int)blockIdx.x / p.parts, part = (int)blockIdx.x % p.parts;
     const float* row = a.x + (int64_t)row_no * a.ld;
     PartSlot& slot = part_slots[(p.first_slot + (unsigned)row_no) % PART_SLOTS];
-    // a wave's block of 256 elements, four per lane
-    const int first = ((tid >> 6) * p.parts + part) * PART_BLOCK + 4 * (tid & 63);      // (PART_MAX parts: below 2^18)
+    // blocks of 4 << p.lanes elements, four per lane
+    const int first = (((tid >> p.lanes) * p.parts + part) << (p.lanes + 2)) + 4 * (tid & ((1 << p.lanes) - 1));      // (PART_MAX parts: below 2^18)
     const int there = first >= a.n ? 0 : first + 4 <= a.n ? 4 : (int)a.n - first;
     float4_u held = {0, 0, 0, 0};
     if (there == 4) held = *(const float4_u*)(row + first);
@@ -760,35 +784,64 @@ __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
     pick_digit<LONG_T>(hist, 2048, p.want, wsum[0], &found);
     // the elements of the digit found and of those above it, where there is room for them; else from the want-th largest up
     uint32_t bound = (uint32_t)found.digit << 21;         // (fewer than `want` elements: 0, all of them are listed)
-    const int count = found.count, at_least = p.want - found.left + count;
-    if (at_least > p.room && count <= FEW_KEYS) {
+    int shift = 21, left = found.left, count = found.count;
+    while (shift > 0 && p.want - left + count > p.room && count > FEW_KEYS) {       // 11 bits more, then the last 10
+        const int low = shift > 11 ? shift - 11 : 0, bits = shift - low;
+        hist[tid] = hist[LONG_T + tid] = 0;
+        __syncthreads();
+        uint32_t bin[4];
+        bool on[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            bin[e] = (key[e] >> low) & ((1u << bits) - 1);
+            on[e] = e < there && key[e] >> shift == bound >> shift;
+        }
+        count_bins(hist, bin, on);
+        __syncthreads();
+        pick_digit<LONG_T>(hist, 1 << bits, left, wsum[0], &found);
+        bound |= (uint32_t)found.digit << low;
+        left = found.left;
+        count = found.count;
+        shift = low;
+    }
+    if (shift > 0 && p.want - left + count > p.room) {
         int in_digit = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) in_digit += e < there && key[e] >> 21 == bound >> 21;
+        for (int e = 0; e < 4; ++e) in_digit += e < there && key[e] >> shift == bound >> shift;
         int at = take_places(in_digit, &listed);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (e < there && key[e] >> 21 == bound >> 21) few[at++] = key[e];
+            if (e < there && key[e] >> shift == bound >> shift) few[at++] = key[e];
         __syncthreads();
         if (tid < 64) {
-            const Cut c = cut_of_listed(few, bins, count, found.left, bound, 21);
+            const Cut c = cut_of_listed(few, bins, count, left, bound, shift);
             if (tid == 0) cut = c;
         }
         __syncthreads();
         bound = cut.equal > 0 ? cut.thr : cut.thr + 1;
     }
-    int n = 0, total;
+    // (more than there is room for only where `bound` is the want-th largest key itself)
+    int gt = 0, eq = 0, totals;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) n += e < there && key[e] >= bound;
-    int at = join_scan<LONG_T>(wave_scan(n), wsum[1], &total) - n;
-    if (total <= p.room && n > 0) {
+    for (int e = 0; e < 4; ++e) {
+        gt += e < there && key[e] > bound;
+        eq += e < there && key[e] == bound;
+    }
+    const int before = join_scan<LONG_T>(wave_scan(gt | (eq << 16)), wsum[1], &totals) - (gt | (eq << 16));
+    const int above = totals & 0xFFFF, equal = totals >> 16, keep = p.room - above;
+    if (gt + eq > 0) {
         uint2* list = slot.list + part * p.room;
+        int g = before & 0xFFFF, e0 = before >> 16;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (e < there && key[e] >= bound) list[at++] = make_uint2(__float_as_uint(held[e]), (uint32_t)(first + e));
+        for (int e = 0; e < 4; ++e) {
+            const bool is_gt = e < there && key[e] > bound, is_eq = e < there && key[e] == bound;
+            if (is_gt || (is_eq && e0 < keep)) list[g + (e0 < keep ? e0 : keep)] = make_uint2(__float_as_uint(held[e]), (uint32_t)(first + e));
+            g += is_gt;
+            e0 += is_eq;
+        }
     }
     if (tid == 0) {
-        slot.part[part] = make_uint2(total <= p.room ? (unsigned)total : ~0u, bound);
+        slot.part[part] = make_uint2((unsigned)(above + equal), bound);
         __hip_atomic_fetch_add(&slot.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -798,7 +851,7 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
     constexpr int ITEMS = PART_LIST / LONG_T;
     __shared__ LongShared sh;
     __shared__ uint2 part[PART_MAX];
-    __shared__ unsigned int lowest, largest_bound, highest, too_many;
+    __shared__ unsigned int lowest, largest_bound, highest, tied;
     const int tid = threadIdx.x;
     const float* row = a.x + (int64_t)blockIdx.x * a.ld;
     PartSlot& slot = part_slots[(p.first_slot + blockIdx.x) % PART_SLOTS];
@@ -810,16 +863,18 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
     uint2 entry[ITEMS];
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) entry[j] = slot.list[j * LONG_T + tid];
-    if (tid == 0) { sh.found = Digit{0, 0, 0}; sh.listed = sh.few = 0; lowest = ~0u; largest_bound = highest = 0; too_many = 0; }
+    if (tid == 0) { sh.found = Digit{0, 0, 0}; sh.listed = sh.few = 0; lowest = ~0u; largest_bound = highest = tied = 0; }
     sh.hist[tid] = sh.hist[LONG_T + tid] = 0;
     __syncthreads();
     const bool held = owner == tag;
+    // from which key up a part's list holds all that the k largest may be
+    auto left_out = [&](uint2 of) { return of.x > (unsigned)p.room && a.k > p.want; };
+    auto complete_from = [&](uint2 of) { return a.k <= p.want ? 0u : left_out(of) ? of.y + 1 : of.y; };
     if (tid < PART_MAX) {
         part[tid] = mine;
         if (held && tid < p.parts) {
             atomicMin(&lowest, mine.y);
-            atomicMax(&largest_bound, mine.y);
-            if (mine.x > (unsigned)p.room) too_many = 1;
+            atomicMax(&largest_bound, complete_from(mine));
         }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                 // every wave's loads of the list have come (a barrier does not wait for them)
@@ -829,102 +884,106 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
         __hip_atomic_store(&slot.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&slot.owner, 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (held && arrived == (unsigned)p.parts && !too_many) {
+    if (held && arrived == (unsigned)p.parts) {
         bool there[ITEMS];
         uint32_t key[ITEMS], top = 0;
-        int n = 0, listed;
+        int sure = 0, all_sure = (int)a.k;
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
             const unsigned i = j * LONG_T + tid, of = __umulhi(i, p.room_inverse);
             there[j] = of < (unsigned)p.parts && i - of * p.room < part[of < PART_MAX ? of : 0].x;
             key[j] = key_of(__uint_as_float(entry[j].x));
-            n += there[j];
+            sure += there[j] && key[j] >= largest_bound;
             if (there[j] && key[j] > top) top = key[j];
         }
         top = wave_max(top);
         if ((tid & 63) == 63) atomicMax(&highest, top);
-        int at = join_scan<LONG_T>(wave_scan(n), sh.wsum, &listed) - n;
-        if (listed >= a.k && a.k <= SHORT_K) {
+        if (a.k > p.want) join_scan<LONG_T>(wave_scan(sure), sh.wsum, &all_sure);
+        else __syncthreads();
+        if (all_sure >= a.k) {
             // The keys lie between the lowest bound and the highest key: 2047 bins over that range (a few bins of the key's
             // top bits would hold nearly all of them, and additions to one bin wait for each other).
             const uint32_t range = highest - lowest;
             int shift = range < 2048 ? 0 : 21 - __clz(range);                   // range >> shift: 1024 .. 2047
             if (range >> shift > 2046) ++shift;
             auto place_of = [&](uint32_t k) { return k - lowest + (1u << shift); };       // (bins from 1: see cut_of_listed on 0)
+            uint32_t bin[ITEMS];
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j) bin[j] = place_of(key[j]) >> shift;
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j)
-                if (there[j]) atomicAdd(&sh.hist[place_of(key[j]) >> shift], 1);
+                if (there[j]) atomicAdd(&sh.hist[bin[j]], 1);
             __syncthreads();
             pick_digit<LONG_T>(sh.hist, 2048, (int)a.k, sh.wsum, &sh.found);
             const uint32_t digit = sh.found.digit;
             const int count = sh.found.count;
             Cut c = {digit << shift, sh.found.left};
+            const bool known = count <= FEW_KEYS || shift == 0;
             if (count <= FEW_KEYS) {
                 int in_digit = 0;
 #pragma unroll
-                for (int j = 0; j < ITEMS; ++j) in_digit += there[j] && place_of(key[j]) >> shift == digit;
+                for (int j = 0; j < ITEMS; ++j) in_digit += there[j] && bin[j] == digit;
                 int to = take_places(in_digit, &sh.few);
 #pragma unroll
                 for (int j = 0; j < ITEMS; ++j)
-                    if (there[j] && place_of(key[j]) >> shift == digit) sh.few_keys[to++] = place_of(key[j]);
+                    if (there[j] && bin[j] == digit) sh.few_keys[to++] = place_of(key[j]);
                 __syncthreads();
                 if (tid < 64) {
                     const Cut w = cut_of_listed(sh.few_keys, sh.bins, count, sh.found.left, digit << shift, shift);
-                    if (tid == 0) { sh.cut = w; sh.few = 0; }
+                    if (tid == 0) sh.cut = w;
                 }
                 __syncthreads();
                 c = sh.cut;
-                // a clean cut: the k keys above c.thr are taken, and their order by index is each one's rank among them
-                if (c.equal == 0 && c.thr + 1 + lowest - (1u << shift) >= largest_bound) {
-                    int taken = 0;
+            }
+            // those that may be taken: the k keys above c.thr where the cut is a clean one, and what equals it (or shares its bin,
+            // many as they are) where not
+            const bool clean = known && c.equal == 0;
+            int taken = 0;
 #pragma unroll
-                    for (int j = 0; j < ITEMS; ++j) taken += there[j] && place_of(key[j]) > c.thr;
-                    int to = take_places(taken, &sh.few);
+            for (int j = 0; j < ITEMS; ++j) taken += there[j] && place_of(key[j]) + (clean ? 0 : 1) > c.thr;
+            int to = take_places(taken, &sh.listed);
 #pragma unroll
-                    for (int j = 0; j < ITEMS; ++j)
-                        if (there[j] && place_of(key[j]) > c.thr && to < SHORT_K) {
-                            sh.bits[to] = entry[j].x;
-                            sh.idx[to++] = (int32_t)entry[j].y;
-                        }
-                    __syncthreads();
-                    const int k = (int)a.k, q = tid >> 2;           // four lanes for one
-                    if (q < k) {
-                        const int32_t index = sh.idx[q];
-                        int rank = 0;
-                        for (int i = tid & 3; i < k; i += 4) rank += sh.idx[i] < index;
-                        rank += __shfl_xor(rank, 1, 64);
-                        rank += __shfl_xor(rank, 2, 64);
-                        if ((tid & 3) == 0) {
-                            a.idx[(int64_t)blockIdx.x * a.k + rank] = index;
-                            a.val[(int64_t)blockIdx.x * a.k + rank] = __uint_as_float(sh.bits[q]);
-                        }
-                    }
-                    return;
+            for (int j = 0; j < ITEMS; ++j)
+                if (there[j] && place_of(key[j]) + (clean ? 0 : 1) > c.thr) {
+                    sh.bits[to] = entry[j].x;
+                    sh.idx[to++] = (int32_t)entry[j].y;
                 }
-            }
             __syncthreads();
-        }
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j)
-            if (there[j]) {
-                sh.bits[at] = entry[j].x;
-                sh.idx[at++] = (int32_t)entry[j].y;
+            const int k = (int)a.k, q = tid >> 2;           // four lanes for one
+            if (clean && k <= SHORT_K) {
+                // their order by index is each one's rank among them
+                if (q < k) {
+                    const int32_t index = sh.idx[q];
+                    int rank = 0;
+                    for (int i = tid & 3; i < k; i += 4) rank += sh.idx[i] < index;
+                    rank += __shfl_xor(rank, 1, 64);
+                    rank += __shfl_xor(rank, 2, 64);
+                    if ((tid & 3) == 0) {
+                        a.idx[(int64_t)blockIdx.x * a.k + rank] = index;
+                        a.val[(int64_t)blockIdx.x * a.k + rank] = __uint_as_float(sh.bits[q]);
+                    }
+                }
+                return;
             }
-        __syncthreads();
-        if (listed >= a.k && finish_list(a, sh, listed, largest_bound)) return;
-        __syncthreads();
-        if (tid == 0) { sh.found = Digit{0, 0, 0}; sh.listed = 0; }
+            // (the cut as a key again; a clean one's lies above the key 0, which no number has)
+            const uint32_t from = (clean ? c.thr + 1 : c.thr) + lowest - (1u << shift);
+            finish_list(a, sh, sh.listed, known, Cut{clean ? (from > 0 ? from - 1 : 0) : from, c.equal});
+            return;
+        }
+        // the row's k-th largest lies below the largest bound: where more elements than the filter can list lie there, it is not tried
+        if (tid < p.parts && left_out(mine) && complete_from(mine) == largest_bound) atomicAdd(&tied, mine.x);
         __syncthreads();
     }
-    if (long_row_takes_filter(a.n, a.k) && long_row_filtered(a, row, sh)) return;
+    if (tied <= LONG_CAP && long_row_takes_filter(a.n, a.k) && long_row_filtered(a, row, sh)) return;
     long_row_general(a, row, sh);
 }
 
 // Which rows are cut: up to 32 of them (beyond, one workgroup per row has enough CUs: uncut / cut, k = 16, 64 x 32768 16.1 /
 // 16.0 us, 64 x 131072 26.4 / 32.6, 128 x 131072 29.1 / 52.0), longer than the resident state takes.  Uncut / cut: 1 x 17000,
-// k = 16, 14.1 / 10.5; 24 x 24000, k = 200, 21.3 / 14.6; 8 x 131072, k = 64, 26.6 / 14.9; 1 x 200000, k = 16, 27.2 / 13.5; 24 x
-// 200000, k = 16, 34.1 / 25.1.  More than SHORT_K elements take the slower end of the second kernel, which pays on longer rows:
-// k = 500, 8 x 17000 18.0 / 18.1, 8 x 32768 21.4 / 20.0, 8 x 50000 27.0 / 20.9; k = 1500, 1 x 131072 48.0 / 23.8.
+// k = 16, 14.8 / 10.4; 24 x 24000, k = 200, 21.8 / 14.8; 8 x 131072, k = 64, 26.9 / 15.2; 1 x 200000, k = 16, 27.3 / 14.1; 24 x
+// 200000, k = 16, 34.4 / 25.7.  More than SHORT_K elements are put in order by finish_list: their line lies where cutting paid
+// when that sorted the whole list (k = 500, 8 x 32768 21.4 / 20.0, 8 x 50000 27.0 / 20.9, now 27.2 / 15.0; 1 x 131072, k = 1500, 48.1 /
+// 17.1); with a list of candidates only it would pay from PART_FROM_N on (k = 500, 8 x 17000 15.6 / 13.8, 8 x 32768 18.9 / 14.5).
 constexpr int64_t PART_FROM_N = 16384, PART_FROM_N_MANY = 49152, PART_ROWS = 32;
 PartArgs parts_of(int64_t batch, int64_t n, int64_t k)
 {
@@ -934,7 +993,10 @@ PartArgs parts_of(int64_t batch, int64_t n, int64_t k)
     // of k elements spread at random a part holds more than this once in a million
     const double mean = (double)k / (double)parts;
     if (k > want && mean + 5 * __builtin_sqrt(mean) + 8 > want) return PartArgs{};
-    return PartArgs{(int)parts, room, want, (unsigned)((((uint64_t)1 << 32) + room - 1) / room), 0};
+    // blocks of 256 elements are read a little faster (32 x 50000, k = 100, 16.4 us against 16.7 with blocks of 32, a line of 128
+    // bytes); with 32, at most `want` of k neighbours lie in one part: 32 times (k + 62) / 32 / parts, rounded up, for every k
+    // that gets here
+    return PartArgs{(int)parts, room, want, k <= want ? 6 : 3, (unsigned)((((uint64_t)1 << 32) + room - 1) / room), 0};
 }
 std::atomic<unsigned> part_ticket{0};
 

@@ -60,6 +60,29 @@ def test_rows_cut_into_parts(kind, batch, n, ld, k):
         np.testing.assert_array_equal(val.view(np.uint32), np.take_along_axis(x, want, 1).view(np.uint32))
 
 
+@pytest.mark.parametrize("kind", KINDS + ["uniform", "shifted", "descending", "sparse"])
+@pytest.mark.parametrize("batch,n,k", [(2, 20481, 250), (3, 100001, 60), (2, 100001, 500), (1, 131072, 1500), (2, 262111, 58)])
+def test_rows_whose_parts_overflow(kind, batch, n, k):
+    """Rows of which the parts cannot list all elements near their bounds: values that share their first digits, equal ones (also
+    where only some of a row's are taken), neighbours; k below and above what each part lists."""
+    rng = np.random.default_rng(n + k)
+    if kind == "uniform":
+        x = rng.random((batch, n), dtype=np.float32)
+    elif kind == "shifted":
+        x = (rng.standard_normal((batch, n)) - 10).astype(np.float32)
+    elif kind == "descending":
+        x = -np.sort(-rng.standard_normal((batch, n)).astype(np.float32), axis=1)
+    elif kind == "sparse":                    # fewer than k above a run of equal values
+        x = np.maximum(rng.standard_normal((batch, n)).astype(np.float32) - np.float32(3.5), np.float32(0))
+    else:
+        x = rows(kind, batch, n, n, rng)
+    want = by_sort(x, n, k)
+    rc, idx, val, q = run_state(1, x, n, k)
+    assert rc == gemm.GEMM_OK and "parts" in q.path, q
+    np.testing.assert_array_equal(idx, want)
+    np.testing.assert_array_equal(val.view(np.uint32), np.take_along_axis(x, want, 1).view(np.uint32))
+
+
 def test_parts_of_more_rows_than_slots_on_several_streams_and_under_a_graph():
     """Eight streams with 32 rows each in flight at once: rows whose slot another call holds are read uncut, and every result
     is the same; so is that of a graph, replayed among them."""
