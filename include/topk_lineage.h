@@ -26,8 +26,10 @@
  * and query results are HOST memory; nothing is allocated, no state is kept from call to call (the parts of
  * cut rows meet in device memory that belongs to the loaded library, 4 MiB, in slots held while the call runs;
  * a row that finds its slot taken by a call on another stream is read uncut); launches are asynchronous
- * on the given stream; errors are gemm_status_t values; on any status other than GEMM_OK nothing was
- * launched; a state whose conditions do not hold is refused with GEMM_ERR_PRECONDITION.
+ * on the given stream; errors are gemm_status_t values; on any status other than GEMM_OK and
+ * GEMM_ERR_LAUNCH nothing was launched (after the latter, which can come between the two launches that
+ * cut rows take, idx and val are unspecified and no slot stays held); a state whose conditions do not
+ * hold is refused with GEMM_ERR_PRECONDITION.
  */
 #ifndef TOPK_LINEAGE_H
 #define TOPK_LINEAGE_H

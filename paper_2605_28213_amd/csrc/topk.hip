@@ -978,6 +978,15 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
     long_row_general(a, row, sh);
 }
 
+// Gives the slots back that topk_parts has claimed, one workgroup per row, when topk_merge could not be launched.
+__global__ void topk_give_back(TopkArgs a, PartArgs p)
+{
+    PartSlot& slot = part_slots[(p.first_slot + blockIdx.x) % PART_SLOTS];
+    if (threadIdx.x != 0 || slot.owner != (unsigned long long)(uintptr_t)(a.idx + (int64_t)blockIdx.x * a.k)) return;
+    __hip_atomic_store(&slot.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&slot.owner, 0ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Which rows are cut: up to 32 of them (beyond, one workgroup per row has enough CUs: uncut / cut, k = 16, 64 x 32768 16.1 /
 // 16.0 us, 64 x 131072 26.4 / 32.6, 128 x 131072 29.1 / 52.0), longer than the resident state takes.  Uncut / cut: 1 x 17000,
 // k = 16, 14.8 / 10.4; 24 x 24000, k = 200, 21.8 / 14.8; 8 x 131072, k = 64, 26.9 / 15.2; 1 x 200000, k = 16, 27.3 / 14.1; 24 x
@@ -1094,13 +1103,22 @@ int topk_run(int variant, const topk_desc_t* d, const float* x, int32_t* idx, fl
     if (p.status != GEMM_OK) return p.status;
     if (p.empty) return GEMM_OK;
     (void)hipGetLastError();
+    hipError_t e = hipSuccess;
     const dim3 grid((unsigned)d->batch);
     if (variant == TOPK_T0_SELECTION)
         hipLaunchKernelGGL(topk_selection, grid, dim3(SEL_T), 0, p.stream, p.a);
     else if (p.parts.parts > 0) {
         p.parts.first_slot = part_ticket.fetch_add((unsigned)d->batch, std::memory_order_relaxed);
         hipLaunchKernelGGL(topk_parts, dim3((unsigned)p.q.grid), dim3(LONG_T), 0, p.stream, p.a, p.parts);
-        hipLaunchKernelGGL(topk_merge, grid, dim3(LONG_T), 0, p.stream, p.a, p.parts);
+        e = hipGetLastError();
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(topk_merge, grid, dim3(LONG_T), 0, p.stream, p.a, p.parts);
+            e = hipGetLastError();
+            if (e != hipSuccess) {
+                hipLaunchKernelGGL(topk_give_back, grid, dim3(64), 0, p.stream, p.a, p.parts);
+                (void)hipGetLastError();
+            }
+        }
     } else if (variant == TOPK_T1_RADIX_SELECT && p.threads == LONG_T)
         hipLaunchKernelGGL(topk_long, grid, dim3(LONG_T), 0, p.stream, p.a);
     else if (variant == TOPK_T1_RADIX_SELECT)
@@ -1109,7 +1127,7 @@ int topk_run(int variant, const topk_desc_t* d, const float* x, int32_t* idx, fl
         hipLaunchKernelGGL((topk_radix<1024, 4, true, 3, 11, 11, 10, 0>), grid, dim3(1024), 0, p.stream, p.a);
     else
         hipLaunchKernelGGL((topk_radix<1024, RES_ITEMS, true, 3, 11, 11, 10, 0>), grid, dim3(1024), 0, p.stream, p.a);
-    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) last_topk_launch_error = e;
     return e == hipSuccess ? GEMM_OK : GEMM_ERR_LAUNCH;
 }

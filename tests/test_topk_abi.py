@@ -3,6 +3,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 
 import pytest
 
@@ -96,3 +97,49 @@ def test_argument_validation():
     assert st(k=0) == gemm.GEMM_OK and st(batch=0) == gemm.GEMM_OK and st(n=0, k=0) == gemm.GEMM_OK
     assert topk.topk_query(1, topk.make_desc(2, 100, 0)).grid == 0
     assert topk.topk_run(1, topk.make_desc(2, 100, 10), None, 256, 256) == gemm.GEMM_ERR_BAD_ARG
+
+
+LAUNCHES = r'''
+#include <stdint.h>
+#include <stddef.h>
+typedef struct { uint32_t x, y, z; } dim3_t;
+static dim3_t g, b; static size_t shm; static void* st; static int error;
+int launches, fail_at; uint32_t grids[8]; const void* kernels[8]; void* streams[8];
+int __hipPushCallConfiguration(dim3_t grid, dim3_t block, size_t s, void* stream) { g = grid; b = block; shm = s; st = stream; return 0; }
+int __hipPopCallConfiguration(dim3_t* grid, dim3_t* block, size_t* s, void** stream) { *grid = g; *block = b; *s = shm; *stream = st; return 0; }
+int hipLaunchKernel(const void* f, dim3_t grid, dim3_t block, void** args, size_t s, void* stream)
+{
+    (void)block; (void)args; (void)s;
+    kernels[launches] = f; grids[launches] = grid.x; streams[launches] = stream;
+    if (++launches != fail_at) return 0;
+    error = 1;
+    return 1;
+}
+int hipGetLastError(void) { const int e = error; error = 0; return e; }
+'''
+CALLER = r'''
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)        # found before the runtime's own launch calls
+lib = ctypes.CDLL(sys.argv[2])
+class Desc(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int64) for n in ("batch", "n", "k", "ld")] + [("stream", ctypes.c_void_p), ("flags", ctypes.c_uint32), ("reserved", ctypes.c_uint32)]
+lib.topk_run.argtypes = [ctypes.c_int, ctypes.POINTER(Desc), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+count, fail_at = ctypes.c_int.in_dll(stub, "launches"), ctypes.c_int.in_dll(stub, "fail_at")
+for fail in (0, 1, 2, 3):
+    count.value, fail_at.value = 0, fail
+    rc = lib.topk_run(1, ctypes.byref(Desc(3, 20000, 9, 20000, 0x77, 0, 0)), 4096, 1 << 20, 2 << 20)
+    n = count.value
+    print(fail, rc, n, *(ctypes.c_uint32 * 8).in_dll(stub, "grids")[:n], len(set((ctypes.c_void_p * 8).in_dll(stub, "kernels")[:n])),
+          set((ctypes.c_void_p * 8).in_dll(stub, "streams")[:n]) == {0x77})
+'''
+
+
+def test_a_launch_that_fails_leaves_no_slot_of_cut_rows_claimed(tmp_path):
+    """Rows in parts take two launches.  The second is not made where the first fails, and where it fails itself a third kernel
+    gives the slots back, one workgroup per row.  The runtime's launch calls are replaced in a process of its own: no GPU."""
+    (tmp_path / "launches.c").write_text(LAUNCHES)
+    stub = tmp_path / "liblaunches.so"
+    subprocess.run(["gcc", "-shared", "-fPIC", "-Wall", "-Werror", str(tmp_path / "launches.c"), "-o", str(stub)], check=True)
+    r = subprocess.run([sys.executable, "-c", CALLER, str(stub), gemm.LIB_PATH], check=True, capture_output=True, text=True)
+    ok, bad = gemm.GEMM_OK, gemm.GEMM_ERR_LAUNCH
+    assert r.stdout.split("\n")[:4] == [f"0 {ok} 2 15 3 2 True", f"1 {bad} 1 15 1 True", f"2 {bad} 3 15 3 3 3 True", f"3 {ok} 2 15 3 2 True"]
