@@ -69,8 +69,9 @@ typedef struct {
     int32_t  passes;                    /* passes over the row's keys (histogram passes + compaction; k rounds for T0);
                                          * with T1's filter the 2, with its parts the 1, of a row whose candidates they hold, which the
                                          * query cannot know of: rows with many equal values about the k-th largest (in parts: more
-                                         * than a part has room for, and k beyond what each part lists) take up to 8 */
-    int32_t  lds_bytes;
+                                         * than a part has room for, and k beyond what each part lists) take up to 8; T2's 4 at
+                                         * most: a row with few keys in the threshold's first bin is done after 2 */
+    int32_t  lds_bytes;                 /* of a workgroup; the larger of two kernels' where rows are cut */
     int64_t  grid;
     char     path[64];
 } topk_query_t;

@@ -271,18 +271,28 @@ __device__ __forceinline__ Cut cut_of_listed(const uint32_t* keys, volatile int*
 // NPASS histogram passes over digits of B0, B1, ... bits, most significant first (they add up to 32).
 // RESIDENT: the thread's ITEMS consecutive keys are loaded once (16 bytes at a time) and every pass
 // runs from registers; otherwise every pass reads the row again (any n).
+template <int T, int BINS, bool RESIDENT>
+struct RadixShared {
+    int hist[BINS];
+    int wsum[T / 64];
+    Digit found;
+};
+template <int T, int BINS>
+struct RadixShared<T, BINS, true> : RadixShared<T, BINS, false> {
+    uint32_t few[FEW_KEYS];
+    int bins[64], listed;
+    Cut cut;
+};
 template <int T, int ITEMS, bool RESIDENT, int NPASS, int B0, int B1, int B2, int B3>
 __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
 {
     static_assert(B0 + B1 + B2 + B3 == 32 && NPASS >= 1 && NPASS <= 4, "the digits cover the key");
     constexpr int MAXB = B0 > B1 ? (B0 > B2 ? (B0 > B3 ? B0 : B3) : (B2 > B3 ? B2 : B3)) : (B1 > B2 ? (B1 > B3 ? B1 : B3) : (B2 > B3 ? B2 : B3));
     constexpr int BITS[4] = {B0, B1, B2, B3};
-    __shared__ int hist[1 << MAXB];
-    __shared__ int wsum[T / 64];
-    __shared__ Digit found;
-    __shared__ uint32_t few[RESIDENT ? FEW_KEYS : 1];
-    __shared__ int bins[64], listed;
-    __shared__ Cut cut;
+    __shared__ RadixShared<T, 1 << MAXB, RESIDENT> sh;
+    auto& hist = sh.hist;
+    auto& wsum = sh.wsum;
+    Digit& found = sh.found;
     const float* row = a.x + (int64_t)blockIdx.x * a.ld;
     const int tid = threadIdx.x;
     const int64_t n = a.n;
@@ -308,7 +318,10 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
             }
         }
     }
-    if (tid == 0) { found = Digit{0, 0, 0}; listed = 0; }
+    if (tid == 0) {
+        found = Digit{0, 0, 0};
+        if constexpr (RESIDENT) sh.listed = 0;
+    }
 
     uint32_t prefix = 0, mask = 0;
     int remaining = (int)a.k, shift = 32;
@@ -342,20 +355,20 @@ __global__ __launch_bounds__(T) void topk_radix(TopkArgs a)
                 int in_digit = 0;
 #pragma unroll
                 for (int j = 0; j < ITEMS; ++j) in_digit += j < mine && (key_of(__uint_as_float(held[j])) & mask) == prefix;
-                int at = take_places(in_digit, &listed);
+                int at = take_places(in_digit, &sh.listed);
 #pragma unroll
                 for (int j = 0; j < ITEMS; ++j) {
                     const uint32_t key = key_of(__uint_as_float(held[j]));
-                    if (j < mine && (key & mask) == prefix) few[at++] = key;
+                    if (j < mine && (key & mask) == prefix) sh.few[at++] = key;
                 }
                 __syncthreads();
                 if (tid < 64) {
-                    const Cut c = cut_of_listed(few, bins, count, remaining, prefix, shift);
-                    if (tid == 0) cut = c;
+                    const Cut c = cut_of_listed(sh.few, sh.bins, count, remaining, prefix, shift);
+                    if (tid == 0) sh.cut = c;
                 }
                 __syncthreads();
-                prefix = cut.thr;
-                remaining = cut.equal;
+                prefix = sh.cut.thr;
+                remaining = sh.cut.equal;
                 break;
             }
         }
@@ -748,7 +761,7 @@ struct PartArgs { int parts, room, want, lanes; unsigned int room_inverse, first
 
 __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
 {
-    __shared__ int hist[2048];
+    __shared__ int hist[2048];              // (less than topk_merge holds)
     __shared__ int wsum[2][LONG_T / 64];
     __shared__ uint32_t few[FEW_KEYS];
     __shared__ int bins[64], listed, ok;
@@ -846,6 +859,7 @@ __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
     }
 }
 
+constexpr int MERGE_LDS = sizeof(LongShared) + PART_MAX * sizeof(uint2) + 4 * sizeof(unsigned int);     // (one struct of them all measured 0.1 us slower)
 __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
 {
     constexpr int ITEMS = PART_LIST / LONG_T;
@@ -1051,7 +1065,7 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
         p.parts = parts_of(d->batch, d->n, d->k);
         if (p.parts.parts > 0) {
             path = "parts of 4096 listed and merged, else group-maxima filter";
-            p.threads = LONG_T; q.passes = 1; q.lds_bytes = 2048 * 4 + FEW_KEYS * 4 + 64 * 4 + 160;
+            p.threads = LONG_T; q.passes = 1; q.lds_bytes = MERGE_LDS;
             break;
         }
         // (the lines: see topk_long; a launch holds fewer than 2^32 threads, so 2^22 rows and more stay with 256 lanes each)
@@ -1062,7 +1076,7 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
             break;
         }
         path = "radix-select(8+8+8+8, streaming)";
-        p.threads = 256; q.passes = 5; q.lds_bytes = 256 * 4 + 24;
+        p.threads = 256; q.passes = 5; q.lds_bytes = sizeof(RadixShared<256, 256, false>);
         break;
     default:
         required = TOPK_COND_ROW_IN_REGISTERS | TOPK_COND_ALIGN16;
@@ -1071,7 +1085,7 @@ Plan make_plan(int variant, const topk_desc_t* d, const float* x, const void* id
         p.threads = 1024;
         p.items = d->n <= 1024 * 4 ? 4 : RES_ITEMS;
         path = p.items == 4 ? "radix-select(11+11+10, 4 keys/lane x 1024)" : "radix-select(11+11+10, 16 keys/lane x 1024)";
-        q.passes = 4; q.lds_bytes = 2048 * 4 + 72;
+        q.passes = 4; q.lds_bytes = sizeof(RadixShared<1024, 2048, true>);
         break;
     }
     q.required = required; q.holds = holds; q.violated = required & ~holds;

@@ -143,3 +143,14 @@ def test_a_launch_that_fails_leaves_no_slot_of_cut_rows_claimed(tmp_path):
     r = subprocess.run([sys.executable, "-c", CALLER, str(stub), gemm.LIB_PATH], check=True, capture_output=True, text=True)
     ok, bad = gemm.GEMM_OK, gemm.GEMM_ERR_LAUNCH
     assert r.stdout.split("\n")[:4] == [f"0 {ok} 2 15 3 2 True", f"1 {bad} 1 15 1 True", f"2 {bad} 3 15 3 3 3 True", f"3 {ok} 2 15 3 2 True"]
+
+
+def test_reported_lds_is_what_the_kernels_were_built_with():
+    """Every form's lds_bytes against the compiler's record of its kernel; the larger of two where a call launches two."""
+    kernels = gl_build.resources()["kernels"]
+    for v, b, n, k, names in [(0, 2, 1000, 9, ["topk_selection"]), (1, 2, 1000, 9, ["topk_radix<256, 1, false"]), (1, 40, 12000, 9, ["topk_long"]),
+                              (1, 40, 70000, 9, ["topk_long"]), (1, 2, 70000, 9, ["topk_parts", "topk_merge"]), (2, 2, 4096, 9, ["topk_radix<1024, 4, true"]),
+                              (2, 2, 5000, 9, ["topk_radix<1024, 16, true"])]:
+        q = topk.topk_query(v, topk.make_desc(b, n, k))
+        built = [f["lds_bytes"] for name, f in kernels.items() if any(x in name for x in names)]
+        assert q.status == gemm.GEMM_OK and len(built) == len(names) and q.lds_bytes == max(built), (v, b, n, k, q, built)
