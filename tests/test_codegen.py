@@ -149,7 +149,7 @@ def check_wait_states_of_inline_loads(text, at_least):
     checked = 0
     for i in loads:
         assert code[i - 1].startswith("s_nop") and code[i - 2].startswith("s_mov_b32 m0"), code[i - 3:i + 1]
-        m = re.match(r"buffer_load_dwordx4 v\d+, s\[(\d+):(\d+)\], (s\d+|vcc_lo|vcc_hi) offen lds", code[i])
+        m = re.match(r"buffer_load_dwordx4 v\d+, s\[(\d+):(\d+)\], (s\d+|vcc_lo|vcc_hi) offen(?: nt)? lds", code[i])
         assert m, code[i]
         used = {"s%d" % r for r in range(int(m.group(1)), int(m.group(2)) + 1)} | {m.group(3)}
         waited, j = 0, i - 1
@@ -236,4 +236,33 @@ def test_masked_states_direct_to_lds_form(tmp_path):
         assert meta["vgpr"] <= 256 and count("v_readlane_b32") == 0 and count("v_readfirstlane_b32") <= 4, name
         assert count({"F32": "v_mfma_f32_32x32x2_f32", "F16": "v_mfma_f32_32x32x16_f16", "BF16": "v_mfma_f32_32x32x16_bf16"}[dtype]) > 0
         assert (count("ds_read_b64_tr_b16") > 0) == (dtype != "F32" and "0" in (ka, kb)), name
+    check_wait_states_of_inline_loads(text, 8 * len(names))
+
+
+def test_wide_tiles_with_loading_waves(tmp_path):
+    """Every instantiation: nothing spilled and no scratch (the 256 x 128 tiles hold up to 246 of the 256 registers that two waves
+    per SIMD have), the LDS of its rings, resources that stay in scalar registers, the loads' hand-placed wait states, the matrix
+    instruction of its type, transposing reads where an operand's rows are contiguous, and loads past the caches' replacement in the
+    form that streams B only."""
+    src = os.path.join(ROOT, "paper_2605_28213_amd", "csrc", "k4_wide.hip")
+    out = tmp_path / "wide.s"
+    flags = [f for f in gl_build.FLAGS if f != "-fPIC"] + gl_build.EXTRA_FLAGS.get("k4_wide.hip", [])
+    r = subprocess.run(["hipcc", *flags, "-S", "--cuda-device-only", src, "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    text = out.read_text()
+    names = re.findall(r"^(_ZN2gl12k4_mfma_wideINS_7WideCfgINS_(?:3F16|4BF16|4E4M3)ELi\d+ELb[01]ELb[01]ELi\d+ELb[01]E\w*):", text, flags=re.M)
+    assert len(names) == 2 * 8 + 1 + 3 * 2          # four layouts of two heights, e4m3 in one, and K ranges with and without streaming
+    for name in names:
+        dtype, bm, ka, kb, rot, nt = re.search(r"INS_\d(F16|BF16|E4M3)ELi(\d+)ELb([01])ELb([01])ELi(\d+)ELb([01])E", name).groups()
+        body = re.search(r"^%s:[^\n]*\n(.*?)\.Lfunc_end" % re.escape(name), text, flags=re.S | re.M).group(1)
+        lines = [l.strip() for l in body.split("\n") if l.strip() and not l.strip().startswith((";", "."))]
+        count = lambda o: sum(l.split()[0] == o for l in lines)
+        meta = metadata(text, name)
+        both = ka == kb == "1"
+        assert meta["vgpr_spill"] == 0 and meta["scratch"] == 0 and meta["vgpr"] <= 256 and meta["agpr"] == 0, (name, meta)
+        assert meta["lds"] == (3 * 48 if bm == "256" else 9 * 16 if both else 10 * 16) * 1024, (name, meta)
+        assert count("v_readlane_b32") == 0 and count("v_readfirstlane_b32") <= 6, name
+        assert count({"F16": "v_mfma_f32_16x16x32_f16", "BF16": "v_mfma_f32_16x16x32_bf16", "E4M3": "v_mfma_scale_f32_16x16x128_f8f6f4"}[dtype]) > 0
+        assert (count("ds_read_b64_tr_b16") > 0) == (not both), name
+        assert any(l.endswith("offen nt lds") for l in lines) == (nt == "1") and (nt == "0" or rot != "0"), name
     check_wait_states_of_inline_loads(text, 8 * len(names))
