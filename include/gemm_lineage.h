@@ -181,7 +181,11 @@ typedef struct {
                                  also where the product is then multiplied in place, which `path` shows) */
     char     path[64];        /* name of the code path gemm_run_ex would take (K4's masked state: "vec16" and "elementwise"
                                  say whether an operand's rows are aligned to 16 bytes with K contiguous or to an element
-                                 only, "(direct-to-lds)" that its loads go to LDS 16 bytes at a time all the same) */
+                                 only, "(direct-to-lds)" that its loads go to LDS 16 bytes at a time all the same; a path has
+                                 one name for the kernels of its tile sizes: threads 512 are tiles with loading waves, bm x
+                                 bn 256 x 256 in the masked state the persistent kernel.  "+splitK(n)": n partial sums are
+                                 what scratch is asked for; the ranges that run, at most n, are grid over the tiles of bm x bn.
+                                 "(rotated)": one row of tiles and a B that is streamed past the caches) */
 } gemm_query_t;
 
 /*

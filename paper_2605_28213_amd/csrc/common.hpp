@@ -127,8 +127,8 @@ size_t k4_packed_workspace_bytes(const Args& a, int keep_mask);   // keep_mask: 
 // is cut into (1: not applicable), and the fp32 scratch the partial products need.
 int k4_splitk_factor(const Args& a);
 size_t k4_splitk_workspace_bytes(const Args& a, int splits);
-int k4_splitk_wide(const Args& a);        // the ranges that the wide tiles with loading waves run (neighbours may be joined), 0: the fast kernel
-bool k4_splitk_rotates(const Args& a);    // its ranges run with a rotated K walk
+int k4_splitk_wide(const Args& a);        // the ranges that the wide tiles with loading waves run (at most the factor), 0: the factor's on the fast kernel
+bool k4_splitk_rotates(const Args& a);    // B is streamed ("(rotated)" in the path)
 // True when the fast kernel's launcher hands a thin remainder of rows (M % 256 in 1..64, where that saves a
 // round of the chip) to the streaming kernel.
 bool k4_splits_m_tail(const Args& a);

@@ -167,7 +167,9 @@ static bool k4_small_tiles_deep(const Args& a)
 // 16.1 / 12.7; fewer tiles than CUs and a short K go to smaller ones (k4_direct_takes_few_tiles).  e4m3, whose fast kernel has
 // the shorter start: 20 x 400 x 300 x 640 11.3 / 9.3, 16 x 512 x 512 x 512 8.9 / 7.7, 8 x 500 x 500 x 512 9.4 / 8.4, 40 x 256 x
 // 256 x 384 6.8 / 6.0; with 8 slabs only where more than 128 tiles share the L2s' delivery: 25 x 300 x 200 x 1024 (150 tiles)
-// 10.8 / 10.5, 2 x 1024^3 (128) 8.5 / 9.0, 2 x 150 x 150 x 1024 (8) 8.4 / 9.5.
+// 10.8 / 10.5, 2 x 1024^3 (128) 8.5 / 9.0, 2 x 150 x 150 x 1024 (8) 8.4 / 9.5.  There is no lower line on K: 2048 x 2048 x 64
+// (256 tiles, one slab) 5.3 / 5.2, x 128 6.1 / 5.5, x 256 7.9 / 6.5, x 512 9.6 / 8.7, 1536 x 1536 x 64 (144) 4.6 / 4.4, 35 x 346 x
+// 152 x 64 (210) 6.3 / 6.0; e4m3 2048 x 2048 x 128 5.4 / 5.3, x 256 6.4 / 5.9, 4 x 512 x 512 x 128 (64) 4.2 / 4.1.
 int k4_fast_wide(const Args& a)
 {
     if (a.K <= 0 || !k4_small_tiles(a)) return 0;
