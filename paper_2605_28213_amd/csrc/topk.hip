@@ -952,13 +952,14 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
             // those that may be taken: the k keys above c.thr where the cut is a clean one, and what equals it (or shares its bin,
             // many as they are) where not
             const bool clean = known && c.equal == 0;
+            const uint32_t first = clean ? c.thr + 1 : c.thr;
             int taken = 0;
 #pragma unroll
-            for (int j = 0; j < ITEMS; ++j) taken += there[j] && place_of(key[j]) + (clean ? 0 : 1) > c.thr;
+            for (int j = 0; j < ITEMS; ++j) taken += there[j] && place_of(key[j]) >= first;
             int to = take_places(taken, &sh.listed);
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j)
-                if (there[j] && place_of(key[j]) + (clean ? 0 : 1) > c.thr) {
+                if (there[j] && place_of(key[j]) >= first) {
                     sh.bits[to] = entry[j].x;
                     sh.idx[to++] = (int32_t)entry[j].y;
                 }
@@ -980,7 +981,7 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
                 return;
             }
             // (the cut as a key again; a clean one's lies above the key 0, which no number has)
-            const uint32_t from = (clean ? c.thr + 1 : c.thr) + lowest - (1u << shift);
+            const uint32_t from = first + lowest - (1u << shift);
             finish_list(a, sh, sh.listed, known, Cut{clean ? (from > 0 ? from - 1 : 0) : from, c.equal});
             return;
         }

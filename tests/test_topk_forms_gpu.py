@@ -83,6 +83,26 @@ def test_rows_whose_parts_overflow(kind, batch, n, k):
     np.testing.assert_array_equal(val.view(np.uint32), np.take_along_axis(x, want, 1).view(np.uint32))
 
 
+@pytest.mark.parametrize("nan", [0x7FFFFFFF, 0xFFFFFFFF, 0x7FC00000, 0xFF800001])
+@pytest.mark.parametrize("n,k", [(16385, 256), (20481, 300), (100001, 500)])
+def test_rows_with_nans_stay_inside_their_buffers(nan, n, k):
+    """The selection of such rows is not defined, but every index written is one of the row's and nothing beside the results is."""
+    rng = np.random.default_rng(n)
+    bits = rng.standard_normal((3, n)).astype(np.float32).view(np.uint32)
+    bits[0, ::7] = nan
+    bits[1] = nan
+    bits[2, 5:5 + k] = nan
+    x = torch.from_numpy(bits.view(np.float32)).cuda()
+    idx = torch.full((3 * k + 64,), -7, dtype=torch.int32, device="cuda")
+    val = torch.full((3 * k + 64,), -7.0, device="cuda")
+    assert topk.topk_run(1, topk.make_desc(3, n, k), x, idx[32:], val[32:]) == gemm.GEMM_OK
+    torch.cuda.synchronize()
+    for t in (idx, val):
+        assert bool((t[:32] == -7).all()) and bool((t[-32:] == -7).all())
+    inside = idx[32:-32]
+    assert bool(((inside == -7) | ((inside >= 0) & (inside < n))).all())
+
+
 def test_parts_of_more_rows_than_slots_on_several_streams_and_under_a_graph():
     """Eight streams with 32 rows each in flight at once: rows whose slot another call holds are read uncut, and every result
     is the same; so is that of a graph, replayed among them."""
