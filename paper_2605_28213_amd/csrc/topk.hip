@@ -207,27 +207,26 @@ __device__ __forceinline__ void pick_digit(const int* hist, int nb, int remainin
     __syncthreads();
 }
 
-// Adds a lane's elements to a histogram: at once for the wave where all that count fall into one bin (additions to one word of
-// LDS wait for each other: 4096 of them take 4 us).  All lanes of the wave take part.
-template <int N>
-__device__ __forceinline__ void count_bins(int* hist, const uint32_t (&bin)[N], const bool (&on)[N])
+// Adds four neighbouring elements per lane to a histogram, at once where they share a bin, and at once for the wave where all
+// of its elements do (sorted, smooth and equal rows: additions to one word of LDS wait for each other, 4096 of them 4 us).
+// All lanes of the wave take part.
+__device__ __forceinline__ void count_bins(int* hist, const uint32_t (&bin)[4], const bool (&on)[4])
 {
-    const uint32_t first = __builtin_amdgcn_readfirstlane(bin[0]);
-    bool same = !on[0] || bin[0] == first;
-    if (__all(same)) {                                      // (mostly not: the other elements are not looked at)
-#pragma unroll
-        for (int e = 1; e < N; ++e) same = same && (!on[e] || bin[e] == first);
-        if (__all(same)) {
-            int n = 0;
-#pragma unroll
-            for (int e = 0; e < N; ++e) n += __popcll(__ballot(on[e]));
-            if ((threadIdx.x & 63) == 0 && n > 0) atomicAdd(&hist[first], n);
+    const bool all = on[0] && on[1] && on[2] && on[3], alike = all && bin[0] == bin[1] && bin[1] == bin[2] && bin[2] == bin[3];
+    if (__any(alike)) {
+        const uint32_t first = __builtin_amdgcn_readfirstlane(bin[0]);
+        if (__all(alike && bin[0] == first)) {
+            if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], 4 * 64);
             return;
         }
     }
+    if (alike) {
+        atomicAdd(&hist[bin[0]], 4);
+    } else {
 #pragma unroll
-    for (int e = 0; e < N; ++e)
-        if (on[e]) atomicAdd(&hist[bin[e]], 1);
+        for (int e = 0; e < 4; ++e)
+            if (on[e]) atomicAdd(&hist[bin[e]], 1);
+    }
 }
 
 // The keys that share the k-th largest one's first digit, listed in LDS: once they are few, one wave finishes, six bits a
@@ -731,17 +730,21 @@ __global__ __launch_bounds__(LONG_T) void topk_long(TopkArgs a)
 
 // ---- T1 on few long rows ---------------------------------------------------------------------------
 // One workgroup reads a row no faster than one CU can fetch, and most CUs have no row.  Here a row is cut into parts of 4096
-// elements (blocks of 256 in turn, of 32 where a run of large values has to be shared out), a workgroup each: it keeps its elements in
+// elements (blocks of 256 in turn, of 32 where k neighbours have to be shared out), a workgroup each: it keeps its elements in
 // registers, finds its own `want`-th largest, digit by digit until few keys share what has been found, and lists its elements
 // from there up; of those that equal it, if there are more than there is room for, the first.  A second kernel, one
-// workgroup per row, finds the k largest of the lists.  For k <= want they are the row's: each part has listed its `want`
-// largest, the first of equal ones first.  For more the result is checked, not assumed: what a part has not listed lies below
-// its bound (or, where equal ones were left out, not above it), so the result holds if all k lie at or above the largest bound.
-// A row for which it does not hold is read again by the one workgroup as if it had not been cut.
-// 8 x 131072, k = 64, uncut / cut: normal values 26.8 / 15.2 us, uniform ones 29.2 / 15.5, normal around -10 27.2 / 15.2, rounded to
-// bf16 26.9 / 18.7, to halves 29.2 / 21.1, one value 392 / 49, sorted 25.8 / 18.0; k = 500, more than `want`: one value 392 / 393,
-// sorted 26.0 / 23.7.  (With the part's bound no finer than the first digit where more than 512 keys share it, and equal
-// elements beyond the room sent to the uncut form, uniform values took 36 and one value 400.)
+// workgroup per row, finds the k largest of the lists.  Where there is room for it `want` is k: each part has listed its k
+// largest, the first of equal ones first, so the row's are among them.  Otherwise it is what a part holds of k elements spread at
+// random, or of k neighbours, and the result is checked, not assumed: in the order of larger keys and then smaller indices a
+// part's list is complete down to its bound, or to the last one listed that equals it, so the result holds if k of the listed
+// elements come no later than the first of these.  A row for which they do not is read again by the one workgroup as if it had
+// not been cut.
+// 8 x 131072, k = 64, uncut / cut: normal values 26.8 / 12.5 us, uniform ones 29.1 / 13.9, normal around -10 27.3 / 12.9, rounded to
+// bf16 26.9 / 15.3, to halves 29.3 / 19.5, one value 392 / 45, sorted 25.8 / 13.9; k = 500, for which there is no room: normal
+// 38.1 / 14.4, one value 393 / 45, sorted 26.0 / 19.3; 31 x 197076, k = 1, normal 26.9 / 23.6, sorted 29.0 / 27.1.  (With 120
+// elements listed per part whatever k is, bounds no finer than the first digit where more than 512 keys share it, equal elements
+// beyond the room sent to the uncut form, and bounds joined by additions to one word of LDS: normal 15.2, uniform 36, one value
+// 400, sorted 18.0 and for k = 500 42; 31 x 197076 29.4 and 46.)
 //
 // The lists are device memory of the loaded library (one copy per GPU, held until the process ends), because the interface
 // lends no scratch.  A call's rows take consecutive slots from a ticket; the first part to arrive claims the row's slot for the
@@ -754,6 +757,7 @@ struct PartSlot {
     unsigned long long owner;           // address of the row's indices, 0: free
     unsigned int arrived;
     uint2 part[PART_MAX];               // elements from the bound up (as many are listed as there is room for) and bound of each part
+    unsigned int last[PART_MAX];        // where they are more: index of the last one listed that equals the bound
     uint2 list[PART_LIST];              // pattern and index; part i's begin at i * room
 };
 __device__ PartSlot part_slots[PART_SLOTS];
@@ -787,12 +791,15 @@ __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
     hist[tid] = hist[LONG_T + tid] = 0;
     __syncthreads();
     if (!ok) return;
-    uint32_t key[4];
+    uint32_t key[4], bin[4];
+    bool on[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         key[e] = key_of(held[e]);
-        if (e < there) atomicAdd(&hist[key[e] >> 21], 1);
+        bin[e] = key[e] >> 21;
+        on[e] = e < there;
     }
+    count_bins(hist, bin, on);
     __syncthreads();
     pick_digit<LONG_T>(hist, 2048, p.want, wsum[0], &found);
     // the elements of the digit found and of those above it, where there is room for them; else from the want-th largest up
@@ -802,8 +809,6 @@ __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
         const int low = shift > 11 ? shift - 11 : 0, bits = shift - low;
         hist[tid] = hist[LONG_T + tid] = 0;
         __syncthreads();
-        uint32_t bin[4];
-        bool on[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             bin[e] = (key[e] >> low) & ((1u << bits) - 1);
@@ -849,6 +854,7 @@ __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
         for (int e = 0; e < 4; ++e) {
             const bool is_gt = e < there && key[e] > bound, is_eq = e < there && key[e] == bound;
             if (is_gt || (is_eq && e0 < keep)) list[g + (e0 < keep ? e0 : keep)] = make_uint2(__float_as_uint(held[e]), (uint32_t)(first + e));
+            if (is_eq && e0 == keep - 1) slot.last[part] = (unsigned)(first + e);
             g += is_gt;
             e0 += is_eq;
         }
@@ -859,13 +865,14 @@ __global__ __launch_bounds__(LONG_T) void topk_parts(TopkArgs a, PartArgs p)
     }
 }
 
-constexpr int MERGE_LDS = sizeof(LongShared) + PART_MAX * sizeof(uint2) + 4 * sizeof(unsigned int);     // (one struct of them all measured 0.1 us slower)
+constexpr int MERGE_LDS = sizeof(LongShared) + PART_MAX * sizeof(uint2) + 5 * sizeof(unsigned int);     // (one struct of them all measured 0.1 us slower)
 __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
 {
     constexpr int ITEMS = PART_LIST / LONG_T;
     __shared__ LongShared sh;
     __shared__ uint2 part[PART_MAX];
-    __shared__ unsigned int lowest, largest_bound, highest, tied;
+    __shared__ unsigned long long bound;
+    __shared__ unsigned int lowest, highest, tied;
     const int tid = threadIdx.x;
     const float* row = a.x + (int64_t)blockIdx.x * a.ld;
     PartSlot& slot = part_slots[(p.first_slot + blockIdx.x) % PART_SLOTS];
@@ -874,21 +881,28 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
     const unsigned long long owner = slot.owner;
     const unsigned int arrived = slot.arrived;
     const uint2 mine = tid < PART_MAX ? slot.part[tid] : make_uint2(0, 0);
+    const unsigned int last = tid < PART_MAX ? slot.last[tid] : 0;
     uint2 entry[ITEMS];
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) entry[j] = slot.list[j * LONG_T + tid];
-    if (tid == 0) { sh.found = Digit{0, 0, 0}; sh.listed = sh.few = 0; lowest = ~0u; largest_bound = highest = tied = 0; }
     sh.hist[tid] = sh.hist[LONG_T + tid] = 0;
-    __syncthreads();
     const bool held = owner == tag;
-    // from which key up a part's list holds all that the k largest may be
-    auto left_out = [&](uint2 of) { return of.x > (unsigned)p.room && a.k > p.want; };
-    auto complete_from = [&](uint2 of) { return a.k <= p.want ? 0u : left_out(of) ? of.y + 1 : of.y; };
+    // An element's place in the order of the row, larger keys and then smaller indices first.  For k > want: from which place on
+    // all parts' lists are complete.
+    auto order_of = [](uint32_t key, uint32_t index) { return (unsigned long long)key << 32 | ~index; };
+    const bool left_out = mine.x > (unsigned)p.room;
     if (tid < PART_MAX) {
+        static_assert(PART_MAX == 64, "a part per lane of one wave");
+        const bool is_part = tid < p.parts;
+        const uint32_t key = __builtin_amdgcn_readlane(wave_max(is_part ? mine.y : 0u), 63), low = ~__builtin_amdgcn_readlane(wave_max(is_part ? ~mine.y : 0u), 63);
+        const uint32_t index = ~__builtin_amdgcn_readlane(wave_max(is_part && left_out && mine.y == key ? ~last : 0u), 63);
         part[tid] = mine;
-        if (held && tid < p.parts) {
-            atomicMin(&lowest, mine.y);
-            atomicMax(&largest_bound, complete_from(mine));
+        if (tid == 0) {
+            sh.found = Digit{0, 0, 0};
+            sh.listed = sh.few = 0;
+            lowest = low;
+            bound = a.k > p.want ? order_of(key, index) : 0;
+            highest = tied = 0;
         }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                 // every wave's loads of the list have come (a barrier does not wait for them)
@@ -907,7 +921,7 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
             const unsigned i = j * LONG_T + tid, of = __umulhi(i, p.room_inverse);
             there[j] = of < (unsigned)p.parts && i - of * p.room < part[of < PART_MAX ? of : 0].x;
             key[j] = key_of(__uint_as_float(entry[j].x));
-            sure += there[j] && key[j] >= largest_bound;
+            sure += there[j] && order_of(key[j], entry[j].y) >= bound;
             if (there[j] && key[j] > top) top = key[j];
         }
         top = wave_max(top);
@@ -985,8 +999,9 @@ __global__ __launch_bounds__(LONG_T) void topk_merge(TopkArgs a, PartArgs p)
             finish_list(a, sh, sh.listed, known, Cut{clean ? (from > 0 ? from - 1 : 0) : from, c.equal});
             return;
         }
-        // the row's k-th largest lies below the largest bound: where more elements than the filter can list lie there, it is not tried
-        if (tid < p.parts && left_out(mine) && complete_from(mine) == largest_bound) atomicAdd(&tied, mine.x);
+        // the row's k-th largest lies at the key of the bound or below: where more elements than the filter can list lie from there up,
+        // it is not tried
+        if (tid < p.parts && left_out && mine.y == (unsigned)(bound >> 32)) atomicAdd(&tied, mine.x);
         __syncthreads();
     }
     if (tied <= LONG_CAP && long_row_takes_filter(a.n, a.k) && long_row_filtered(a, row, sh)) return;
@@ -1003,24 +1018,27 @@ __global__ void topk_give_back(TopkArgs a, PartArgs p)
 }
 
 // Which rows are cut: up to 32 of them (beyond, one workgroup per row has enough CUs: uncut / cut, k = 16, 64 x 32768 16.1 /
-// 16.0 us, 64 x 131072 26.4 / 32.6, 128 x 131072 29.1 / 52.0), longer than the resident state takes.  Uncut / cut: 1 x 17000,
-// k = 16, 14.8 / 10.4; 24 x 24000, k = 200, 21.8 / 14.8; 8 x 131072, k = 64, 26.9 / 15.2; 1 x 200000, k = 16, 27.3 / 14.1; 24 x
-// 200000, k = 16, 34.4 / 25.7.  More than SHORT_K elements are put in order by finish_list: their line lies where cutting paid
-// when that sorted the whole list (k = 500, 8 x 32768 21.4 / 20.0, 8 x 50000 27.0 / 20.9, now 27.2 / 15.0; 1 x 131072, k = 1500, 48.1 /
-// 17.1); with a list of candidates only it would pay from PART_FROM_N on (k = 500, 8 x 17000 15.6 / 13.8, 8 x 32768 18.9 / 14.5).
+// 16.0 us, 64 x 131072 26.4 / 32.6, 128 x 131072 29.1 / 52.0, when each part listed up to 120 elements), longer than the resident
+// state takes.  Uncut / cut: 1 x 17000, k = 16, 14.7 / 9.3; 24 x 24000, k = 200, 21.7 / 13.1; 8 x 131072, k = 64, 26.7 / 12.4; 1 x
+// 200000, k = 16, 27.4 / 10.4; 24 x 200000, k = 16, 34.7 / 21.0.  More than SHORT_K elements are put in order by finish_list: their
+// line lies where cutting paid when that sorted the whole list (k = 500, 8 x 32768 21.4 / 20.0, 8 x 50000 27.0 / 20.9, now 27.3 /
+// 12.9; 1 x 131072, k = 1500, 48.1 / 15.3); with a list of candidates only it would pay from PART_FROM_N on (8 x 17000 15.6 /
+// 13.8, 8 x 32768 18.9 / 14.5).
 constexpr int64_t PART_FROM_N = 16384, PART_FROM_N_MANY = 49152, PART_ROWS = 32;
 PartArgs parts_of(int64_t batch, int64_t n, int64_t k)
 {
     const int64_t parts = (n + PART_N - 1) / PART_N;
     if (batch < 1 || batch > PART_ROWS || n <= (k <= SHORT_K ? PART_FROM_N : PART_FROM_N_MANY) || parts > PART_MAX || k < 1) return PartArgs{};
-    const int room = (int)(PART_LIST / parts), want = room - room / 16;      // (a sixteenth is left for elements equal to the last one listed)
-    // of k elements spread at random a part holds more than this once in a million
+    const int room = (int)(PART_LIST / parts), most = room - room / 16;      // (a sixteenth is left for elements that share the last one's first digits)
+    const unsigned room_inverse = (unsigned)((((uint64_t)1 << 32) + room - 1) / room);
+    if (k <= most) return PartArgs{(int)parts, room, (int)k, 6, room_inverse, 0};
+    // Of k elements spread at random a part holds more than `spread` once in a million, of k neighbours dealt out in blocks of 32 at
+    // most `run`, and one more shows that they were all.  (Blocks of 256 are read a little faster: 32 x 50000, k = 100, 16.4 us
+    // against 16.7.)
     const double mean = (double)k / (double)parts;
-    if (k > want && mean + 5 * __builtin_sqrt(mean) + 8 > want) return PartArgs{};
-    // blocks of 256 elements are read a little faster (32 x 50000, k = 100, 16.4 us against 16.7 with blocks of 32, a line of 128
-    // bytes); with 32, at most `want` of k neighbours lie in one part: 32 times (k + 62) / 32 / parts, rounded up, for every k
-    // that gets here
-    return PartArgs{(int)parts, room, want, k <= want ? 6 : 3, (unsigned)((((uint64_t)1 << 32) + room - 1) / room), 0};
+    const int spread = (int)__builtin_ceil(mean + 5 * __builtin_sqrt(mean) + 8), run = 32 * (int)(((k + 62) / 32 + parts - 1) / parts);
+    if (spread > most || run >= most) return PartArgs{};
+    return PartArgs{(int)parts, room, spread > run ? spread : run + 1, 3, room_inverse, 0};
 }
 std::atomic<unsigned> part_ticket{0};
 
