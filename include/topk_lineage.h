@@ -70,8 +70,7 @@ typedef struct {
                                          * with T1's filter the 2, with its parts the 1, of a row whose candidates they hold, which the
                                          * query cannot know of: others (for the filter many equal values about the k-th largest, for
                                          * the parts large values crowded into few of them and more of those than one can list) take
-                                         * up to 8; T2's 4 at
-                                         * most: a row with few keys in the threshold's first bin is done after 2 */
+                                         * up to 8; T2's is 4 at most: a row with few keys in the threshold's first bin is done after 2 */
     int32_t  lds_bytes;                 /* of a workgroup; the larger of two kernels' where rows are cut */
     int64_t  grid;
     char     path[64];
